@@ -6,7 +6,8 @@
 //   pass A  GEMM over every 64th row of A; the epilogue histograms the lower
 //           bounds |c^| - margin(i,j) of the computed values (2048 monotone
 //           bins).  The lower edge tau of the bin holding the t-th largest
-//           bound is <= the t-th largest |c| over all pairs.
+//           bound is <= the t-th largest |c| over all pairs, and the count of
+//           the bins that may reach tau sizes pass B's list.
 //   pass B  GEMM over all pairs; the epilogue appends every pair with
 //           |c^| + margin(i,j) >= tau.  That set holds every pair of the
 //           exact top t.
@@ -137,6 +138,7 @@ struct GemmArgs {
   float d_f;       // d (for the eta * eta term)
   // pass A
   unsigned* hist;
+  const unsigned* maxes;  // n2, n1, eta maxima of A, then (+4) of B
   int screen;      // 1: no error margin (screening by the computed value)
   float mg_max;    // margin upper bound over all pairs (cheap pre-test)
   // pass B
@@ -200,6 +202,57 @@ __device__ __forceinline__ int fbin32(uint32_t bits) {
   return (int)(bits >> 20) & 2047;
 }
 
+// Pass A's bins of the lower bounds.  Screening takes fbin32's (their edges
+// are part of its result: the pairs it re-ranks are those above one).  The
+// certified filter's result does not depend on tau, only its survivors do,
+// so its bins are 64 per octave over the 8 octaves below the largest
+// possible |c| (bins 1536 up) and fbin32's digits below those: at 1e5 x 1e6
+// x 256 in bf16 fbin32's edge lay up to 12% under the t-th bound and let
+// 1.7e6 pairs through.  fine0 is the first fine digit (a multiple of 8, so
+// that it is a coarse edge too), -1 for screening.
+struct BoundBins {
+  int fine0;
+  __device__ __forceinline__ int bin(float v) const {
+    const uint32_t bits = __float_as_uint(v);
+    if (fine0 < 0) return fbin32(bits);
+    const int f = (int)(bits >> 17) - fine0;
+    if (f >= 0) return f < 512 ? 1536 + f : 2047;
+    const int c = 1536 - (fine0 >> 3) + (int)(bits >> 20);
+    return c > 0 ? c : 0;
+  }
+  // float bits of the bin's lower edge
+  __device__ __forceinline__ unsigned edge(int b) const {
+    if (b <= 0) return 0u;
+    if (fine0 < 0) return (unsigned)b << 20;
+    if (b >= 1536) return (unsigned)(fine0 + b - 1536) << 17;
+    const int c = b - 1536 + (fine0 >> 3);
+    return c > 0 ? (unsigned)c << 20 : 0u;
+  }
+};
+
+__device__ __forceinline__ BoundBins bound_bins(const unsigned* maxes,
+                                                int screen) {
+  BoundBins r;
+  r.fine0 = -1;
+  if (!screen) {
+    // |c| <= ||a||_2 ||b||_2 (a larger value falls in the top bin)
+    const float top = __uint_as_float(maxes[0]) * __uint_as_float(maxes[4]);
+    const int hi = (int)(__float_as_uint(top) >> 17) | 7;
+    r.fine0 = hi > 511 ? hi - 511 : 0;
+  }
+  return r;
+}
+
+// the largest margin over all pairs
+__device__ __forceinline__ float margin_max(const GemmArgs& g) {
+  if (g.screen) return 0.0f;
+  const unsigned* m = g.maxes;
+  return g.kappa * __uint_as_float(m[0]) * __uint_as_float(m[4]) +
+         g.onepu * (__uint_as_float(m[2]) * __uint_as_float(m[5]) +
+                    __uint_as_float(m[6]) * __uint_as_float(m[1])) +
+         g.d_f * __uint_as_float(m[2]) * __uint_as_float(m[6]);
+}
+
 // E8M0 byte of a vector's power-of-two inverse scale (the MFMA multiplies
 // the products of a lane's 32-element K block by 2^(byte - 127) per operand)
 __device__ __forceinline__ int e8m0_of(float inv_s) {
@@ -246,6 +299,8 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
   const char* Ab = (const char*)g.A;
   const char* Bb = (const char*)g.B;
   const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
+  BoundBins bins{-1};
+  if (HIST) bins = bound_bins(g.maxes, g.screen);
   const int64_t G = gridDim.x;  // a multiple of 8
   const int64_t v = (int64_t)(blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
   // this thread's 4 x 16 bytes of each operand's stage: rows (t >> 3) +
@@ -430,7 +485,7 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
                                       g.d_f * va.eta * vb.eta;
           if (HIST) {
             const float lo = fabsf(c) - mg;
-            if (lo > 0.0f) atomicAdd(&hist[fbin32(__float_as_uint(lo))], 1u);
+            if (lo > 0.0f) atomicAdd(&hist[bins.bin(lo)], 1u);
           } else if (fabsf(c) + mg >= tau) {
             const unsigned long long p = atomicAdd(g.ccount, 1ull);
             if ((int64_t)p < g.ccap) {
@@ -487,17 +542,43 @@ __global__ void k_vecinfo_max(const VecInfo* v, int64_t rows, unsigned* mx) {
   }
 }
 
-// lower edge (float bits) of the histogram bin holding the t-th largest
-// bound, from the top; 0 when fewer than t bounds are positive
-__global__ void k_bf_tau(const unsigned* hist, int64_t t, unsigned* tau_bits) {
-  if (threadIdx.x != 0) return;
-  unsigned long long acc = 0;
-  int b = 2047;
-  for (; b >= 0; --b) {
-    acc += hist[b];
-    if ((int64_t)acc >= t) break;
+// One wave over pass A's histogram: tau_bits = the lower edge of the bin
+// holding the t-th largest bound, from the top (0 when fewer than t bounds
+// are positive), and est = the subset's pairs that pass B's filter may
+// keep, those whose lower bound is at least tau - 2 mg_max.  (One thread
+// walking the 2048 bins took 54 us.)
+__global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g, int64_t t,
+                                               unsigned* tau_bits,
+                                               unsigned long long* est) {
+  const int lane = threadIdx.x;
+  const BoundBins bins = bound_bins(g.maxes, g.screen);
+  // lane l: bins 2047 - 32 l down to 2016 - 32 l
+  const int hi = 2047 - 32 * lane;
+  unsigned long long sum = 0;
+  for (int b = hi; b > hi - 32; --b) sum += g.hist[b];
+  const unsigned long long incl = wave_incl_scan(sum);
+  const uint64_t reach = __ballot((int64_t)incl >= t);
+  const int src = reach ? __builtin_ctzll(reach) : 63;
+  int found = 0;
+  if (reach && lane == src) {
+    unsigned long long acc = incl - sum;
+    found = hi;
+    for (; found > hi - 31; --found) {
+      acc += g.hist[found];
+      if ((int64_t)acc >= t) break;
+    }
   }
-  *tau_bits = b > 0 ? (unsigned)b << 20 : 0u;
+  found = __shfl(found, src, 64);
+  const unsigned tb = bins.edge(found);
+  const float low = __uint_as_float(tb) - 2.0f * margin_max(g);
+  const int bl = low > 0.0f ? bins.bin(low) : 0;
+  unsigned long long in = 0;
+  for (int b = hi; b > hi - 32; --b) in += b >= bl ? g.hist[b] : 0u;
+  in = wave_sum(in);
+  if (lane == 0) {
+    *tau_bits = tb;
+    *est = in;
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -618,8 +699,9 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   unsigned* tau_bits = hist + 2048;
   unsigned long long* ccount = (unsigned long long*)(hist + 2048 + 16);
   unsigned* maxes = hist + 2048 + 32;  // n2, n1, eta of A then of B
-  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8, 0ull, st)) !=
-      hipSuccess)
+  unsigned long long* est = (unsigned long long*)(hist + 2048 + 48);
+  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8 + 8, 0ull,
+                           st)) != hipSuccess)
     return e;
   k_vecinfo_max<<<64, 256, 0, st>>>((const VecInfo*)w.ia.p, m, maxes);
   k_vecinfo_max<<<64, 256, 0, st>>>((const VecInfo*)w.ib.p, n, maxes + 4);
@@ -639,6 +721,7 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   a.onepu = (float)((1 + u) * (1 + 1e-5));
   a.d_f = (float)d;
   a.hist = hist;
+  a.maxes = maxes;
   a.tau_bits = tau_bits;
   // screening (t_screen > 0, low precision): threshold and filter on the
   // computed value, keep the t_screen largest, re-rank those in fp32
@@ -668,18 +751,21 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
     // pass A's subset holds about 1/stride of the pairs
     const int64_t target =
         screen ? (cap_hint + stride - 1) / stride : t;
-    k_bf_tau<<<1, 64, 0, st>>>(hist, target, tau_bits);
+    k_bf_tau<<<1, 64, 0, st>>>(a, target, tau_bits, est);
   }
   (void)hipEventRecord(ev[1], st);
-  // the largest margin over all pairs, for pass B's pre-test
+  // the largest margin over all pairs, for pass B's pre-test, and pass A's
+  // estimate of its survivors
+  unsigned long long sub = 0;
   {
-    unsigned mxb[8];
+    unsigned mxb[18];
     if ((e = hipMemcpyAsync(mxb, maxes, sizeof mxb, hipMemcpyDeviceToHost,
                             st)) != hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
       return e;
     float f[8];
     memcpy(f, mxb, sizeof f);
+    memcpy(&sub, mxb + 16, 8);
     const double mgm = screen ? 0.0
                               : (double)a.kappa * f[0] * f[4] +
                                     (double)a.onepu * (f[2] * f[5] + f[6] * f[1]) +
@@ -689,6 +775,20 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   // pass B over all pairs
   int64_t cap = screen ? 4 * cap_hint : (cap_hint > 0 ? cap_hint : (1 << 20));
   if (cap < 16 * t) cap = 16 * t;
+  // room for what pass A's subset (1 / stride of the rows) lets expect, a
+  // quarter and four standard deviations over it: a list that overflows
+  // costs the whole GEMM again (1e5 x 1e6 x 256 in bf16, t = 1000: 153.8
+  // ms a call with two runs, 70.6 with one).  Above 2^26 pairs the estimate is not followed: the first
+  // run counts the pairs exactly before that much memory is taken.
+  const double want = ((double)sub * 1.25 + 4.0 * sqrt((double)sub)) *
+                          (double)stride + 1024.0;
+  if (want > (double)cap && want <= (double)(int64_t(1) << 26))
+    cap = (int64_t)want;
+  // a longer list that the workspace holds already is used as it is
+  const int64_t have = (int64_t)(w.keys.bytes / 8 < w.vals.bytes / 4
+                                     ? w.keys.bytes / 8
+                                     : w.vals.bytes / 4);
+  if (cap < have) cap = have;
   a.m_rows = m;
   a.a_stride_rows = 1;
   a.m_key = 1;
