@@ -1,0 +1,192 @@
+// bf_common.hpp -- what the brute-force kernels share: precisions, the GEMM
+// arguments, the bins of pass A and the conversions of the inputs.
+#pragma once
+
+#include "mad_common.hpp"
+#include "plan.hpp"
+
+namespace mad {
+
+typedef float f16v __attribute__((ext_vector_type(16)));
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef int i8v __attribute__((ext_vector_type(8)));
+
+enum Prec { kF32 = 0, kBF16 = 1, kFP8 = 2 };
+
+// element bytes, k per MFMA, k per LDS chunk (a 128-byte row slice)
+template <int P> struct PrecT;
+template <> struct PrecT<kF32> {
+  static constexpr int EB = 4, KS = 2, KC = 32;
+};
+template <> struct PrecT<kBF16> {
+  static constexpr int EB = 2, KS = 16, KC = 64;
+};
+template <> struct PrecT<kFP8> {
+  static constexpr int EB = 1, KS = 64, KC = 128;
+};
+
+__device__ __forceinline__ uint8_t to_fp8(float x) {
+  // round to nearest even into e4m3; |x| < 2^7 after scaling
+  const unsigned pk = __builtin_amdgcn_cvt_pk_fp8_f32(x, 0.0f, 0, false);
+  return (uint8_t)(pk & 0xff);
+}
+
+__device__ __forceinline__ uint16_t to_bf16(float x) {
+  // round to nearest even (inputs are finite)
+  uint32_t u = __float_as_uint(x);
+  u += 0x7FFFu + ((u >> 16) & 1u);
+  return (uint16_t)(u >> 16);
+}
+
+// norms, rounding floor and scale of one vector from its sums and largest |x|
+template <int P>
+__device__ __forceinline__ VecInfo vec_info(double s2, double s1, float mx) {
+  float scale = 1.0f, eta = 0.0f;
+  if (P == kFP8) {
+    int e = 0;
+    if (mx > 0.0f) (void)frexpf(mx, &e);  // mx < 2^e
+    // scaled max < 2^7; 1 / scale stays a normal float (an E8M0 exponent)
+    if (e < -119) e = -119;
+    scale = ldexpf(1.0f, 7 - e);
+    eta = ldexpf(1.0f, -10) / scale;      // half the e4m3 subnormal step
+  } else if (P == kBF16) {
+    eta = ldexpf(1.0f, -134);
+  }
+  VecInfo vi;
+  vi.n2 = (float)(sqrt(s2) * (1.0 + 1e-6));
+  vi.n1 = (float)(s1 * (1.0 + 1e-6));
+  vi.eta = eta;
+  vi.inv_s = 1.0f / scale;
+  return vi;
+}
+
+// the scale that vec_info took (a power of two, so its inverse is exact)
+template <int P>
+__device__ __forceinline__ float vec_scale(const VecInfo& vi) {
+  return P == kFP8 ? 1.0f / vi.inv_s : 1.0f;
+}
+
+__device__ __forceinline__ float wave_max(float v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, 64));
+  return v;
+}
+
+struct GemmArgs {
+  const void* A;  // rows of Kp elements
+  const void* B;
+  const VecInfo* ia;
+  const VecInfo* ib;
+  int64_t m_rows;  // rows of A used
+  int64_t a_stride_rows;  // A row i of this pass is row i*stride of the copy
+  int64_t m_key;   // row index multiplier for keys (= stride)
+  int64_t n, Kp;
+  float kappa;     // relative margin factor on ||a||_2 ||b||_2
+  float onepu;     // 1 + u
+  float d_f;       // d (for the eta * eta term)
+  // pass A
+  unsigned* hist;
+  const unsigned* maxes;  // n2, n1, eta maxima of A, then (+4) of B
+  int screen;      // 1: no error margin (screening by the computed value)
+  float mg_max;    // margin upper bound over all pairs (cheap pre-test)
+  // pass B
+  const unsigned* tau_bits;  // lower bound (float bits)
+  float* cval;     // computed value of each survivor
+  uint64_t* ckey;
+  int64_t ccap;
+  unsigned long long* ccount;
+};
+
+// monotone 11-bit digit of a non-negative float (exponent and the top 3
+// mantissa bits); bin b holds the floats with bits in [b << 20, (b+1) << 20)
+__device__ __forceinline__ int fbin32(uint32_t bits) {
+  return (int)(bits >> 20) & 2047;
+}
+
+// Pass A's bins of the lower bounds.  Screening takes fbin32's (their edges
+// are part of its result: the pairs it re-ranks are those above one).  The
+// certified filter's result does not depend on tau, only its survivors do,
+// so its bins are 64 per octave over the 8 octaves below the largest
+// possible |c| (bins 1536 up) and fbin32's digits below those: at 1e5 x 1e6
+// x 256 in bf16 fbin32's edge lay up to 12% under the t-th bound and let
+// 1.7e6 pairs through.  fine0 is the first fine digit (a multiple of 8, so
+// that it is a coarse edge too), -1 for screening.
+struct BoundBins {
+  int fine0;
+  __device__ __forceinline__ int bin(float v) const {
+    const uint32_t bits = __float_as_uint(v);
+    if (fine0 < 0) return fbin32(bits);
+    const int f = (int)(bits >> 17) - fine0;
+    if (f >= 0) return f < 512 ? 1536 + f : 2047;
+    const int c = 1536 - (fine0 >> 3) + (int)(bits >> 20);
+    return c > 0 ? c : 0;
+  }
+  // float bits of the bin's lower edge
+  __device__ __forceinline__ unsigned edge(int b) const {
+    if (b <= 0) return 0u;
+    if (fine0 < 0) return (unsigned)b << 20;
+    if (b >= 1536) return (unsigned)(fine0 + b - 1536) << 17;
+    const int c = b - 1536 + (fine0 >> 3);
+    return c > 0 ? (unsigned)c << 20 : 0u;
+  }
+};
+
+__device__ __forceinline__ BoundBins bound_bins(const unsigned* maxes,
+                                                int screen) {
+  BoundBins r;
+  r.fine0 = -1;
+  if (!screen) {
+    // |c| <= ||a||_2 ||b||_2 (a larger value falls in the top bin)
+    const float top = __uint_as_float(maxes[0]) * __uint_as_float(maxes[4]);
+    const int hi = (int)(__float_as_uint(top) >> 17) | 7;
+    r.fine0 = hi > 511 ? hi - 511 : 0;
+  }
+  return r;
+}
+
+// the largest margin over all pairs
+__device__ __forceinline__ float margin_max(const GemmArgs& g) {
+  if (g.screen) return 0.0f;
+  const unsigned* m = g.maxes;
+  return g.kappa * __uint_as_float(m[0]) * __uint_as_float(m[4]) +
+         g.onepu * (__uint_as_float(m[2]) * __uint_as_float(m[5]) +
+                    __uint_as_float(m[6]) * __uint_as_float(m[1])) +
+         g.d_f * __uint_as_float(m[2]) * __uint_as_float(m[6]);
+}
+
+// E8M0 byte of a vector's power-of-two inverse scale (the MFMA multiplies
+// the products of a lane's 32-element K block by 2^(byte - 127) per operand)
+__device__ __forceinline__ int e8m0_of(float inv_s) {
+  return (int)((__float_as_uint(inv_s) >> 23) & 0xff);
+}
+
+// launch of the register-panel GEMM (bf_panel*.hip): pass A (hist) or pass B
+// over fragment-ordered copies of A and B
+struct PanelArgs {
+  GemmArgs g;
+  int64_t tiles_n;   // column tiles
+  int64_t panels;    // row panels
+  int64_t seg;       // column tiles per work item
+  int64_t items;     // panels x segments
+  int64_t target;    // pass A: rank of the bound that tau is taken at
+  const int* sb;     // fp8: E8M0 bytes of B's vectors (padded rows too)
+  unsigned* thr;     // pass A: running lower bound (float bits)
+};
+
+// steps of 16 bytes per lane that a vector of d coordinates takes in the
+// fragment order, rounded up to a built kernel; 0: no panel kernel for d
+int panel_steps(int prec, int64_t d);
+// bytes of `rows` vectors in the fragment order (rows padded to 128)
+int64_t panel_bytes(int prec, int64_t d, int64_t rows);
+hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
+                         void* out, VecInfo* info, int* scale, hipStream_t st);
+hipError_t launch_panel(const GemmArgs& a, int prec, int64_t d, bool hist,
+                        int64_t target, const int* sb, unsigned* thr,
+                        hipStream_t st);
+// per-precision launches (one file each)
+hipError_t launch_panel_bf16(const PanelArgs& a, int ns, bool hist,
+                             unsigned grid, hipStream_t st);
+hipError_t launch_panel_fp8(const PanelArgs& a, int ns, bool hist,
+                            unsigned grid, hipStream_t st);
+
+}  // namespace mad

@@ -1,0 +1,318 @@
+// bf_panel.hpp -- the brute force's GEMM for short vectors: each wave keeps
+// its 64 rows of A in registers for all of K and streams the columns of B
+// through LDS.
+//
+// What bounds a GEMM of K <= 256 here is not the matrix cores but feeding
+// them: with both operands of a 64 x 64 wave tile read from LDS, each MFMA
+// (32 cycles) needs one 1 KB fragment, and four SIMDs then ask for all of
+// the LDS's 128 bytes per cycle; bf16 and fp8 stood at 0.29 of peak.  With
+// the rows of A in registers (K x 64 rows: 128 VGPRs at K = 256 in bf16) a
+// fragment of B serves two MFMAs, so LDS reads take half its rate, and a
+// stage is a whole column tile (64 or 128 columns, all of K): one barrier
+// per 32 or more MFMAs of each wave.
+//
+// Both copies are stored in fragment order: the 1 KB that a wave's MFMA
+// operand takes (32 vectors x one K step, 16 bytes per lane) is contiguous,
+// lane by lane.  A column tile is then one contiguous run of memory, goes
+// to LDS by direct 16-byte loads without passing registers, and is read
+// back without bank conflicts at immediate offsets.
+#pragma once
+
+#include "bf_common.hpp"
+
+namespace mad {
+
+typedef int i4v __attribute__((ext_vector_type(4)));
+
+constexpr int kPanelRows = 256;  // rows of A per workgroup (4 waves x 64)
+
+// column blocks of 32 per tile: a tile is at most 32 KB, two buffers and two
+// workgroups per CU
+constexpr int panel_tile_blocks(int ns) { return ns <= 8 ? 4 : 2; }
+
+// bytes [16 lane, 16 lane + 16) of dst (wave-uniform) from src (per lane)
+__device__ __forceinline__ void lds_load16(const char* src, char* dst) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void*)src,
+      (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+}
+
+__device__ __forceinline__ void lds_load4(const int* src, int* dst) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void*)src,
+      (__attribute__((address_space(3))) void*)dst, 4, 0, 0);
+}
+
+// one MFMA operand per lane: step s of a block's fragments (two steps in fp8)
+template <int P> struct PanelFrag { typedef bf8v T; };
+template <> struct PanelFrag<kFP8> { typedef i8v T; };
+
+template <int P>
+__device__ __forceinline__ typename PanelFrag<P>::T frag_at(const i4v* p,
+                                                            int s) {
+  if constexpr (P == kFP8) {
+    const i4v x = p[2 * s * 64], y = p[(2 * s + 1) * 64];
+    return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+  } else {
+    return __builtin_bit_cast(bf8v, p[s * 64]);
+  }
+}
+
+// NS: steps of 16 bytes per lane (bf16: 16 coordinates and one MFMA each;
+// fp8: 32 coordinates, one MFMA per two steps).  HIST: pass A.
+template <int P, int NS, bool HIST>
+__global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
+  constexpr int TB = panel_tile_blocks(NS);
+  constexpr int NM = P == kFP8 ? NS / 2 : NS;  // MFMAs per 32 x 32 block
+  constexpr int kTile = TB * NS * 1024;        // bytes of a column tile
+  __shared__ __attribute__((aligned(16))) char buf0[kTile];
+  __shared__ __attribute__((aligned(16))) char buf1[kTile];
+  __shared__ int sc0[P == kFP8 ? TB * 32 : 1];
+  __shared__ int sc1[P == kFP8 ? TB * 32 : 1];
+  __shared__ unsigned hist[HIST ? 2048 : 1];
+  __shared__ unsigned thr_s;
+  const GemmArgs& g = a.g;
+  const int t = threadIdx.x, lane = t & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+  const int rl = lane & 31, rg = lane >> 5;
+  BoundBins bins{-1};
+  float mg2 = 0.0f;  // pass A keeps what may reach tau after the margins
+  if (HIST) {
+    bins = bound_bins(g.maxes, g.screen);
+    mg2 = 2.0f * margin_max(g);
+    for (int b = t; b < 2048; b += 256) hist[b] = 0;
+    if (t == 0) thr_s = 0u;
+    __syncthreads();
+  }
+  const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
+  // |c| below `pre` is dropped at once.  Pass B: |c| + margin >= tau only
+  // when |c| >= tau - mg_max, and tau (1 - 2^-20) absorbs the roundings of
+  // both comparisons.  Pass A: `pre` follows the bound that this workgroup
+  // or another already holds `target` values above.
+  float pre = HIST ? 0.0f : fmaf(tau, 1.0f - 0x1p-20f, -g.mg_max);
+  // Work items (a row panel x a run of column tiles) in segment-major
+  // order; each XCD takes a contiguous share, so that the workgroups of one
+  // L2 stream the same columns at the same time.
+  const int64_t G = gridDim.x >> 3;  // workgroups per XCD
+  const int64_t xcd = blockIdx.x & 7;
+  const int64_t lo = a.items * xcd / 8, hi = a.items * (xcd + 1) / 8;
+  int64_t item = lo + (blockIdx.x >> 3);
+  const char* Ab = (const char*)g.A;
+  const char* Bb = (const char*)g.B;
+  typedef typename PanelFrag<P>::T frag_t;
+  frag_t fa[2][NM];
+  int sa[2] = {127, 127};
+  int64_t i0 = 0, tile = 0, tend = 0;
+  auto locate = [&](int64_t it) {
+    const int64_t seg = it / a.panels;
+    i0 = (it - seg * a.panels) * kPanelRows + wv * 64;
+    tile = seg * a.seg;
+    tend = tile + a.seg < a.tiles_n ? tile + a.seg : a.tiles_n;
+  };
+  auto load_a = [&]() {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      int64_t i = i0 + u * 32 + rl;
+      i = (i < g.m_rows ? i : g.m_rows - 1) * g.a_stride_rows;
+      const i4v* p = (const i4v*)(Ab + (i >> 5) * (NS * 1024)) + rg * 32 +
+                     (i & 31);
+#pragma unroll
+      for (int s = 0; s < NM; ++s) fa[u][s] = frag_at<P>(p, s);
+      if (P == kFP8) sa[u] = e8m0_of(g.ia[i].inv_s);
+    }
+    // the rows are waited for here (once per item), so that no wait for
+    // them stands in the tile loop, where it would also wait for the next
+    // tile's loads
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+  };
+  // the tile's 1 KB fragments, shared out over the four waves
+  auto fetch = [&](int64_t tl, char* dst, int* sdst) {
+    const char* src = Bb + tl * kTile + lane * 16;
+#pragma unroll
+    for (int q = 0; q < (TB * NS + 3) / 4; ++q) {
+      const int f = q * 4 + wv;
+      if ((TB * NS) % 4 == 0 || f < TB * NS)
+        lds_load16(src + f * 1024, dst + f * 1024);
+    }
+    if (P == kFP8 && wv < TB / 2)
+      lds_load4(a.sb + tl * (TB * 32) + wv * 64 + lane, sdst + wv * 64);
+  };
+  // the kept values of one 64 x 32 block
+  auto emit = [&](const f16v& c0, const f16v& c1, int64_t j) {
+    if (j >= g.n) return;
+    const VecInfo vb = g.ib[j];
+    // an opaque copy of the lane's first row: without it the 32 rows'
+    // addresses are computed ahead of the tile loop and spill
+    int row = 4 * rg;
+    asm volatile("" : "+v"(row));
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) {
+        const float c = u ? c1[e] : c0[e];
+        if (!(fabsf(c) >= pre)) continue;
+        const int64_t i = i0 + (u * 32 + 8 * (e >> 2) + (e & 3) + row);
+        if (i >= g.m_rows) continue;
+        float mg = 0.0f;
+        if (!g.screen) {
+          const VecInfo va = g.ia[i * g.a_stride_rows];
+          mg = g.kappa * va.n2 * vb.n2 +
+               g.onepu * (va.eta * vb.n1 + vb.eta * va.n1) +
+               g.d_f * va.eta * vb.eta;
+        }
+        if (HIST) {
+          const float low = fabsf(c) - mg;
+          if (low > 0.0f) atomicAdd(&hist[bins.bin(low)], 1u);
+        } else if (fabsf(c) + mg >= tau) {
+          const unsigned long long p = atomicAdd(g.ccount, 1ull);
+          if ((int64_t)p < g.ccap) {
+            g.ckey[p] = (uint64_t)(i * g.m_key) * (uint64_t)g.n + (uint64_t)j;
+            g.cval[p] = c;
+          }
+        }
+      }
+  };
+  auto compute = [&](const char* buf, const int* sc, int64_t tl) {
+    const f16v zero = {};
+#pragma unroll 1
+    for (int cb = 0; cb < TB; ++cb) {
+      const i4v* fb = (const i4v*)(buf + cb * (NS * 1024)) + lane;
+      int sb = 127;
+      if (P == kFP8) sb = sc[cb * 32 + rl];
+      f16v c0, c1;
+      // kAhead operands are in flight ahead of the MFMAs that take them, in
+      // the order written (the barriers keep it: left alone, the compiler
+      // reads two fragments at a time into the same registers and waits
+      // them out before each four MFMAs)
+      constexpr int kAhead = P == kFP8 ? 2 : 4;
+      frag_t b[kAhead];
+#pragma unroll
+      for (int s = 0; s < kAhead && s < NM; ++s) b[s] = frag_at<P>(fb, s);
+#pragma unroll
+      for (int s = 0; s < NM; ++s) {
+        __builtin_amdgcn_sched_barrier(0);
+        const frag_t x = b[s % kAhead];
+        if constexpr (P == kFP8) {
+          c0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+              fa[0][s], x, s == 0 ? zero : c0, 0, 0, 0, sa[0], 0, sb);
+          c1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
+              fa[1][s], x, s == 0 ? zero : c1, 0, 0, 0, sa[1], 0, sb);
+        } else {
+          c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              fa[0][s], x, s == 0 ? zero : c0, 0, 0, 0);
+          c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+              fa[1][s], x, s == 0 ? zero : c1, 0, 0, 0);
+        }
+        if (s + kAhead < NM) b[s % kAhead] = frag_at<P>(fb, s + kAhead);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      // one max of |c| over the lane's 32 values; the per-value work runs
+      // only in waves where a lane reaches `pre`
+      float mx = 0.0f;
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        mx = fmaxf(fmaxf(mx, fabsf(c0[e])), fabsf(c1[e]));
+      if (mx >= pre) {
+        emit(c0, c1, tl * (TB * 32) + cb * 32 + rl);
+        // emit's loads end here, for the reason given in load_a
+        __builtin_amdgcn_s_waitcnt(0x0f70);
+      }
+    }
+  };
+  // pass A: the bound that `target` of this workgroup's values lie above,
+  // shared with the other workgroups
+  auto raise = [&]() {
+    __syncthreads();
+    if (wv == 0) {
+      const int top = 2047 - 32 * lane;
+      unsigned sum = 0;
+      for (int b = top; b > top - 32; --b) sum += hist[b];
+      const unsigned incl = wave_incl_scan(sum);
+      const uint64_t reach = __ballot((int64_t)incl >= a.target);
+      unsigned bits = 0;
+      if (reach) {
+        const int src = __builtin_ctzll(reach);
+        if (lane == src) {
+          unsigned acc = incl - sum;
+          int b = top;
+          for (; b > top - 31; --b) {
+            acc += hist[b];
+            if ((int64_t)acc >= a.target) break;
+          }
+          bits = bins.edge(b);
+        }
+        bits = __shfl(bits, src, 64);
+      }
+      if (lane == 0) {
+        const unsigned old = atomicMax(a.thr, bits);
+        thr_s = old > bits ? old : bits;
+      }
+    }
+    __syncthreads();
+    pre = __uint_as_float(thr_s) - mg2;
+  };
+  if (item < hi) {
+    locate(item);
+    fetch(tile, buf0, sc0);
+    load_a();
+    unsigned done = 0;
+    bool more = true;
+    // one tile: wait for its loads, start the next tile's into the other
+    // buffer (every wave has left that one at the barrier), compute
+    auto step = [&](char* cur, int* scur, char* oth, int* soth) {
+      const int64_t tl = tile;
+      int64_t nitem = item, ntile = tile + 1, ni0 = i0, nend = tend;
+      if (ntile == tend) {
+        nitem = item + G;
+        if (nitem < hi) {
+          const int64_t keep = i0;
+          locate(nitem);
+          ntile = tile;
+          ni0 = i0;
+          nend = tend;
+          i0 = keep;
+        } else {
+          more = false;
+        }
+      }
+      __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's loads
+      __syncthreads();
+      if (more) fetch(ntile, oth, soth);
+      compute(cur, scur, tl);
+      ++done;
+      if (HIST && (done & (done - 1)) == 0) raise();
+      if (more) {
+        tile = ntile;
+        tend = nend;
+        i0 = ni0;
+        if (nitem != item) {
+          item = nitem;
+          load_a();
+        }
+      }
+    };
+    while (true) {
+      step(buf0, sc0, buf1, sc1);
+      if (!more) break;
+      step(buf1, sc1, buf0, sc0);
+      if (!more) break;
+    }
+  }
+  if (HIST) {
+    __syncthreads();
+    for (int b = t; b < 2048; b += 256)
+      if (hist[b]) atomicAdd(&g.hist[b], hist[b]);
+  }
+}
+
+template <int P, int NS>
+hipError_t launch_panel_ns(const PanelArgs& a, bool hist, unsigned grid,
+                           hipStream_t st) {
+  if (hist)
+    k_gemm_panel<P, NS, true><<<grid, 256, 0, st>>>(a);
+  else
+    k_gemm_panel<P, NS, false><<<grid, 256, 0, st>>>(a);
+  return hipGetLastError();
+}
+
+}  // namespace mad

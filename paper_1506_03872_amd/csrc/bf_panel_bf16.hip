@@ -1,0 +1,23 @@
+// bf_panel_bf16.hip -- bf16 instances of the register-panel GEMM, one per
+// step count (K rounded up to 16).
+#include "bf_panel.hpp"
+
+namespace mad {
+
+hipError_t launch_panel_bf16(const PanelArgs& a, int ns, bool hist,
+                             unsigned grid, hipStream_t st) {
+  switch (ns) {
+#define MAD_PANEL_CASE(N) \
+  case N:                 \
+    return launch_panel_ns<kBF16, N>(a, hist, grid, st);
+    MAD_PANEL_CASE(1) MAD_PANEL_CASE(2) MAD_PANEL_CASE(3) MAD_PANEL_CASE(4)
+    MAD_PANEL_CASE(5) MAD_PANEL_CASE(6) MAD_PANEL_CASE(7) MAD_PANEL_CASE(8)
+    MAD_PANEL_CASE(9) MAD_PANEL_CASE(10) MAD_PANEL_CASE(11)
+    MAD_PANEL_CASE(12) MAD_PANEL_CASE(13) MAD_PANEL_CASE(14)
+    MAD_PANEL_CASE(15) MAD_PANEL_CASE(16)
+#undef MAD_PANEL_CASE
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mad

@@ -25,28 +25,11 @@
 #include <string.h>
 
 #include "../../include/mad.h"
+#include "bf_common.hpp"
 #include "mad_common.hpp"
 #include "plan.hpp"
 
 namespace mad {
-
-typedef float f16v __attribute__((ext_vector_type(16)));
-typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
-typedef int i8v __attribute__((ext_vector_type(8)));
-
-enum Prec { kF32 = 0, kBF16 = 1, kFP8 = 2 };
-
-// element bytes, k per MFMA, k per LDS chunk (a 128-byte row slice)
-template <int P> struct PrecT;
-template <> struct PrecT<kF32> {
-  static constexpr int EB = 4, KS = 2, KC = 32;
-};
-template <> struct PrecT<kBF16> {
-  static constexpr int EB = 2, KS = 16, KC = 64;
-};
-template <> struct PrecT<kFP8> {
-  static constexpr int EB = 1, KS = 64, KC = 128;
-};
 
 constexpr int kBM = 128, kBN = 128;  // workgroup tile
 constexpr int kRowBytes = 128;       // bytes of one row slice in LDS
@@ -57,19 +40,6 @@ constexpr int kLdsStride = kRowBytes + 16;
 // per-vector scale (fp8: a power of two), L2 and L1 norms of the fp32
 // vector and the absolute rounding floor eta (in the vector's own units)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint8_t to_fp8(float x) {
-  // round to nearest even into e4m3; |x| < 2^7 after scaling
-  const unsigned pk = __builtin_amdgcn_cvt_pk_fp8_f32(x, 0.0f, 0, false);
-  return (uint8_t)(pk & 0xff);
-}
-
-__device__ __forceinline__ uint16_t to_bf16(float x) {
-  // round to nearest even (inputs are finite)
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
 template <int P>
 __global__ __launch_bounds__(256) void k_prep(const float* X, int64_t rows,
                                               int64_t d, int64_t Kp,
@@ -86,29 +56,9 @@ __global__ __launch_bounds__(256) void k_prep(const float* X, int64_t rows,
     s1 += fabs(v);
     mx = fmaxf(mx, fabsf(x[k]));
   }
-  s2 = wave_sum(s2);
-  s1 = wave_sum(s1);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-  float scale = 1.0f, eta = 0.0f;
-  if (P == kFP8) {
-    int e = 0;
-    if (mx > 0.0f) (void)frexpf(mx, &e);  // mx < 2^e
-    // scaled max < 2^7; 1 / scale stays a normal float (an E8M0 exponent)
-    if (e < -119) e = -119;
-    scale = ldexpf(1.0f, 7 - e);
-    eta = ldexpf(1.0f, -10) / scale;      // half the e4m3 subnormal step
-  } else if (P == kBF16) {
-    eta = ldexpf(1.0f, -134);
-  }
-  if (lane == 0) {
-    VecInfo vi;
-    vi.n2 = (float)(sqrt(s2) * (1.0 + 1e-6));
-    vi.n1 = (float)(s1 * (1.0 + 1e-6));
-    vi.eta = eta;
-    vi.inv_s = 1.0f / scale;
-    info[r] = vi;
-  }
+  const VecInfo vi = vec_info<P>(wave_sum(s2), wave_sum(s1), wave_max(mx));
+  const float scale = vec_scale<P>(vi);
+  if (lane == 0) info[r] = vi;
   for (int64_t k = lane; k < Kp; k += 64) {
     const float v = k < d ? x[k] : 0.0f;
     if (P == kF32) ((float*)out)[r * Kp + k] = v;
@@ -124,31 +74,6 @@ __global__ __launch_bounds__(256) void k_prep(const float* X, int64_t rows,
 // (l / 32); accumulator register r of lane l is row 8(r/4) + 4(l/32) + r%4,
 // column l mod 32 of the block.
 // ---------------------------------------------------------------------------
-struct GemmArgs {
-  const void* A;  // rows of Kp elements
-  const void* B;
-  const VecInfo* ia;
-  const VecInfo* ib;
-  int64_t m_rows;  // rows of A used
-  int64_t a_stride_rows;  // A row i of this pass is row i*stride of the copy
-  int64_t m_key;   // row index multiplier for keys (= stride)
-  int64_t n, Kp;
-  float kappa;     // relative margin factor on ||a||_2 ||b||_2
-  float onepu;     // 1 + u
-  float d_f;       // d (for the eta * eta term)
-  // pass A
-  unsigned* hist;
-  const unsigned* maxes;  // n2, n1, eta maxima of A, then (+4) of B
-  int screen;      // 1: no error margin (screening by the computed value)
-  float mg_max;    // margin upper bound over all pairs (cheap pre-test)
-  // pass B
-  const unsigned* tau_bits;  // lower bound (float bits)
-  float* cval;     // computed value of each survivor
-  uint64_t* ckey;
-  int64_t ccap;
-  unsigned long long* ccount;
-};
-
 // the MFMA operands of one K step: rows (l mod 32) of the wave's two
 // 32-row blocks of A and of B, K group l / 32
 template <int P> struct Frag;
@@ -194,69 +119,6 @@ __device__ __forceinline__ void frag_mma(const Frag<P>& f, f16v (&acc)[2][2],
         acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
             f.a[bi], f.b[bj], c, 0, 0, 0, sa[bi], 0, sb[bj]);
     }
-}
-
-// monotone 11-bit digit of a non-negative float (exponent and the top 3
-// mantissa bits); bin b holds the floats with bits in [b << 20, (b+1) << 20)
-__device__ __forceinline__ int fbin32(uint32_t bits) {
-  return (int)(bits >> 20) & 2047;
-}
-
-// Pass A's bins of the lower bounds.  Screening takes fbin32's (their edges
-// are part of its result: the pairs it re-ranks are those above one).  The
-// certified filter's result does not depend on tau, only its survivors do,
-// so its bins are 64 per octave over the 8 octaves below the largest
-// possible |c| (bins 1536 up) and fbin32's digits below those: at 1e5 x 1e6
-// x 256 in bf16 fbin32's edge lay up to 12% under the t-th bound and let
-// 1.7e6 pairs through.  fine0 is the first fine digit (a multiple of 8, so
-// that it is a coarse edge too), -1 for screening.
-struct BoundBins {
-  int fine0;
-  __device__ __forceinline__ int bin(float v) const {
-    const uint32_t bits = __float_as_uint(v);
-    if (fine0 < 0) return fbin32(bits);
-    const int f = (int)(bits >> 17) - fine0;
-    if (f >= 0) return f < 512 ? 1536 + f : 2047;
-    const int c = 1536 - (fine0 >> 3) + (int)(bits >> 20);
-    return c > 0 ? c : 0;
-  }
-  // float bits of the bin's lower edge
-  __device__ __forceinline__ unsigned edge(int b) const {
-    if (b <= 0) return 0u;
-    if (fine0 < 0) return (unsigned)b << 20;
-    if (b >= 1536) return (unsigned)(fine0 + b - 1536) << 17;
-    const int c = b - 1536 + (fine0 >> 3);
-    return c > 0 ? (unsigned)c << 20 : 0u;
-  }
-};
-
-__device__ __forceinline__ BoundBins bound_bins(const unsigned* maxes,
-                                                int screen) {
-  BoundBins r;
-  r.fine0 = -1;
-  if (!screen) {
-    // |c| <= ||a||_2 ||b||_2 (a larger value falls in the top bin)
-    const float top = __uint_as_float(maxes[0]) * __uint_as_float(maxes[4]);
-    const int hi = (int)(__float_as_uint(top) >> 17) | 7;
-    r.fine0 = hi > 511 ? hi - 511 : 0;
-  }
-  return r;
-}
-
-// the largest margin over all pairs
-__device__ __forceinline__ float margin_max(const GemmArgs& g) {
-  if (g.screen) return 0.0f;
-  const unsigned* m = g.maxes;
-  return g.kappa * __uint_as_float(m[0]) * __uint_as_float(m[4]) +
-         g.onepu * (__uint_as_float(m[2]) * __uint_as_float(m[5]) +
-                    __uint_as_float(m[6]) * __uint_as_float(m[1])) +
-         g.d_f * __uint_as_float(m[2]) * __uint_as_float(m[6]);
-}
-
-// E8M0 byte of a vector's power-of-two inverse scale (the MFMA multiplies
-// the products of a lane's 32-element K block by 2^(byte - 127) per operand)
-__device__ __forceinline__ int e8m0_of(float inv_s) {
-  return (int)((__float_as_uint(inv_s) >> 23) & 0xff);
 }
 
 // Tiles of 128 x 128 in bands of 8 row-tiles; within a band the column
@@ -585,7 +447,7 @@ __global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g, int64_t t,
 // host side
 // ---------------------------------------------------------------------------
 struct BfWork {
-  DeviceBuffer ac, bc, ia, ib, misc, keys, vals, sel, selbuf, fin;
+  DeviceBuffer ac, bc, ia, ib, e8, misc, keys, vals, sel, selbuf, fin;
   int64_t m = 0, n = 0, d = 0;
   int prec = -1;
   const float* A = nullptr;
@@ -670,11 +532,23 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   int KC = prec == kF32 ? 32 : prec == kBF16 ? 64 : 128;
   int EB = prec == kF32 ? 4 : prec == kBF16 ? 2 : 1;
   const int64_t Kp = (d + KC - 1) / KC * KC;
+  const bool panel = panel_steps(prec, d) > 0;
+  const size_t abytes = panel ? (size_t)panel_bytes(prec, d, m)
+                              : (size_t)m * Kp * EB;
+  const size_t bbytes = panel ? (size_t)panel_bytes(prec, d, n)
+                              : (size_t)n * Kp * EB;
   BfWork& w = g_bf;
   const bool fresh = w.m != m || w.n != n || w.d != d || w.prec != prec ||
                      w.A != A || w.B != B;
-  if ((e = dev_alloc(w.ac, (size_t)m * Kp * EB)) != hipSuccess) return e;
-  if ((e = dev_alloc(w.bc, (size_t)n * Kp * EB)) != hipSuccess) return e;
+  if ((e = dev_alloc(w.ac, abytes)) != hipSuccess) return e;
+  if ((e = dev_alloc(w.bc, bbytes)) != hipSuccess) return e;
+  // E8M0 scales of both sides' vectors (fp8 panels), padded rows too
+  const int64_t mpad = (m + 127) / 128 * 128, npad = (n + 127) / 128 * 128;
+  if (panel && prec == kFP8 &&
+      (e = dev_alloc(w.e8, (size_t)(mpad + npad) * 4)) != hipSuccess)
+    return e;
+  int* ea8 = (int*)w.e8.p;
+  int* eb8 = ea8 + mpad;
   if ((e = dev_alloc(w.ia, (size_t)m * sizeof(VecInfo))) != hipSuccess) return e;
   if ((e = dev_alloc(w.ib, (size_t)n * sizeof(VecInfo))) != hipSuccess) return e;
   if ((e = dev_alloc(w.misc, 2048 * 4 + 512)) != hipSuccess) return e;
@@ -685,7 +559,13 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   (void)hipEventRecord(ev[0], st);
   // conversion is part of every call (the inputs may change between calls)
   const unsigned ga = (unsigned)((m + 3) / 4), gb = (unsigned)((n + 3) / 4);
-  if (prec == kF32) {
+  if (panel) {
+    if ((e = panel_prepare(A, m, d, prec, w.ac.p, (VecInfo*)w.ia.p, ea8,
+                           st)) != hipSuccess ||
+        (e = panel_prepare(B, n, d, prec, w.bc.p, (VecInfo*)w.ib.p, eb8,
+                           st)) != hipSuccess)
+      return e;
+  } else if (prec == kF32) {
     k_prep<kF32><<<ga, 256, 0, st>>>(A, m, d, Kp, w.ac.p, (VecInfo*)w.ia.p);
     k_prep<kF32><<<gb, 256, 0, st>>>(B, n, d, Kp, w.bc.p, (VecInfo*)w.ib.p);
   } else if (prec == kBF16) {
@@ -700,7 +580,8 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   unsigned long long* ccount = (unsigned long long*)(hist + 2048 + 16);
   unsigned* maxes = hist + 2048 + 32;  // n2, n1, eta of A then of B
   unsigned long long* est = (unsigned long long*)(hist + 2048 + 48);
-  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8 + 8, 0ull,
+  unsigned* thr = hist + 2048 + 64;  // pass A's running bound
+  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8 + 8 + 8, 0ull,
                            st)) != hipSuccess)
     return e;
   k_vecinfo_max<<<64, 256, 0, st>>>((const VecInfo*)w.ia.p, m, maxes);
@@ -736,6 +617,14 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   a.ckey = nullptr;
   a.ccap = 0;
   a.ccount = ccount;
+  auto gemm = [&](bool hist_pass, int64_t target) -> hipError_t {
+    if (panel)
+      return launch_panel(a, prec, d, hist_pass, target, eb8, thr, st);
+    if (prec == kF32) launch_gemm<kF32>(a, hist_pass, st);
+    else if (prec == kBF16) launch_gemm<kBF16>(a, hist_pass, st);
+    else launch_gemm<kFP8>(a, hist_pass, st);
+    return hipGetLastError();
+  };
   if (tau_user >= 0.0f) {
     // a threshold given by the caller (a lower bound it knows for the t-th
     // largest |c|): pass B keeps every pair that may reach it
@@ -745,12 +634,10 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
         hipSuccess)
       return e;
   } else {
-    if (prec == kF32) launch_gemm<kF32>(a, true, st);
-    else if (prec == kBF16) launch_gemm<kBF16>(a, true, st);
-    else launch_gemm<kFP8>(a, true, st);
     // pass A's subset holds about 1/stride of the pairs
     const int64_t target =
         screen ? (cap_hint + stride - 1) / stride : t;
+    if ((e = gemm(true, target)) != hipSuccess) return e;
     k_bf_tau<<<1, 64, 0, st>>>(a, target, tau_bits, est);
   }
   (void)hipEventRecord(ev[1], st);
@@ -801,9 +688,7 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
     a.ccap = cap;
     if ((e = launch_fill_u64((uint64_t*)ccount, 1, 0ull, st)) != hipSuccess)
       break;
-    if (prec == kF32) launch_gemm<kF32>(a, false, st);
-    else if (prec == kBF16) launch_gemm<kBF16>(a, false, st);
-    else launch_gemm<kFP8>(a, false, st);
+    if ((e = gemm(false, 0)) != hipSuccess) break;
     if ((e = hipMemcpyAsync(&count, ccount, 8, hipMemcpyDeviceToHost, st)) !=
         hipSuccess) break;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) break;
