@@ -170,7 +170,6 @@ struct PanelArgs {
   int64_t items;     // panels x segments
   int64_t target;    // pass A: rank of the bound that tau is taken at
   const int* sb;     // fp8: E8M0 bytes of B's vectors (padded rows too)
-  unsigned* thr;     // pass A: running lower bound (float bits)
 };
 
 // steps of 16 bytes per lane that a vector of d coordinates takes in the
@@ -181,12 +180,11 @@ int64_t panel_bytes(int prec, int64_t d, int64_t rows);
 hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
                          void* out, VecInfo* info, int* scale, hipStream_t st);
 hipError_t launch_panel(const GemmArgs& a, int prec, int64_t d, bool hist,
-                        int64_t target, const int* sb, unsigned* thr,
-                        hipStream_t st);
-// per-precision launches (one file each)
+                        int64_t target, const int* sb, hipStream_t st);
+// per-precision launches (one file each); grid 0: as many workgroups as fit
 hipError_t launch_panel_bf16(const PanelArgs& a, int ns, bool hist,
-                             unsigned grid, hipStream_t st);
+                             int64_t grid, hipStream_t st);
 hipError_t launch_panel_fp8(const PanelArgs& a, int ns, bool hist,
-                            unsigned grid, hipStream_t st);
+                            int64_t grid, hipStream_t st);
 
 }  // namespace mad

@@ -26,9 +26,9 @@ typedef int i4v __attribute__((ext_vector_type(4)));
 
 constexpr int kPanelRows = 256;  // rows of A per workgroup (4 waves x 64)
 
-// column blocks of 32 per tile: a tile is at most 32 KB, two buffers and two
-// workgroups per CU
-constexpr int panel_tile_blocks(int ns) { return ns <= 8 ? 4 : 2; }
+// column blocks of 32 per tile: about 16 KB up to 8 steps, so that LDS (two
+// buffers per workgroup) allows as many workgroups per CU as the registers
+constexpr int panel_tile_blocks(int ns) { return ns <= 4 ? 4 : 2; }
 
 // bytes [16 lane, 16 lane + 16) of dst (wave-uniform) from src (per lane)
 __device__ __forceinline__ void lds_load16(const char* src, char* dst) {
@@ -219,9 +219,19 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       }
     }
   };
-  // pass A: the bound that `target` of this workgroup's values lie above,
-  // shared with the other workgroups
+  // pass A: hand this workgroup's counts over, and take the bound that
+  // `target` of all counts so far lie above.  (A bound from the workgroup's
+  // own values alone stays far below the final one: nearly every 64 x 32
+  // block then held a value above it, 2.4 ms instead of 1.0 at 1563 x 1e6 x
+  // 256 in bf16.)
   auto raise = [&]() {
+    __syncthreads();
+    for (int b = t; b < 2048; b += 256)
+      if (hist[b]) atomicAdd(&g.hist[b], hist[b]);
+    // a count read too early only leaves the bound lower
+    for (int b = t; b < 2048; b += 256)
+      hist[b] = __hip_atomic_load(&g.hist[b], __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (wv == 0) {
       const int top = 2047 - 32 * lane;
@@ -229,25 +239,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       for (int b = top; b > top - 32; --b) sum += hist[b];
       const unsigned incl = wave_incl_scan(sum);
       const uint64_t reach = __ballot((int64_t)incl >= a.target);
-      unsigned bits = 0;
-      if (reach) {
-        const int src = __builtin_ctzll(reach);
-        if (lane == src) {
-          unsigned acc = incl - sum;
-          int b = top;
-          for (; b > top - 31; --b) {
-            acc += hist[b];
-            if ((int64_t)acc >= a.target) break;
-          }
-          bits = bins.edge(b);
+      if (reach && lane == __builtin_ctzll(reach)) {
+        unsigned acc = incl - sum;
+        int b = top;
+        for (; b > top - 31; --b) {
+          acc += hist[b];
+          if ((int64_t)acc >= a.target) break;
         }
-        bits = __shfl(bits, src, 64);
-      }
-      if (lane == 0) {
-        const unsigned old = atomicMax(a.thr, bits);
-        thr_s = old > bits ? old : bits;
+        thr_s = bins.edge(b);
       }
     }
+    __syncthreads();
+    for (int b = t; b < 2048; b += 256) hist[b] = 0;
     __syncthreads();
     pre = __uint_as_float(thr_s) - mg2;
   };
@@ -305,14 +308,43 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   }
 }
 
-template <int P, int NS>
-hipError_t launch_panel_ns(const PanelArgs& a, bool hist, unsigned grid,
-                           hipStream_t st) {
-  if (hist)
-    k_gemm_panel<P, NS, true><<<grid, 256, 0, st>>>(a);
-  else
-    k_gemm_panel<P, NS, false><<<grid, 256, 0, st>>>(a);
+// workgroups that fill the chip: what registers and LDS let a CU hold
+template <int P, int NS, bool HIST>
+unsigned panel_grid() {
+  static const unsigned per_cu = [] {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+            &n, k_gemm_panel<P, NS, HIST>, 256, 0) != hipSuccess ||
+        n < 1)
+      n = 2;
+    return (unsigned)n;
+  }();
+  return 256 * per_cu;
+}
+
+template <int P, int NS, bool HIST>
+hipError_t launch_panel_one(PanelArgs a, int64_t grid, hipStream_t st) {
+  if (grid <= 0) grid = panel_grid<P, NS, HIST>();
+  constexpr int tn = panel_tile_blocks(NS) * 32;
+  a.tiles_n = (a.g.n + tn - 1) / tn;
+  a.panels = (a.g.m_rows + kPanelRows - 1) / kPanelRows;
+  // column tiles per item: up to 2048 columns, so that loading the rows of A
+  // (once per item) is a few percent of it, but a dozen items or more per
+  // workgroup while there are tiles enough, so that the last round is short
+  int64_t seg = a.tiles_n * a.panels / (grid * 12);
+  if (seg > 2048 / tn) seg = 2048 / tn;
+  if (seg < 1) seg = 1;
+  a.seg = seg;
+  a.items = a.panels * ((a.tiles_n + seg - 1) / seg);
+  k_gemm_panel<P, NS, HIST><<<(unsigned)grid, 256, 0, st>>>(a);
   return hipGetLastError();
+}
+
+template <int P, int NS>
+hipError_t launch_panel_ns(const PanelArgs& a, bool hist, int64_t grid,
+                           hipStream_t st) {
+  return hist ? launch_panel_one<P, NS, true>(a, grid, st)
+              : launch_panel_one<P, NS, false>(a, grid, st);
 }
 
 }  // namespace mad

@@ -5,7 +5,7 @@
 namespace mad {
 
 hipError_t launch_panel_bf16(const PanelArgs& a, int ns, bool hist,
-                             unsigned grid, hipStream_t st) {
+                             int64_t grid, hipStream_t st) {
   switch (ns) {
 #define MAD_PANEL_CASE(N) \
   case N:                 \

@@ -381,8 +381,16 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
 #undef MAD_BF_LSTORE1
 #undef MAD_BF_LSTORE
 
-// maxima of n2, n1 and eta over the vectors (float bits, atomically)
-__global__ void k_vecinfo_max(const VecInfo* v, int64_t rows, unsigned* mx) {
+// maxima of n2, n1 and eta over the vectors of A (blockIdx.y 0, to mx[0..2])
+// and of B (1, to mx[4..6]), as float bits
+__global__ __launch_bounds__(1024) void k_vecinfo_max(const VecInfo* va,
+                                                      int64_t m,
+                                                      const VecInfo* vb,
+                                                      int64_t n,
+                                                      unsigned* mx) {
+  __shared__ float red[3][16];
+  const VecInfo* v = blockIdx.y ? vb : va;
+  const int64_t rows = blockIdx.y ? n : m;
   float a = 0.0f, b = 0.0f, c = 0.0f;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; r < rows;
@@ -391,16 +399,20 @@ __global__ void k_vecinfo_max(const VecInfo* v, int64_t rows, unsigned* mx) {
     b = fmaxf(b, v[r].n1);
     c = fmaxf(c, v[r].eta);
   }
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    a = fmaxf(a, __shfl_xor(a, off, 64));
-    b = fmaxf(b, __shfl_xor(b, off, 64));
-    c = fmaxf(c, __shfl_xor(c, off, 64));
-  }
+  a = wave_max(a);
+  b = wave_max(b);
+  c = wave_max(c);
+  const int wv = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) {
-    atomicMax(&mx[0], __float_as_uint(a));
-    atomicMax(&mx[1], __float_as_uint(b));
-    atomicMax(&mx[2], __float_as_uint(c));
+    red[0][wv] = a;
+    red[1][wv] = b;
+    red[2][wv] = c;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    float x = 0.0f;
+    for (int w = 0; w < 16; ++w) x = fmaxf(x, red[threadIdx.x][w]);
+    atomicMax(&mx[4 * blockIdx.y + threadIdx.x], __float_as_uint(x));
   }
 }
 
@@ -580,12 +592,11 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   unsigned long long* ccount = (unsigned long long*)(hist + 2048 + 16);
   unsigned* maxes = hist + 2048 + 32;  // n2, n1, eta of A then of B
   unsigned long long* est = (unsigned long long*)(hist + 2048 + 48);
-  unsigned* thr = hist + 2048 + 64;  // pass A's running bound
-  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8 + 8 + 8, 0ull,
+  if ((e = launch_fill_u64((uint64_t*)hist, 1024 + 8 + 8 + 8 + 8, 0ull,
                            st)) != hipSuccess)
     return e;
-  k_vecinfo_max<<<64, 256, 0, st>>>((const VecInfo*)w.ia.p, m, maxes);
-  k_vecinfo_max<<<64, 256, 0, st>>>((const VecInfo*)w.ib.p, n, maxes + 4);
+  k_vecinfo_max<<<dim3(64, 2), 1024, 0, st>>>(
+      (const VecInfo*)w.ia.p, m, (const VecInfo*)w.ib.p, n, maxes);
   // margin factor: input rounding (2u + u^2) plus gamma_d for the MFMA
   // accumulation and gamma_d for the fp32 re-rank
   const double u = prec == kF32 ? 0.0 : prec == kBF16 ? ldexp(1.0, -8)
@@ -619,7 +630,7 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   a.ccount = ccount;
   auto gemm = [&](bool hist_pass, int64_t target) -> hipError_t {
     if (panel)
-      return launch_panel(a, prec, d, hist_pass, target, eb8, thr, st);
+      return launch_panel(a, prec, d, hist_pass, target, eb8, st);
     if (prec == kF32) launch_gemm<kF32>(a, hist_pass, st);
     else if (prec == kBF16) launch_gemm<kBF16>(a, hist_pass, st);
     else launch_gemm<kFP8>(a, hist_pass, st);
