@@ -129,10 +129,11 @@ __global__ __launch_bounds__(kHistThreads) void k_score_hist(
 
 // step 2a (one block): the boundary bin from the histogram, then clear it.
 // The element count is *n_ptr, or the histogram's total when n_ptr is
-// null; n_store (if set) receives it.
+// null; n_store (if set) receives it.  clear2 (if set): two counts that the
+// split after it starts from zero.
 __global__ __launch_bounds__(256) void k_coarse_decide(
     unsigned* hist, const int64_t* n_ptr, int64_t k, Coarse* out,
-    int64_t* n_store, Refine* rf = nullptr) {
+    int64_t* n_store, Refine* rf = nullptr, int64_t* clear2 = nullptr) {
   __shared__ unsigned long long wsum[4];
   __shared__ int chosen;
   __shared__ unsigned long long before;
@@ -171,6 +172,7 @@ __global__ __launch_bounds__(256) void k_coarse_decide(
       rf->active = 0;
       rf->nout = 0ull;
     }
+    if (clear2) clear2[0] = clear2[1] = 0;
     if (n_store) *n_store = n;
     out->n = n;
     out->k = k;
@@ -1013,49 +1015,57 @@ struct PairOut {
   float c, x;
 };
 
-// the final set ordered by (|c| desc, key asc): each element's rank is the
-// number of elements before it, counted against the set staged in LDS in
-// chunks
-constexpr int kSortChunk = 2048;
+// The final set ordered by (|c| desc, key asc): each element's rank is the
+// number of elements before it.  A workgroup ranks 16 elements against the
+// whole set, a thread per other element and a ballot per comparison, so t
+// elements take t / 16 workgroups and t / 256 rounds each.  (A thread per
+// element, walking the set in LDS, left 4 workgroups in a chain of t LDS
+// reads: 73 us at t = 1000, 10 us now.)
+constexpr int kSortElems = 16;
 
 __global__ __launch_bounds__(256) void k_final_sort(
     const uint64_t* fkey, const uint64_t* fx, const float* fc,
     const int64_t* counts, int64_t tcap, int64_t n, const float* bmax,
     int64_t s_for_F, int x_shift, PairOut* out, int64_t* n_out) {
-  __shared__ float sa[kSortChunk];
-  __shared__ uint64_t sk[kSortChunk];
+  __shared__ float ea[kSortElems];
+  __shared__ uint64_t ek[kSortElems];
+  __shared__ unsigned long long rank[kSortElems];
   const int64_t nf = counts[kCntFinal] < tcap ? counts[kCntFinal] : tcap;
-  const int F = (bmax ? fix_exponent(*bmax, s_for_F) : 0) + x_shift;
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const float ae = e < nf ? fabsf(fc[e]) : 0.0f;
-  const uint64_t ke = e < nf ? fkey[e] : 0ull;
-  int64_t rank = 0;
-  for (int64_t o0 = 0; o0 < nf; o0 += kSortChunk) {
-    const int64_t no = nf - o0 < kSortChunk ? nf - o0 : kSortChunk;
-    __syncthreads();
-    for (int64_t o = threadIdx.x; o < no; o += blockDim.x) {
-      sa[o] = fabsf(fc[o0 + o]);
-      sk[o] = fkey[o0 + o];
-    }
-    __syncthreads();
-    if (e < nf) {
-      const int nn = (int)no;
-      int r = 0;
-#pragma unroll 8
-      for (int o = 0; o < nn; ++o)
-        r += (sa[o] > ae || (sa[o] == ae && sk[o] < ke)) ? 1 : 0;
-      rank += r;
-    }
+  if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = nf;
+  const int64_t e0 = (int64_t)blockIdx.x * kSortElems;
+  if (e0 >= nf) return;
+  const int t = threadIdx.x, lane = t & 63;
+  if (t < kSortElems) {
+    const bool in = e0 + t < nf;
+    ea[t] = in ? fabsf(fc[e0 + t]) : 0.0f;
+    ek[t] = in ? fkey[e0 + t] : 0ull;
+    rank[t] = 0ull;
   }
-  if (e < nf) {
+  __syncthreads();
+  unsigned long long before[kSortElems] = {};
+  for (int64_t o0 = 0; o0 < nf; o0 += 256) {
+    const bool in = o0 + t < nf;
+    const float ao = in ? fabsf(fc[o0 + t]) : 0.0f;
+    const uint64_t ko = in ? fkey[o0 + t] : 0ull;
+#pragma unroll
+    for (int u = 0; u < kSortElems; ++u)
+      before[u] += __popcll(
+          __ballot(in && (ao > ea[u] || (ao == ea[u] && ko < ek[u]))));
+  }
+  if (lane == 0)
+#pragma unroll
+    for (int u = 0; u < kSortElems; ++u) atomicAdd(&rank[u], before[u]);
+  __syncthreads();
+  if (t < kSortElems && e0 + t < nf) {
+    const int F = (bmax ? fix_exponent(*bmax, s_for_F) : 0) + x_shift;
+    const uint64_t ke = ek[t];
     PairOut p;
     p.i = (int64_t)(ke / (uint64_t)n);
     p.j = (int64_t)(ke % (uint64_t)n);
-    p.c = fc[e];
-    p.x = (float)ldexp((double)(int64_t)fx[e], -F);
-    out[rank] = p;
+    p.c = fc[e0 + t];
+    p.x = (float)ldexp((double)(int64_t)fx[e0 + t], -F);
+    out[rank[t]] = p;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *n_out = nf;
 }
 
 // every key of X (closed diamonds), for parity checks
@@ -1105,6 +1115,25 @@ __global__ __launch_bounds__(256) void k_absval_hist(const float* v,
   block_hist_flush(h, hist);
 }
 
+// one launch of the clears the two selections below start from: counts (256
+// bytes), the Coarse (256) and the histogram, which lie in a row, and x2; the
+// candidate count goes where the verification kernel reads it
+static hipError_t rerank_fills(int64_t* counts, uint64_t* x2, int64_t cnt,
+                               int64_t count, hipStream_t st) {
+  FillBatch f{};
+  f.count = 4;
+  f.p[0] = (uint64_t*)counts;
+  f.n[0] = kCntCand;
+  f.p[1] = (uint64_t*)&counts[kCntCand];
+  f.n[1] = 1;
+  f.v[1] = (uint64_t)count;
+  f.p[2] = (uint64_t*)&counts[kCntCand + 1];
+  f.n[2] = 31 - kCntCand + 32 + kBins / 2;
+  f.p[3] = x2;
+  f.n[3] = cnt;
+  return launch_fill_multi(f, st);
+}
+
 hipError_t launch_select_keys_by_absval(const uint64_t* keys, const float* v,
                                         int64_t count, int64_t k,
                                         DeviceBuffer& buf, uint64_t* out_keys,
@@ -1121,11 +1150,7 @@ hipError_t launch_select_keys_by_absval(const uint64_t* keys, const float* v,
   uint64_t* x2 = (uint64_t*)p; p += (size_t)cnt * 8;
   uint64_t* absbits = (uint64_t*)p; p += (size_t)cnt * 8;
   uint64_t* key = (uint64_t*)p;
-  if ((e = launch_fill_u64((uint64_t*)counts, 32, 0ull, st)) != hipSuccess ||
-      (e = launch_fill_u64((uint64_t*)hist, kBins / 2, 0ull, st)) != hipSuccess ||
-      (e = launch_fill_u64(x2, cnt, 0ull, st)) != hipSuccess ||
-      (e = launch_fill_u64((uint64_t*)&counts[kCntCand], 1, (uint64_t)count,
-                           st)) != hipSuccess)
+  if ((e = rerank_fills(counts, x2, cnt, count, st)) != hipSuccess)
     return e;
   k_absval_hist<<<blocks_for(cnt, 256 * 8, 2048), 256, 0, st>>>(v, count,
                                                                 absbits, hist);
@@ -1169,13 +1194,8 @@ hipError_t launch_rerank_topk(const uint64_t* keys, int64_t count,
   p = (char*)(((uintptr_t)p + 15) & ~(uintptr_t)15);
   uint64_t* absbits = (uint64_t*)p; p += (size_t)cnt * 8;
   uint64_t* key = (uint64_t*)p;
-  if ((e = launch_fill_u64((uint64_t*)counts, 32, 0ull, st)) != hipSuccess ||
-      (e = launch_fill_u64((uint64_t*)hist, kBins / 2, 0ull, st)) != hipSuccess ||
-      (e = launch_fill_u64(x2, cnt, 0ull, st)) != hipSuccess)
+  if ((e = rerank_fills(counts, x2, cnt, count, st)) != hipSuccess)
     return e;
-  // the candidate count goes where the verification kernel reads it
-  e = launch_fill_u64((uint64_t*)&counts[kCntCand], 1, (uint64_t)count, st);
-  if (e != hipSuccess) return e;
   if (csr)
     k_verify_csr<<<blocks_for(cnt * 64, 256, 2048), 256, 0, st>>>(
         keys, counts, *csr, n, cnt, c, absbits, hist);
@@ -1200,7 +1220,7 @@ hipError_t launch_rerank_topk(const uint64_t* keys, int64_t count,
                                             counts, kCntWin, fp, fkey, fx, fc,
                                             t, kCntFinal);
   // x = 0 for brute-force results (no sampler score); F is irrelevant
-  k_final_sort<<<blocks_for(t, 256, 1 << 30), 256, 0, st>>>(
+  k_final_sort<<<blocks_for(t, kSortElems, 1u << 30), 256, 0, st>>>(
       fkey, fx, fc, counts, t, n, nullptr, 0, 0, (PairOut*)out, n_out);
   return hipGetLastError();
 }
@@ -1280,11 +1300,9 @@ hipError_t launch_postprocess(const HashTable& h, const float* A,
     k_verify<<<blocks_for(t_prime * 16, 256, 2048), 256, 0, st>>>(
         w.key2, counts, A, B, n, d, w.cap2, w.c, w.x, w.hist);
   // ---- final selection: top t by |c| ----------------------------------------------
-  e = launch_fill_u64((uint64_t*)&counts[kCntBound], 2, 0ull, st);
-  if (e != hipSuccess) return e;
   Refine* rf2 = rf + 1;
   k_coarse_decide<<<1, 256, 0, st>>>(w.hist, &counts[kCntCand], t, cz + 1,
-                                     nullptr, rf2);
+                                     nullptr, rf2, &counts[kCntBound]);
   // final set in w.key[0 .. 4t): |c| bits, key, x, c; boundary after it
   uint64_t* fp = w.key;
   uint64_t* fkey = w.key + t;
@@ -1323,7 +1341,7 @@ hipError_t launch_postprocess(const HashTable& h, const float* A,
   k_fine_select<<<1, kFineThreads, 0, st>>>(
       cz + 1, bp, bkey, bx, bc, bcap, counts, kCntWin, fp, fkey, fx, fc, t,
       kCntFinal, rf2, rp, rk, rxx, rc, rcap2);
-  k_final_sort<<<blocks_for(t, 256, 1 << 30), 256, 0, st>>>(
+  k_final_sort<<<blocks_for(t, kSortElems, 1u << 30), 256, 0, st>>>(
       fkey, fx, fc, counts, t, n, bmax, s, x_shift, (PairOut*)out, n_out);
   return hipGetLastError();
 }
