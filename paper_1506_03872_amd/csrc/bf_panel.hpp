@@ -328,12 +328,18 @@ hipError_t launch_panel_one(PanelArgs a, int64_t grid, hipStream_t st) {
   constexpr int tn = panel_tile_blocks(NS) * 32;
   a.tiles_n = (a.g.n + tn - 1) / tn;
   a.panels = (a.g.m_rows + kPanelRows - 1) / kPanelRows;
-  // column tiles per item: up to 2048 columns, so that loading the rows of A
+  // Column tiles per item: up to 2048 columns, so that loading the rows of A
   // (once per item) is a few percent of it, but a dozen items or more per
-  // workgroup while there are tiles enough, so that the last round is short
+  // workgroup, so that the last round is short.  With fewer than a dozen
+  // tiles per workgroup, one item each (pass A at 1563 x 1e5 x 100 in fp8:
+  // 94 us, against 119 with one-tile items, each loading its rows of A).
   int64_t seg = a.tiles_n * a.panels / (grid * 12);
   if (seg > 2048 / tn) seg = 2048 / tn;
-  if (seg < 1) seg = 1;
+  if (seg < 1) {
+    const int64_t per = grid / a.panels > 1 ? grid / a.panels : 1;
+    seg = (a.tiles_n + per - 1) / per;
+    if (seg > 12) seg = 12;
+  }
   a.seg = seg;
   a.items = a.panels * ((a.tiles_n + seg - 1) / seg);
   k_gemm_panel<P, NS, HIST><<<(unsigned)grid, 256, 0, st>>>(a);
