@@ -64,12 +64,12 @@ int64_t next_pow2(int64_t v) {
 struct MipsState {
   mad::Family T0q;  // stage-0 table per query (capacity nq_cap tables)
   int64_t nq_cap = 0;
-  mad::DeviceBuffer qscratch, qinfo, order, chunks, hash, cx, ck, sx,
-      sk, sc, sab, qstats, ctr;
+  mad::DeviceBuffer qscratch, qinfo, order, chunks, units, items, hash, part,
+      offs, qcnt, cw, sw, sc, sab, qstats, ctr;
   // layout of the prepared batch
   std::vector<int64_t> s, tp;
   int64_t nq = -1, t = -1;
-  int64_t hslots = 0, nchunks = 0;
+  int64_t hslots = 0, nchunks = 0, nunits = 0, nitems = 0, unit = 1;
   int chunk_prepared = -1, slots_prepared = -1;
   // launch shape and score-table slots per possible key (result-invariant)
   int chunk = 4096, unroll = 4, grid = 2048, slots = 2;
@@ -137,8 +137,9 @@ static void mips_free(MipsState* ms) {
   if (ms->cap_stream) (void)hipStreamDestroy(ms->cap_stream);
   mad::family_free_pub(ms->T0q);
   mad::DeviceBuffer* bufs[] = {&ms->qscratch, &ms->qinfo, &ms->order,
-                               &ms->chunks, &ms->hash, &ms->cx,
-                               &ms->ck, &ms->sx, &ms->sk, &ms->sc, &ms->sab,
+                               &ms->chunks, &ms->units, &ms->items, &ms->hash,
+                               &ms->part, &ms->offs, &ms->qcnt, &ms->cw,
+                               &ms->sw, &ms->sc, &ms->sab,
                                &ms->qstats, &ms->ctr, &ms->qlp, &ms->qlpi};
   for (mad::DeviceBuffer* b : bufs) mad::dev_free(*b);
   delete ms;
@@ -1367,7 +1368,20 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
   const int64_t m = p->m;
   std::vector<mad::MipsQuery> qi((size_t)nq);
   std::vector<int32_t> order((size_t)nq);
-  int64_t hs = 0, cs = 0, ss = 0;
+  // bins are ranges of i: key i falls in bin i >> shift
+  int lm = 0;
+  while ((int64_t(1) << lm) < m) ++lm;
+  const int64_t unit =
+      ms->chunk < mad::kMipsUnit ? ms->chunk : mad::kMipsUnit;
+  // samples per bin aimed at: up to 1024 (half the table of a bin), fewer in
+  // a small batch, whose bins would not fill the chip (16 queries of 64 to
+  // 512 samples: 85 us a batch with 1024 to a bin, 56 us with 64)
+  int64_t total = 0;
+  for (int64_t q = 0; q < nq; ++q)
+    if (s[q] <= mad::kMaxPartBudget) total += s[q];
+  int64_t words = 64;
+  while (words < 1024 && total / words > 2048) words *= 2;
+  int64_t hs = 0, cs = 0, ss = 0, po = 0, oo = 0;
   for (int64_t q = 0; q < nq; ++q) {
     mad::MipsQuery& x = qi[(size_t)q];
     memset(&x, 0, sizeof x);
@@ -1378,33 +1392,68 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
     const int64_t sc1 = sq > 0 ? sq : 1;
     if (tpe > sc1) tpe = sc1;
     if (tpe < t) tpe = t;
-    const int64_t hcap =
-        next_pow2((int64_t)ms->slots * (pairs > 512 ? pairs : 512));
     x.s = sq;
     x.tp = tpe;
-    x.hoff = hs;
-    x.hmask = (uint32_t)(hcap - 1);
-    x.coff = cs;
     x.ccap = pairs > 1 ? pairs : 1;
     x.soff = ss;
     x.scap = x.ccap < tpe ? x.ccap : tpe;
-    hs += hcap;
-    cs += x.ccap;
+    if (sq > 0 && sq <= mad::kMaxPartBudget) {  // summed in LDS
+      x.shift = lm;
+      while (x.shift > 0 && lm - x.shift < mad::kMaxBinsLog &&
+             (((m - 1) >> x.shift) + 1) * words < sq)
+        --x.shift;
+      x.bins = (int)((m - 1) >> x.shift) + 1;
+      x.poff = po;
+      x.ooff = oo;
+      po += (sq + 1) / 2 * 2;
+      oo += (sq + unit - 1) / unit * (x.bins + 1);
+    } else if (sq > 0) {  // a table in memory
+      const int64_t hcap =
+          next_pow2((int64_t)ms->slots * (pairs > 512 ? pairs : 512));
+      x.hoff = hs;
+      x.hmask = (uint32_t)(hcap - 1);
+      x.coff = cs;
+      hs += hcap;
+      cs += x.ccap;
+    }
     ss += x.scap;
     order[(size_t)q] = (int32_t)q;
   }
+  const int64_t hclear = hs;  // the tables come first: they are cleared
+  for (mad::MipsQuery& x : qi)
+    if (x.bins) {
+      x.hoff = hs;
+      hs += x.ccap;
+    }
   std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) {
     return s[a] > s[b];
   });
-  std::vector<mad::MipsChunk> ch;
-  for (int32_t q : order)
-    for (int64_t l0 = 0; l0 < s[q]; l0 += ms->chunk) {
+  std::vector<mad::MipsChunk> ch, un;
+  for (int32_t q : order) {
+    const bool part = qi[(size_t)q].bins != 0;
+    const int64_t step = part ? unit : ms->chunk;
+    for (int64_t l0 = 0; l0 < s[q]; l0 += step) {
       mad::MipsChunk c;
       c.q = q;
-      c.count = (int32_t)(s[q] - l0 < ms->chunk ? s[q] - l0 : ms->chunk);
+      c.count = (int32_t)(s[q] - l0 < step ? s[q] - l0 : step);
       c.l0 = l0;
-      ch.push_back(c);
+      (part ? un : ch).push_back(c);
     }
+  }
+  // items by range of i: of the finest ranges, those at which a query's
+  // bin starts
+  std::vector<mad::MipsItem> items;
+  // queries by log2(finest ranges per bin)
+  std::vector<int32_t> by_width[mad::kMaxBinsLog + 1];
+  const int fine = lm > mad::kMaxBinsLog ? lm - mad::kMaxBinsLog : 0;
+  for (int32_t q : order)
+    if (qi[(size_t)q].bins)
+      by_width[qi[(size_t)q].shift - fine].push_back(q);
+  for (int64_t r = 0; r <= (m - 1) >> fine; ++r)
+    for (int f = 0;
+         f <= mad::kMaxBinsLog && (r & ((int64_t(1) << f) - 1)) == 0; ++f)
+      for (int32_t q : by_width[f])
+        items.push_back(mad::MipsItem{q, (int32_t)(r >> f)});
   (void)hipDeviceSynchronize();
   mips_drop_graph(ms);
   hipError_t e = hipSuccess;
@@ -1421,13 +1470,16 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
       (e = mad::dev_alloc(ms->qinfo, nqa * sizeof(mad::MipsQuery))) != hipSuccess ||
       (e = mad::dev_alloc(ms->order, nqa * 4)) != hipSuccess ||
       (e = mad::dev_alloc(ms->chunks, (ch.size() + 1) * sizeof(mad::MipsChunk))) != hipSuccess ||
+      (e = mad::dev_alloc(ms->units, (un.size() + 1) * sizeof(mad::MipsChunk))) != hipSuccess ||
+      (e = mad::dev_alloc(ms->items, (items.size() + 1) * sizeof(mad::MipsItem))) != hipSuccess ||
       (e = mad::dev_alloc(ms->hash, (size_t)(hs + 1) * 8)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->cx, (size_t)(cs + 1) * 8)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->ck, (size_t)(cs + 1) * 4)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->sx, (size_t)(ss + 1) * 8)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->sk, (size_t)(ss + 1) * 4)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->part, (size_t)(po + 2) * 8)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->offs, (size_t)(oo + 1) * 2)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->qcnt, nqa * sizeof(mad::MipsCount))) != hipSuccess ||
+      (e = mad::dev_alloc(ms->cw, (size_t)(cs + 1) * 8)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->sw, (size_t)(ss + 1) * 8)) != hipSuccess ||
       (e = mad::dev_alloc(ms->sc, (size_t)(ss + 1) * 4)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->sab, (size_t)(ss + 1) * 8)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->sab, (size_t)(ss + 1) * 4)) != hipSuccess ||
       (e = mad::dev_alloc(ms->qstats, nqa * sizeof(mad::MipsQueryStats))) != hipSuccess ||
       (e = mad::dev_alloc(ms->ctr, sizeof(mad::SampleCounters))) != hipSuccess) {
     ms->nq = -1;
@@ -1442,12 +1494,22 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
   if (!ch.empty())
     HIP_TRY(hipMemcpy(ms->chunks.p, ch.data(), ch.size() * sizeof ch[0],
                       hipMemcpyHostToDevice), "uploading the batch layout");
+  if (!un.empty())
+    HIP_TRY(hipMemcpy(ms->units.p, un.data(), un.size() * sizeof un[0],
+                      hipMemcpyHostToDevice), "uploading the batch layout");
+  if (!items.empty())
+    HIP_TRY(hipMemcpy(ms->items.p, items.data(),
+                      items.size() * sizeof items[0], hipMemcpyHostToDevice),
+            "uploading the batch layout");
   ms->s.assign(s, s + nq);
   ms->tp.assign(tp, tp + nq);
   ms->nq = nq;
   ms->t = t;
-  ms->hslots = hs;
+  ms->hslots = hclear;
   ms->nchunks = (int64_t)ch.size();
+  ms->nunits = (int64_t)un.size();
+  ms->nitems = (int64_t)items.size();
+  ms->unit = unit;
   ms->chunk_prepared = ms->chunk;
   ms->slots_prepared = ms->slots;
   ++ms->layout_version;
@@ -1485,12 +1547,18 @@ static mad::MipsArgs mips_args(mad_plan* p, const float* Q, uint64_t seed,
   a.nchunks = ms->nchunks;
   a.hslot = (uint64_t*)ms->hash.p;
   a.kb = mips_key_bits(p->m);
-  a.cx = (uint64_t*)ms->cx.p;
-  a.ck = (uint32_t*)ms->ck.p;
-  a.sx = (uint64_t*)ms->sx.p;
-  a.sk = (uint32_t*)ms->sk.p;
+  a.units = (const mad::MipsChunk*)ms->units.p;
+  a.nunits = ms->nunits;
+  a.unit = ms->unit;
+  a.items = (const mad::MipsItem*)ms->items.p;
+  a.nitems = ms->nitems;
+  a.part = (uint64_t*)ms->part.p;
+  a.offs = (uint16_t*)ms->offs.p;
+  a.qcnt = (mad::MipsCount*)ms->qcnt.p;
+  a.cw = (uint64_t*)ms->cw.p;
+  a.sw = (uint64_t*)ms->sw.p;
   a.sc = (float*)ms->sc.p;
-  a.sab = (uint64_t*)ms->sab.p;
+  a.sab = (uint32_t*)ms->sab.p;
   a.ctr = (mad::SampleCounters*)ms->ctr.p;
   a.qstats = (mad::MipsQueryStats*)ms->qstats.p;
   a.out = out;
@@ -1517,8 +1585,10 @@ static hipError_t mips_enqueue(mad_plan* p, const mad::MipsArgs& a,
   hipError_t e;
   if (events) record(p, 0, st);
   if ((e = mad::launch_mips_query_info(a.Q, a.nq, a.d, a.kb,
-                                       (mad::MipsQuery*)ms->qinfo.p, st)) !=
-          hipSuccess ||
+                                       (mad::MipsQuery*)ms->qinfo.p,
+                                       (mad::MipsCount*)ms->qcnt.p,
+                                       (mad::SampleCounters*)ms->ctr.p,
+                                       st)) != hipSuccess ||
       (e = mad::query_tables_build(a.Q, a.nq, a.d, p->dt.v, ms->T0q,
                                    ms->qscratch.p, ms->qscratch.bytes, st)) !=
           hipSuccess)
@@ -1533,15 +1603,18 @@ static hipError_t mips_enqueue(mad_plan* p, const mad::MipsArgs& a,
     record(p, 1, st);
     record(p, 2, st);
   }
-  if ((e = mad::launch_fill_u64((uint64_t*)ms->hash.p, ms->hslots, 0ull,
-                                st)) != hipSuccess ||
-      (e = mad::launch_fill_u64((uint64_t*)ms->ctr.p, 8, 0ull, st)) !=
-          hipSuccess)
+  if (ms->hslots > 0 &&
+      (e = mad::launch_fill_u64((uint64_t*)ms->hash.p, ms->hslots, 0ull,
+                                st)) != hipSuccess)
     return e;
   if (events) record(p, 3, st);
-  if ((e = mad::launch_sample_mips(a, ms->unroll, ms->grid, st)) != hipSuccess)
+  if ((e = mad::launch_sample_mips(a, ms->unroll, ms->grid, st)) !=
+          hipSuccess ||
+      (e = mad::launch_sample_mips_part(a, ms->unroll, ms->grid, st)) !=
+          hipSuccess)
     return e;
   if (events) record(p, 4, st);
+  if ((e = mad::launch_mips_bins(a, st)) != hipSuccess) return e;
   if ((e = mad::launch_mips_post(a, st)) != hipSuccess) return e;
   if (events) record(p, 5, st);
   return hipSuccess;
@@ -1784,7 +1857,15 @@ int mips_stats(mad_plan* p, int64_t* n_pos, int64_t* n_cand, int64_t* closed,
   HIP_TRY(hipMemcpy(&sc, ms->ctr.p, sizeof sc, hipMemcpyDeviceToHost),
           "MIPS stats");
   if (closed) *closed = (int64_t)sc.closed;
-  if (distinct) *distinct = (int64_t)sc.distinct;
+  if (distinct) {  // the tables' keys, and those summed in LDS
+    std::vector<mad::MipsCount> qc((size_t)ms->nq);
+    HIP_TRY(hipMemcpy(qc.data(), ms->qcnt.p, qc.size() * sizeof qc[0],
+                      hipMemcpyDeviceToHost), "MIPS stats");
+    int64_t keys = (int64_t)sc.distinct;
+    for (const mad::MipsCount& c : qc)
+      keys += (int64_t)c.pos + (int64_t)c.rest;
+    *distinct = keys;
+  }
   return MAD_OK;
 }
 

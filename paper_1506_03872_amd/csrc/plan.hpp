@@ -320,16 +320,40 @@ hipError_t stage0_table_build(const double* w, int64_t N, Family& T,
 struct MipsQuery {
   int64_t s;       // sample budget s_q
   int64_t tp;      // candidate budget t'_q (>= t)
-  int64_t hoff;    // first slot of the query's score table
+  int64_t hoff;    // first slot of the query's score table or word list
   int64_t coff;    // first entry of its candidate list (capacity ccap)
   int64_t ccap;    // min(s_q, m) (>= 1)
-  int64_t soff;    // first entry of its verified list (capacity scap)
+  int64_t soff;    // first entry of its selected list (capacity scap)
   int64_t scap;    // min(ccap, t'_q)
   uint32_t hmask;  // table capacity - 1 (a power of two minus one)
   int F;           // fixed-point exponent (device)
   int live;        // 1: finite query (device)
+  int bins;        // ranges of i its words are ordered by (0: its scores
+                   // are kept in a table of hmask + 1 slots)
+  int shift;       // bin of key i: i >> shift
   int pad;
+  int64_t poff;    // first word in MipsArgs::part
+  int64_t ooff;    // first offset in MipsArgs::offs (bins + 1 per unit)
 };
+
+// keys with x > 0 and with x <= 0 that k_mips_bins has listed (device)
+struct MipsCount {
+  unsigned pos, rest;
+};
+
+// one (query, bin) of k_mips_bins
+struct MipsItem {
+  int32_t q, bin;
+};
+
+// Samples per unit of the partition (32 KB of words in LDS) and the most
+// bins and samples of a query whose scores are summed in LDS.  A unit of a
+// query of 2^18 samples has runs of 8 to 16 words per bin; more bins would
+// read ever less of each line.
+constexpr int kMipsUnit = 4096;
+constexpr int kMaxBinsLog = 9;
+constexpr int kMaxBins = 1 << kMaxBinsLog;
+constexpr int64_t kMaxPartBudget = int64_t(1) << 18;
 
 // a contiguous range of one query's samples
 struct MipsChunk {
@@ -363,16 +387,24 @@ struct MipsArgs {
   const int32_t* order;  // queries by descending budget
   const MipsChunk* chunks;
   int64_t nchunks;
-  // score slots of the queries' tables: key i + 1 in the low kb bits, the
-  // score x (fixed point) in the high 64 - kb bits; 0 is an empty slot
+  // score words (key i + 1 in the low kb bits, the score x in fixed point in
+  // the high 64 - kb bits): tables in memory, 0 an empty slot, or the lists
+  // of k_mips_bins
   uint64_t* hslot;
   int kb;
-  uint64_t* cx;  // candidate scores
-  uint32_t* ck;  // candidate keys (i)
-  uint64_t* sx;  // verified: scores
-  uint32_t* sk;  //           keys
-  float* sc;     //           c
-  uint64_t* sab; //           |c| bits
+  // queries summed in LDS: units of at most `unit` samples, the (query, bin)
+  // items by range of i, the units' words and bin offsets, the key counts
+  const MipsChunk* units;
+  int64_t nunits, unit;
+  const MipsItem* items;
+  int64_t nitems;
+  uint64_t* part;
+  uint16_t* offs;
+  MipsCount* qcnt;
+  uint64_t* cw;  // candidate words of the queries with tables in memory
+  uint64_t* sw;  // selected candidates' words
+  float* sc;     //                     c
+  uint32_t* sab; //                     |c| bits (screened queries)
   SampleCounters* ctr;
   MipsQueryStats* qstats;
   void* out;       // nq x t mad_pair
@@ -390,7 +422,11 @@ struct MipsArgs {
 };
 
 hipError_t launch_mips_query_info(const float* Q, int64_t nq, int64_t d,
-                                  int kb, MipsQuery* qi, hipStream_t st);
+                                  int kb, MipsQuery* qi, MipsCount* qcnt,
+                                  SampleCounters* ctr, hipStream_t st);
+hipError_t launch_sample_mips_part(const MipsArgs& a, int unroll, int grid,
+                                   hipStream_t st);
+hipError_t launch_mips_bins(const MipsArgs& a, hipStream_t st);
 hipError_t launch_sample_mips(const MipsArgs& a, int unroll, int grid,
                               hipStream_t st);
 hipError_t launch_mips_post(const MipsArgs& a, hipStream_t st);
