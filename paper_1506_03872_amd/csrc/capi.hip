@@ -6,6 +6,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -158,7 +159,13 @@ static const float* plan_bmax(const mad_plan* p) {
   return p->kind == 2 ? p->ct.bmax : p->dt.bmax;
 }
 
+// Waits for the device: the plan's memory goes to the free list, from which
+// another plan may take it for any stream.
 static void plan_free_all(mad_plan* p) {
+  const bool idle = hipDeviceSynchronize() == hipSuccess;
+  std::unique_ptr<mad::PoolScope> pool(idle ? new (std::nothrow)
+                                                  mad::PoolScope()
+                                            : nullptr);
   mips_free(p->mips);
   p->mips = nullptr;
   mad::dense_tables_free(p->dt);
@@ -313,7 +320,6 @@ int mad_plan_create_dense(const float* A, int64_t m, const float* B,
   int rc = mad_plan_refresh(p, stream);
   if (rc != MAD_OK) {
     std::string keep = g_err;
-    (void)hipDeviceSynchronize();
     plan_free_all(p);
     delete p;
     g_err = keep;
@@ -382,7 +388,6 @@ int mad_plan_refresh(mad_plan* p, void* stream) {
 
 void mad_plan_destroy(mad_plan* p) {
   if (!p) return;
-  (void)hipDeviceSynchronize();
   plan_free_all(p);
   delete p;
 }
@@ -1283,7 +1288,6 @@ int mad_plan_create_csr(const int64_t* a_ptr, const int32_t* a_idx,
   int rc = mad_plan_refresh(p, stream);
   if (rc != MAD_OK) {
     std::string keep = g_err;
-    (void)hipDeviceSynchronize();
     plan_free_all(p);
     delete p;
     g_err = keep;
@@ -1337,7 +1341,6 @@ int mips_plan_create(const float* A, int64_t m, int64_t d, uint32_t flags,
   int rc = mad_plan_refresh(p, stream);
   if (rc != MAD_OK) {
     std::string keep = g_err;
-    (void)hipDeviceSynchronize();
     plan_free_all(p);
     delete p;
     g_err = keep;

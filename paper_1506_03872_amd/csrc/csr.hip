@@ -1121,8 +1121,7 @@ void csr_tables_free(CsrTables& t) {
   void* ps[] = {t.at_ptr, t.at_row, t.at_val, t.at_src, t.bt_ptr, t.bt_row,
                 t.bt_val, t.bt_src, t.at_w, t.om, t.bmax, t.bad, t.at_pay,
                 t.bsig, t.bt_pay, t.bh};
-  for (void* p : ps)
-    if (p) (void)hipFree(p);
+  for (void* p : ps) mem_free(p);
   t.at_ptr = t.bt_ptr = nullptr;
   t.at_row = t.bt_row = nullptr;
   t.at_val = t.bt_val = nullptr;
@@ -1201,27 +1200,27 @@ hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st) {
   const int64_t m = t.m, n = t.n, d = t.d;
   // first build: fixed-size arrays
   if (!t.bad) {
-    if ((e = hipMalloc(&t.bad, 256)) != hipSuccess ||
-        (e = hipMalloc(&t.bmax, 256)) != hipSuccess ||
-        (e = hipMalloc(&t.om, 8 * (size_t)d)) != hipSuccess ||
-        (e = hipMalloc(&t.at_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bt_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.at_row, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.at_val, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bt_row, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bt_val, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.at_src, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bt_src, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.at_w, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.at_pay, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bsig, 8 * (size_t)(n + 1))) != hipSuccess ||
-        (e = hipMalloc(&t.bt_pay, 8 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+    if ((e = mem_alloc((void**)&t.bad, 256)) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bmax, 256)) != hipSuccess ||
+        (e = mem_alloc((void**)&t.om, 8 * (size_t)d)) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bt_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_row, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_val, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bt_row, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bt_val, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_src, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bt_src, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_w, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.at_pay, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bsig, 8 * (size_t)(n + 1))) != hipSuccess ||
+        (e = mem_alloc((void**)&t.bt_pay, 8 * (size_t)(t.nnzB + 1))) != hipSuccess ||
         (e = family_alloc_pub(t.T0, 1, d)) != hipSuccess)
       return e;
     int64_t cap = 1024;
     while (cap < 2 * t.nnzB) cap <<= 1;
     t.bh_mask = (uint64_t)(cap - 1);
-    if ((e = hipMalloc(&t.bh, sizeof(BSlot) * (size_t)cap)) != hipSuccess)
+    if ((e = mem_alloc((void**)&t.bh, sizeof(BSlot) * (size_t)cap)) != hipSuccess)
       return e;
   }
   if (!check && t.structured) {

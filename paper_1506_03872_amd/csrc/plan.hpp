@@ -24,8 +24,18 @@ struct DeviceBuffer {
   size_t bytes = 0;
 };
 
+// ---- mem.hip -------------------------------------------------------------
+hipError_t mem_alloc(void** out, size_t bytes);
+void mem_free(void* p);  // p may be null
 hipError_t dev_alloc(DeviceBuffer& b, size_t bytes);
 void dev_free(DeviceBuffer& b);
+
+// While one is alive on a thread, what that thread frees is kept for later
+// allocations.  Only after the device has been synchronised.
+struct PoolScope {
+  PoolScope();
+  ~PoolScope();
+};
 
 // ---- tables.hip ----------------------------------------------------------
 // Dense preprocessing: na (m), nb (d), v (d), om (d); families T0 (S=1,

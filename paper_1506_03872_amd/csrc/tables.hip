@@ -1279,38 +1279,19 @@ hipError_t launch_check_symmetric(const float* A, int64_t m, int* flag,
   return hipGetLastError();
 }
 
-hipError_t dev_alloc(DeviceBuffer& b, size_t bytes) {
-  if (b.bytes >= bytes && b.p) return hipSuccess;
-  dev_free(b);
-  if (bytes == 0) return hipSuccess;
-  hipError_t e = hipMalloc(&b.p, bytes);
-  if (e != hipSuccess) {
-    b.p = nullptr;
-    b.bytes = 0;
-    return e;
-  }
-  b.bytes = bytes;
-  return hipSuccess;
-}
-
-void dev_free(DeviceBuffer& b) {
-  if (b.p) (void)hipFree(b.p);
-  b.p = nullptr;
-  b.bytes = 0;
-}
-
 static hipError_t family_alloc(Family& f, int64_t S, int64_t N) {
   f.S = S;
   f.N = N;
   f.L = ceil_log2_host(N);
-  hipError_t e = hipMalloc(&f.ent, sizeof(uint64_t) * (size_t)(S << f.L));
+  hipError_t e =
+      mem_alloc((void**)&f.ent, sizeof(uint64_t) * (size_t)(S << f.L));
   if (e != hipSuccess) return e;
-  return hipMalloc(&f.tot, sizeof(double) * (size_t)S);
+  return mem_alloc((void**)&f.tot, sizeof(double) * (size_t)S);
 }
 
 static void family_free(Family& f) {
-  if (f.ent) (void)hipFree(f.ent);
-  if (f.tot) (void)hipFree(f.tot);
+  mem_free(f.ent);
+  mem_free(f.tot);
   f.ent = nullptr;
   f.tot = nullptr;
 }
@@ -1328,11 +1309,11 @@ hipError_t dense_tables_alloc(DenseTables& t, int64_t m, int64_t n,
   t.na = t.T3.tot;
   t.v = t.T1.tot;
   t.nb = t.T2.tot;
-  if ((e = hipMalloc(&t.om, sizeof(double) * (size_t)d)) != hipSuccess)
+  if ((e = mem_alloc((void**)&t.om, sizeof(double) * (size_t)d)) != hipSuccess)
     return e;
-  if ((e = hipMalloc(&t.bmax, 256)) != hipSuccess) return e;
-  if ((e = hipMalloc(&t.bad, 256)) != hipSuccess) return e;
-  if ((e = hipMalloc(&t.bbits, 4 * (size_t)((n * d + 31) / 32))) !=
+  if ((e = mem_alloc((void**)&t.bmax, 256)) != hipSuccess) return e;
+  if ((e = mem_alloc((void**)&t.bad, 256)) != hipSuccess) return e;
+  if ((e = mem_alloc((void**)&t.bbits, 4 * (size_t)((n * d + 31) / 32))) !=
       hipSuccess)
     return e;
   if ((e = hipStreamCreateWithFlags(&t.side, hipStreamNonBlocking)) !=
@@ -1353,10 +1334,10 @@ void dense_tables_free(DenseTables& t) {
   family_free(t.T1);
   family_free(t.T2);
   family_free(t.T3);
-  if (t.om) (void)hipFree(t.om);
-  if (t.bmax) (void)hipFree(t.bmax);
-  if (t.bad) (void)hipFree(t.bad);
-  if (t.bbits) (void)hipFree(t.bbits);
+  mem_free(t.om);
+  mem_free(t.bmax);
+  mem_free(t.bad);
+  mem_free(t.bbits);
   t.bbits = nullptr;
   for (hipEvent_t* ev : {&t.fork, &t.join, &t.t1tot, &t.t2tot, &t.t0done,
                          &t.order_done, &t.sampled}) {
