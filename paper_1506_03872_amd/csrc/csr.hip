@@ -501,10 +501,6 @@ __device__ __forceinline__ int spl_of(int L) {
   return L <= 6 ? 1 : (L == 7 ? 2 : (L == 8 ? 4 : 8));
 }
 
-static inline int spl_class_host(int L) {  // 0..3 for 1, 2, 4, 8 slots/lane
-  return L <= 6 ? 0 : L - 6;
-}
-
 // ---------------------------------------------------------------------------
 // tables of at most 512 items, one wave per table of one slots-per-lane
 // class (every wave of the block runs every step: the block synchronises):
@@ -939,96 +935,227 @@ static void ragged_free(Ragged& R) {
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-static hipError_t ragged_layout(Ragged& R, const int64_t* off_dev, int64_t S,
-                                int esz, hipStream_t st) {
-  R.esz = esz;
-  std::vector<int64_t> off((size_t)S + 1);
-  hipError_t e = hipMemcpyAsync(off.data(), off_dev, off.size() * 8,
-                                hipMemcpyDeviceToHost, st);
-  if (e != hipSuccess || (e = hipStreamSynchronize(st)) != hipSuccess)
-    return e;
-  std::vector<uint64_t> meta((size_t)S);
-  std::vector<BigInfo> big;
-  std::vector<uint32_t> btab, runtab;
-  std::vector<uint32_t> cls[4];
-  int64_t bs = 0, runs = 0, eoff = 0, edges = 0;
-  for (int64_t s = 0; s < S; ++s) {
-    const int64_t N = off[(size_t)s + 1] - off[(size_t)s];
-    if (N <= 512) continue;
-    const int L = ceil_log2_i(N);
-    BigInfo B;
-    B.so = bs;
-    B.o = off[(size_t)s];
-    B.N = N;
-    B.R = (N + kRun - 1) / kRun;
-    B.run0 = runs;
-    B.eoff = eoff;
-    B.edge0 = edges;
-    B.L = L;
-    B.s = (int32_t)s;
-    meta[(size_t)s] = (uint64_t)bs | ((uint64_t)L << 56);
-    const int64_t Np = int64_t(1) << L;
-    for (int64_t b = 0; b < Np / kBigBlk; ++b)
-      btab.push_back((uint32_t)big.size());
-    for (int64_t c = 0; c < B.R; ++c) runtab.push_back((uint32_t)big.size());
-    big.push_back(B);
-    bs += Np;
-    runs += B.R;
-    eoff += B.R + 1;
-    edges += Np / kBigBlk + 1;
+// What a table of N items adds to each running total of the layout: big
+// slots, runs, merge edges, big tables, small slots, small tables of each
+// class.
+constexpr int kLayVals = 9;
+constexpr int kLayPer = 8;                  // tables per thread
+constexpr int kLayTile = 256 * kLayPer;     // tables per workgroup
+
+__device__ __forceinline__ int lay_log2(int64_t N) {
+  return N <= 1 ? 0 : 64 - __clzll((long long)(N - 1));
+}
+
+__device__ __forceinline__ void lay_add(int64_t N, int64_t (&v)[kLayVals]) {
+  const int L = lay_log2(N);
+  if (N > 512) {
+    v[0] += int64_t(1) << L;
+    v[1] += (N + kRun - 1) / kRun;
+    v[2] += (int64_t(1) << L) / kBigBlk + 1;
+    v[3] += 1;
+  } else {
+    v[4] += int64_t(1) << L;
+    const int c = L <= 6 ? 0 : L - 6;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[5 + q] += c == q;
   }
-  int64_t ss = bs;
-  for (int64_t s = 0; s < S; ++s) {
-    const int64_t N = off[(size_t)s + 1] - off[(size_t)s];
-    if (N > 512) continue;
-    const int L = ceil_log2_i(N);
-    meta[(size_t)s] = (uint64_t)ss | ((uint64_t)L << 56);
-    ss += int64_t(1) << L;
-    cls[spl_class_host(L)].push_back((uint32_t)s);
+}
+
+__global__ __launch_bounds__(256) void k_lay_count(const int64_t* off,
+                                                   int64_t S, int64_t* part) {
+  __shared__ int64_t red[4][kLayVals];
+  const int64_t s0 = (int64_t)blockIdx.x * kLayTile +
+                     (int64_t)threadIdx.x * kLayPer;
+  int64_t v[kLayVals] = {};
+  for (int u = 0; u < kLayPer; ++u)
+    if (s0 + u < S) lay_add(off[s0 + u + 1] - off[s0 + u], v);
+#pragma unroll
+  for (int q = 0; q < kLayVals; ++q) {
+    const int64_t x = wave_sum(v[q]);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][q] = x;
   }
-  R.S = S;
-  R.off = off_dev;
-  R.slots = ss;
-  R.big_slots = bs;
-  R.nbig = (int64_t)big.size();
-  R.runs = runs;
-  R.edges = edges;
-  R.cls_off[0] = 0;
-  for (int c = 0; c < 4; ++c)
-    R.cls_off[c + 1] = R.cls_off[c] + (int64_t)cls[c].size();
-  // one layout buffer: meta | big | btab | runtab | small ids
-  const size_t b_meta = al256(8 * (size_t)(S > 0 ? S : 1));
-  const size_t b_big = al256(sizeof(BigInfo) * (big.size() + 1));
-  const size_t b_btab = al256(4 * (btab.size() + 1));
-  const size_t b_run = al256(4 * (runtab.size() + 1));
-  const size_t b_ids = al256(4 * (size_t)(R.cls_off[4] + 1));
-  if ((e = dev_alloc(R.lay, b_meta + b_big + b_btab + b_run + b_ids)) !=
-          hipSuccess ||
-      (e = dev_alloc(R.ent_buf, (size_t)esz * (size_t)(ss > 0 ? ss : 1))) !=
-          hipSuccess ||
-      (e = dev_alloc(R.tot_buf, 8 * (size_t)(S > 0 ? S : 1))) != hipSuccess)
+  __syncthreads();
+  if (threadIdx.x < kLayVals) {
+    int64_t x = 0;
+    for (int w = 0; w < 4; ++w) x += red[w][threadIdx.x];
+    part[(int64_t)blockIdx.x * kLayVals + threadIdx.x] = x;
+  }
+}
+
+// part becomes its exclusive prefix over the workgroups; the totals to tot.
+// A wave per value, 64 workgroups a step.
+__global__ __launch_bounds__(64 * kLayVals) void k_lay_scan(int64_t* part,
+                                                            int64_t nb,
+                                                            int64_t* tot) {
+  const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  int64_t carry = 0;
+  for (int64_t b0 = 0; b0 < nb; b0 += 64) {
+    const int64_t b = b0 + lane;
+    const int64_t x = b < nb ? part[b * kLayVals + q] : 0;
+    const int64_t incl = wave_incl_scan(x);
+    if (b < nb) part[b * kLayVals + q] = carry + incl - x;
+    carry += __shfl(incl, 63, 64);
+  }
+  if (lane == 0) tot[q] = carry;
+}
+
+// meta of every table, the big tables' records and the small tables' ids by
+// class, each in order of the table id
+__global__ __launch_bounds__(256) void k_lay_fill(const int64_t* off,
+                                                  int64_t S,
+                                                  const int64_t* part,
+                                                  const int64_t* tot,
+                                                  uint64_t* meta,
+                                                  BigInfo* big,
+                                                  uint32_t* ids) {
+  __shared__ int64_t wsum[4][kLayVals];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t s0 = (int64_t)blockIdx.x * kLayTile +
+                     (int64_t)threadIdx.x * kLayPer;
+  int64_t v[kLayVals] = {}, at[kLayVals];
+  for (int u = 0; u < kLayPer; ++u)
+    if (s0 + u < S) lay_add(off[s0 + u + 1] - off[s0 + u], v);
+#pragma unroll
+  for (int q = 0; q < kLayVals; ++q) {
+    const int64_t incl = wave_incl_scan(v[q]);
+    at[q] = incl - v[q];
+    if (lane == 63) wsum[wv][q] = incl;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kLayVals; ++q) {
+    at[q] += part[(int64_t)blockIdx.x * kLayVals + q];
+    for (int w = 0; w < wv; ++w) at[q] += wsum[w][q];
+  }
+  const int64_t small0 = tot[0];
+  int64_t cls0[4];  // first id of each class
+  cls0[0] = 0;
+#pragma unroll
+  for (int q = 1; q < 4; ++q) cls0[q] = cls0[q - 1] + tot[4 + q];
+  for (int u = 0; u < kLayPer && s0 + u < S; ++u) {
+    const int64_t s = s0 + u, o = off[s], N = off[s + 1] - o;
+    const int L = lay_log2(N);
+    if (N > 512) {
+      BigInfo B;
+      B.so = at[0];
+      B.o = o;
+      B.N = N;
+      B.R = (N + kRun - 1) / kRun;
+      B.run0 = at[1];
+      B.eoff = at[1] + at[3];  // R + 1 offsets per table
+      B.edge0 = at[2];
+      B.L = L;
+      B.s = (int32_t)s;
+      meta[s] = (uint64_t)at[0] | ((uint64_t)L << 56);
+      big[at[3]] = B;
+    } else {
+      meta[s] = (uint64_t)(small0 + at[4]) | ((uint64_t)L << 56);
+      const int c = L <= 6 ? 0 : L - 6;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (c == q) ids[cls0[q] + at[5 + q]] = (uint32_t)s;
+    }
+    lay_add(N, at);
+  }
+}
+
+// the big table of each 1024-slot block and of each run (one workgroup per
+// big table)
+__global__ __launch_bounds__(256) void k_lay_big(const BigInfo* big,
+                                                 uint32_t* btab,
+                                                 uint32_t* runtab) {
+  const BigInfo B = big[blockIdx.x];
+  const int64_t nblk = (int64_t(1) << B.L) / kBigBlk;
+  for (int64_t b = threadIdx.x; b < nblk; b += 256)
+    btab[B.so / kBigBlk + b] = blockIdx.x;
+  for (int64_t c = threadIdx.x; c < B.R; c += 256)
+    runtab[B.run0 + c] = blockIdx.x;
+}
+
+// one family to lay out: `S` tables, item offsets `off` (device, S + 1)
+struct LayReq {
+  Ragged* R;
+  const int64_t* off;
+  int64_t S;
+  int esz;
+};
+
+static int64_t lay_blocks(int64_t S) { return (S + kLayTile - 1) / kLayTile; }
+
+// layout scratch: the totals of each family, then each family's partials
+static size_t lay_bytes(std::initializer_list<int64_t> S) {
+  size_t b = 8 * kLayVals * S.size();
+  for (int64_t s : S) b += 8 * kLayVals * (size_t)lay_blocks(s);
+  return b;
+}
+
+// The layout of every family, on the device, with one wait for the totals
+// that size its arrays.  (Read back, looped over and uploaded by the host,
+// the three families of 50,000 vectors and 1e5 coordinates took 1.3 ms of
+// a new plan's 3.8, 0.1 now.)
+static hipError_t ragged_layouts(const std::vector<LayReq>& req, void* work,
+                                 hipStream_t st) {
+  hipError_t e;
+  int64_t* tot = (int64_t*)work;
+  int64_t* part = tot + kLayVals * req.size();
+  std::vector<int64_t*> parts;
+  for (size_t f = 0; f < req.size(); ++f) {
+    const int64_t nb = lay_blocks(req[f].S);
+    parts.push_back(part);
+    if (nb > 0)
+      k_lay_count<<<(unsigned)nb, 256, 0, st>>>(req[f].off, req[f].S, part);
+    k_lay_scan<<<1, 64 * kLayVals, 0, st>>>(part, nb, tot + f * kLayVals);
+    part += nb * kLayVals;
+  }
+  std::vector<int64_t> host(kLayVals * req.size());
+  if ((e = hipMemcpyAsync(host.data(), tot, 8 * host.size(),
+                          hipMemcpyDeviceToHost, st)) != hipSuccess ||
+      (e = hipStreamSynchronize(st)) != hipSuccess)
     return e;
-  char* p = (char*)R.lay.p;
-  R.meta = (uint64_t*)p;
-  R.big = p + b_meta;
-  R.btab = (uint32_t*)(p + b_meta + b_big);
-  R.runtab = (uint32_t*)(p + b_meta + b_big + b_btab);
-  R.small_ids = (uint32_t*)(p + b_meta + b_big + b_btab + b_run);
-  R.ent = R.ent_buf.p;
-  R.tot = (double*)R.tot_buf.p;
-  std::vector<char> host(b_meta + b_big + b_btab + b_run + b_ids, 0);
-  memcpy(host.data(), meta.data(), 8 * meta.size());
-  memcpy(host.data() + b_meta, big.data(), sizeof(BigInfo) * big.size());
-  memcpy(host.data() + b_meta + b_big, btab.data(), 4 * btab.size());
-  memcpy(host.data() + b_meta + b_big + b_btab, runtab.data(),
-         4 * runtab.size());
-  char* ids = host.data() + b_meta + b_big + b_btab + b_run;
-  for (int c = 0; c < 4; ++c)
-    memcpy(ids + 4 * R.cls_off[c], cls[c].data(), 4 * cls[c].size());
-  return hipMemcpyAsync(R.lay.p, host.data(), host.size(),
-                        hipMemcpyHostToDevice, st) == hipSuccess
-             ? hipStreamSynchronize(st)
-             : hipErrorInvalidValue;
+  for (size_t f = 0; f < req.size(); ++f) {
+    Ragged& R = *req[f].R;
+    const int64_t* h = host.data() + f * kLayVals;
+    R.esz = req[f].esz;
+    R.S = req[f].S;
+    R.off = req[f].off;
+    R.big_slots = h[0];
+    R.runs = h[1];
+    R.edges = h[2];
+    R.nbig = h[3];
+    R.slots = h[0] + h[4];
+    R.cls_off[0] = 0;
+    for (int c = 0; c < 4; ++c) R.cls_off[c + 1] = R.cls_off[c] + h[5 + c];
+    // one layout buffer: meta | big | btab | runtab | small ids
+    const size_t b_meta = al256(8 * (size_t)(R.S > 0 ? R.S : 1));
+    const size_t b_big = al256(sizeof(BigInfo) * (size_t)(R.nbig + 1));
+    const size_t b_btab = al256(4 * (size_t)(R.big_slots / kBigBlk + 1));
+    const size_t b_run = al256(4 * (size_t)(R.runs + 1));
+    const size_t b_ids = al256(4 * (size_t)(R.cls_off[4] + 1));
+    if ((e = dev_alloc(R.lay, b_meta + b_big + b_btab + b_run + b_ids)) !=
+            hipSuccess ||
+        (e = dev_alloc(R.ent_buf, (size_t)R.esz *
+                                      (size_t)(R.slots > 0 ? R.slots : 1))) !=
+            hipSuccess ||
+        (e = dev_alloc(R.tot_buf, 8 * (size_t)(R.S > 0 ? R.S : 1))) !=
+            hipSuccess)
+      return e;
+    char* p = (char*)R.lay.p;
+    R.meta = (uint64_t*)p;
+    R.big = p + b_meta;
+    R.btab = (uint32_t*)(p + b_meta + b_big);
+    R.runtab = (uint32_t*)(p + b_meta + b_big + b_btab);
+    R.small_ids = (uint32_t*)(p + b_meta + b_big + b_btab + b_run);
+    R.ent = R.ent_buf.p;
+    R.tot = (double*)R.tot_buf.p;
+    if (R.S > 0)
+      k_lay_fill<<<(unsigned)lay_blocks(R.S), 256, 0, st>>>(
+          R.off, R.S, parts[f], tot + f * kLayVals, R.meta, (BigInfo*)R.big,
+          R.small_ids);
+    if (R.nbig > 0)
+      k_lay_big<<<(unsigned)R.nbig, 256, 0, st>>>((const BigInfo*)R.big,
+                                                  R.btab, R.runtab);
+  }
+  return hipGetLastError();
 }
 
 static size_t big_scratch_bytes(const Ragged& R) {
@@ -1118,10 +1245,13 @@ void csr_tables_free(CsrTables& t) {
   ragged_free(t.T2);
   ragged_free(t.T3);
   family_free_pub(t.T0);
-  void* ps[] = {t.at_ptr, t.at_row, t.at_val, t.at_src, t.bt_ptr, t.bt_row,
-                t.bt_val, t.bt_src, t.at_w, t.om, t.bmax, t.bad, t.at_pay,
-                t.bsig, t.bt_pay, t.bh};
+  void* ps[] = {t.at_ptr, t.at_row, t.at_val, t.at_src, t.at_w, t.om, t.bmax,
+                t.bad, t.at_pay, t.bsig, t.bt_pay, t.bh};
   for (void* p : ps) mem_free(p);
+  if (!t.gram)  // else they are A's
+    for (void* p : {(void*)t.bt_ptr, (void*)t.bt_row, (void*)t.bt_val,
+                    (void*)t.bt_src})
+      mem_free(p);
   t.at_ptr = t.bt_ptr = nullptr;
   t.at_row = t.bt_row = nullptr;
   t.at_val = t.bt_val = nullptr;
@@ -1204,19 +1334,30 @@ hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st) {
         (e = mem_alloc((void**)&t.bmax, 256)) != hipSuccess ||
         (e = mem_alloc((void**)&t.om, 8 * (size_t)d)) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
-        (e = mem_alloc((void**)&t.bt_ptr, 8 * (size_t)(d + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_row, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_val, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = mem_alloc((void**)&t.bt_row, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
-        (e = mem_alloc((void**)&t.bt_val, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_src, 4 * (size_t)(t.nnzA + 1))) != hipSuccess ||
-        (e = mem_alloc((void**)&t.bt_src, 4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_w, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.at_pay, 8 * (size_t)(t.nnzA + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.bsig, 8 * (size_t)(n + 1))) != hipSuccess ||
         (e = mem_alloc((void**)&t.bt_pay, 8 * (size_t)(t.nnzB + 1))) != hipSuccess ||
         (e = family_alloc_pub(t.T0, 1, d)) != hipSuccess)
       return e;
+    if (t.gram) {  // B is A, and so is its transpose
+      t.bt_ptr = t.at_ptr;
+      t.bt_row = t.at_row;
+      t.bt_val = t.at_val;
+      t.bt_src = t.at_src;
+    } else if ((e = mem_alloc((void**)&t.bt_ptr, 8 * (size_t)(d + 1))) !=
+                   hipSuccess ||
+               (e = mem_alloc((void**)&t.bt_row,
+                              4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+               (e = mem_alloc((void**)&t.bt_val,
+                              4 * (size_t)(t.nnzB + 1))) != hipSuccess ||
+               (e = mem_alloc((void**)&t.bt_src,
+                              4 * (size_t)(t.nnzB + 1))) != hipSuccess) {
+      return e;
+    }
     int64_t cap = 1024;
     while (cap < 2 * t.nnzB) cap <<= 1;
     t.bh_mask = (uint64_t)(cap - 1);
@@ -1236,7 +1377,7 @@ hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st) {
       k_trans_gather<<<blocks_of(t.nnzA, 256 * 8) < 2048
                            ? blocks_of(t.nnzA, 256 * 8) : 2048,
                        256, 0, st>>>(t.at_src, t.in.a_val, t.nnzA, t.at_val);
-    if (t.nnzB > 0)
+    if (t.nnzB > 0 && !t.gram)
       k_trans_gather<<<blocks_of(t.nnzB, 256 * 8) < 2048
                            ? blocks_of(t.nnzB, 256 * 8) : 2048,
                        256, 0, st>>>(t.bt_src, t.in.b_val, t.nnzB, t.bt_val);
@@ -1272,21 +1413,25 @@ hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st) {
         t.in.b_ptr, t.in.b_idx, n, d, t.bh, t.bh_mask);
   // transposes
   const int64_t nz = t.nnzA > t.nnzB ? t.nnzA : t.nnzB;
-  if ((e = dev_alloc(t.work, sort_bytes(nz))) != hipSuccess) return e;
+  if ((e = dev_alloc(t.work, std::max(sort_bytes(nz),
+                                      lay_bytes({m, d, d})))) != hipSuccess)
+    return e;
   const SortBufs sb = sort_carve(t.work.p, nz);
   if ((e = csr_transpose(t.in.a_ptr, t.in.a_idx, t.in.a_val, m, d, t.nnzA,
                          t.at_ptr, t.at_row, t.at_src, t.at_val, sb,
-                         st)) != hipSuccess ||
+                         st)) != hipSuccess)
+    return e;
+  if (!t.gram &&
       (e = csr_transpose(t.in.b_ptr, t.in.b_idx, t.in.b_val, n, d, t.nnzB,
                          t.bt_ptr, t.bt_row, t.bt_src, t.bt_val, sb,
                          st)) != hipSuccess)
     return e;
-  // layouts (host)
-  // T1's entries carry T3's meta and T2's the signature of b_j (32 bytes);
-  // T3's carry no payload
-  if ((e = ragged_layout(t.T3, t.in.a_ptr, m, 16, st)) != hipSuccess ||
-      (e = ragged_layout(t.T1, t.at_ptr, d, 32, st)) != hipSuccess ||
-      (e = ragged_layout(t.T2, t.bt_ptr, d, 32, st)) != hipSuccess)
+  // layouts; T1's entries carry T3's meta and T2's the signature of b_j (32
+  // bytes); T3's carry no payload
+  if ((e = ragged_layouts({{&t.T3, t.in.a_ptr, m, 16},
+                           {&t.T1, t.at_ptr, d, 32},
+                           {&t.T2, t.bt_ptr, d, 32}},
+                          t.work.p, st)) != hipSuccess)
     return e;
   // the T1 and T2 payloads by transpose position (structure only)
   if (t.nnzA > 0)

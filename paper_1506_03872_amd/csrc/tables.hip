@@ -231,6 +231,9 @@ __global__ void k_run_offsets(const double* Ssum, int64_t S, int64_t R,
   tot[seg] = e;
 }
 
+__global__ void k_col_runoffsets(const double* rtot, int64_t S, int64_t R,
+                                 double* E, double* tot);
+
 // quanta with the item's sign bit in bit 63 (quanta are below 2^62)
 template <class W>
 __global__ void k_quantize(W w, int64_t S, int64_t N, int64_t R, int L,
@@ -280,7 +283,13 @@ static hipError_t uniform_quanta(W w, int64_t S, int64_t N, int L,
   hipError_t e = launch_fill_u64(q, S << L, 0ull, st);
   if (e != hipSuccess) return e;
   k_run_sums<W><<<grid_for(S * R, 256), 256, 0, st>>>(w, S, N, R, Ssum);
-  k_run_offsets<<<grid_for(S, 256), 256, 0, st>>>(Ssum, S, R, E, tot);
+  // few long tables (the stage-0 table of many coordinates: one of 782 runs
+  // takes 13 us here, 110 in one thread's walk through memory): a workgroup
+  // each
+  if (S <= 4096 && R > 16)
+    k_col_runoffsets<<<(unsigned)S, 256, 0, st>>>(Ssum, S, R, E, tot);
+  else
+    k_run_offsets<<<grid_for(S, 256), 256, 0, st>>>(Ssum, S, R, E, tot);
   k_quantize<W><<<grid_for(S * R, 256), 256, 0, st>>>(w, S, N, R, L, E, tot,
                                                         q);
   return hipGetLastError();
