@@ -982,21 +982,35 @@ __global__ __launch_bounds__(256) void k_lay_count(const int64_t* off,
   }
 }
 
-// part becomes its exclusive prefix over the workgroups; the totals to tot.
-// A wave per value, 64 workgroups a step.
-__global__ __launch_bounds__(64 * kLayVals) void k_lay_scan(int64_t* part,
-                                                            int64_t nb,
-                                                            int64_t* tot) {
+// part (nb workgroups x V values) becomes its exclusive prefix over the
+// workgroups; the totals to tot.  A wave per value, 64 workgroups a step.
+__global__ __launch_bounds__(1024) void k_scan_parts(int64_t* part,
+                                                     int64_t nb, int V,
+                                                     int64_t* tot) {
   const int q = threadIdx.x >> 6, lane = threadIdx.x & 63;
   int64_t carry = 0;
   for (int64_t b0 = 0; b0 < nb; b0 += 64) {
     const int64_t b = b0 + lane;
-    const int64_t x = b < nb ? part[b * kLayVals + q] : 0;
+    const int64_t x = b < nb ? part[b * V + q] : 0;
     const int64_t incl = wave_incl_scan(x);
-    if (b < nb) part[b * kLayVals + q] = carry + incl - x;
+    if (b < nb) part[b * V + q] = carry + incl - x;
     carry += __shfl(incl, 63, 64);
   }
   if (lane == 0) tot[q] = carry;
+}
+
+hipError_t launch_scan_parts(int64_t* part, int64_t nb, int V, int64_t* tot,
+                             hipStream_t st) {
+  if (V < 1 || V > 16) return hipErrorInvalidValue;
+  k_scan_parts<<<1, 64 * V, 0, st>>>(part, nb, V, tot);
+  return hipGetLastError();
+}
+
+hipError_t launch_absmax(const float* v, int64_t n, float* amax,
+                         hipStream_t st) {
+  const int64_t want = blocks_of(n > 0 ? n : 1, 1024 * 16);
+  k_absmax<<<(unsigned)(want < 256 ? want : 256), 1024, 0, st>>>(v, n, amax);
+  return hipGetLastError();
 }
 
 // meta of every table, the big tables' records and the small tables' ids by
@@ -1104,7 +1118,9 @@ static hipError_t ragged_layouts(const std::vector<LayReq>& req, void* work,
     parts.push_back(part);
     if (nb > 0)
       k_lay_count<<<(unsigned)nb, 256, 0, st>>>(req[f].off, req[f].S, part);
-    k_lay_scan<<<1, 64 * kLayVals, 0, st>>>(part, nb, tot + f * kLayVals);
+    if ((e = launch_scan_parts(part, nb, kLayVals, tot + f * kLayVals, st)) !=
+        hipSuccess)
+      return e;
     part += nb * kLayVals;
   }
   std::vector<int64_t> host(kLayVals * req.size());
@@ -1369,10 +1385,8 @@ hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st) {
     // first build: regather the transposed values, then the tables
     if ((e = launch_fill_u64((uint64_t*)t.bmax, 1, 0ull, st)) != hipSuccess)
       return e;
-    const int64_t nzb = t.nnzB > 0 ? t.nnzB : 1;
-    k_absmax<<<blocks_of(nzb, 1024 * 16) < 256 ? blocks_of(nzb, 1024 * 16)
-                                               : 256,
-               1024, 0, st>>>(t.in.b_val, t.nnzB, t.bmax);
+    if ((e = launch_absmax(t.in.b_val, t.nnzB, t.bmax, st)) != hipSuccess)
+      return e;
     if (t.nnzA > 0)
       k_trans_gather<<<blocks_of(t.nnzA, 256 * 8) < 2048
                            ? blocks_of(t.nnzA, 256 * 8) : 2048,

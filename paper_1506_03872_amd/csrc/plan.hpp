@@ -303,6 +303,12 @@ struct CsrTables {
 hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st);
 // structure and finiteness of sparse inputs (flag: device, 8-byte aligned
 // scratch); hipErrorInvalidValue when malformed or non-finite.  Synchronises.
+// exclusive prefixes over nb workgroups of V (<= 16) values each, and totals
+hipError_t launch_scan_parts(int64_t* part, int64_t nb, int V, int64_t* tot,
+                             hipStream_t st);
+// *amax (cleared before) = max |v| over n values
+hipError_t launch_absmax(const float* v, int64_t n, float* amax,
+                         hipStream_t st);
 hipError_t csr_validate(const CsrView& in, int64_t m, int64_t n, int64_t d,
                         int64_t nnzA, int64_t nnzB, int* flag,
                         hipStream_t st);
