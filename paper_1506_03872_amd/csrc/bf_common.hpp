@@ -88,6 +88,8 @@ struct GemmArgs {
   unsigned* hist;
   const unsigned* maxes;  // n2, n1, eta maxima of A, then (+4) of B
   int screen;      // 1: no error margin (screening by the computed value)
+  int coarse;      // 1: fbin32's bins (screening, or a t-th bound below the
+                   // finer ones)
   float mg_max;    // margin upper bound over all pairs (cheap pre-test)
   // pass B
   const unsigned* tau_bits;  // lower bound (float bits)
@@ -103,55 +105,83 @@ __device__ __forceinline__ int fbin32(uint32_t bits) {
   return (int)(bits >> 20) & 2047;
 }
 
-// Pass A's bins of the lower bounds.  Screening takes fbin32's (their edges
+// Pass A's bins of the bounds.  Screening takes fbin32's 2048 (their edges
 // are part of its result: the pairs it re-ranks are those above one).  The
-// certified filter's result does not depend on tau, only its survivors do,
-// so its bins are 64 per octave over the 8 octaves below the largest
-// possible |c| (bins 1536 up) and fbin32's digits below those: at 1e5 x 1e6
-// x 256 in bf16 fbin32's edge lay up to 12% under the t-th bound and let
-// 1.7e6 pairs through.  fine0 is the first fine digit (a multiple of 8, so
-// that it is a coarse edge too), -1 for screening.
+// certified filter's result does not depend on tau, only its survivors do:
+// it counts the lower bounds |c^| - margin in 1024 bins, 32 per octave over
+// the 8 octaves below the largest possible |c| (bins 768 up) and 4 per
+// octave over the 192 below those, and the upper bounds |c^| + margin in
+// 1024 more of the same edges, which say how many pairs will pass.  (With
+// fbin32's the edge lay up to 12% under the t-th bound and let 1.7e6 pairs
+// through at 1e5 x 1e6 x 256 in bf16.)  fine0 is the first fine digit, a
+// multiple of 8, so that it is a coarse edge too; -1: fbin32's bins.
+constexpr int kUpperBins = 1024;  // first bin of the upper bounds
+
 struct BoundBins {
   int fine0;
   __device__ __forceinline__ int bin(float v) const {
     const uint32_t bits = __float_as_uint(v);
     if (fine0 < 0) return fbin32(bits);
-    const int f = (int)(bits >> 17) - fine0;
-    if (f >= 0) return f < 512 ? 1536 + f : 2047;
-    const int c = 1536 - (fine0 >> 3) + (int)(bits >> 20);
+    const int f = (int)(bits >> 18) - fine0;
+    if (f >= 0) return f < 256 ? 768 + f : 1023;
+    const int c = 768 - (fine0 >> 3) + (int)(bits >> 21);
     return c > 0 ? c : 0;
   }
   // float bits of the bin's lower edge
   __device__ __forceinline__ unsigned edge(int b) const {
     if (b <= 0) return 0u;
     if (fine0 < 0) return (unsigned)b << 20;
-    if (b >= 1536) return (unsigned)(fine0 + b - 1536) << 17;
-    const int c = b - 1536 + (fine0 >> 3);
-    return c > 0 ? (unsigned)c << 20 : 0u;
+    if (b >= 768) return (unsigned)(fine0 + b - 768) << 18;
+    const int c = b - 768 + (fine0 >> 3);
+    return c > 0 ? (unsigned)c << 21 : 0u;
+  }
+  // bins of lower bounds: [0, count)
+  __device__ __forceinline__ int count() const {
+    return fine0 < 0 ? 2048 : kUpperBins;
   }
 };
 
 __device__ __forceinline__ BoundBins bound_bins(const unsigned* maxes,
-                                                int screen) {
+                                                bool coarse) {
   BoundBins r;
   r.fine0 = -1;
-  if (!screen) {
+  if (!coarse) {
     // |c| <= ||a||_2 ||b||_2 (a larger value falls in the top bin)
     const float top = __uint_as_float(maxes[0]) * __uint_as_float(maxes[4]);
-    const int hi = (int)(__float_as_uint(top) >> 17) | 7;
-    r.fine0 = hi > 511 ? hi - 511 : 0;
+    const int hi = (int)(__float_as_uint(top) >> 18) | 7;
+    r.fine0 = hi > 255 ? hi - 255 : 0;
   }
   return r;
+}
+
+// one value of pass A into a histogram
+__device__ __forceinline__ void count_bounds(const BoundBins& bins, float c,
+                                             float mg, unsigned* hist) {
+  const float low = fabsf(c) - mg;
+  if (low > 0.0f) atomicAdd(&hist[bins.bin(low)], 1u);
+  if (bins.fine0 >= 0)
+    atomicAdd(&hist[kUpperBins + bins.bin(fabsf(c) + mg)], 1u);
+}
+
+// margin of a pair: a bound on |c^ - c_fp32|
+__device__ __forceinline__ float pair_margin(float kappa, float onepu,
+                                             float d_f, const VecInfo& va,
+                                             const VecInfo& vb) {
+  return kappa * va.n2 * vb.n2 + onepu * (va.eta * vb.n1 + vb.eta * va.n1) +
+         d_f * va.eta * vb.eta;
 }
 
 // the largest margin over all pairs
 __device__ __forceinline__ float margin_max(const GemmArgs& g) {
   if (g.screen) return 0.0f;
-  const unsigned* m = g.maxes;
-  return g.kappa * __uint_as_float(m[0]) * __uint_as_float(m[4]) +
-         g.onepu * (__uint_as_float(m[2]) * __uint_as_float(m[5]) +
-                    __uint_as_float(m[6]) * __uint_as_float(m[1])) +
-         g.d_f * __uint_as_float(m[2]) * __uint_as_float(m[6]);
+  VecInfo a{}, b{};
+  a.n2 = __uint_as_float(g.maxes[0]);
+  a.n1 = __uint_as_float(g.maxes[1]);
+  a.eta = __uint_as_float(g.maxes[2]);
+  b.n2 = __uint_as_float(g.maxes[4]);
+  b.n1 = __uint_as_float(g.maxes[5]);
+  b.eta = __uint_as_float(g.maxes[6]);
+  return pair_margin(g.kappa, g.onepu, g.d_f, a, b) * (1.0f + 1e-5f);
 }
 
 // E8M0 byte of a vector's power-of-two inverse scale (the MFMA multiplies

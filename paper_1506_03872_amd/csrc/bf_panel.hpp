@@ -71,25 +71,26 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   __shared__ int sc1[P == kFP8 ? TB * 32 : 1];
   __shared__ unsigned hist[HIST ? 2048 : 1];
   __shared__ unsigned thr_s;
+  // survivors of each wave on their way to memory
+  __shared__ uint64_t qkey[HIST ? 1 : 4][HIST ? 1 : 64];
+  __shared__ float qval[HIST ? 1 : 4][HIST ? 1 : 64];
   const GemmArgs& g = a.g;
   const int t = threadIdx.x, lane = t & 63;
   const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
   const int rl = lane & 31, rg = lane >> 5;
   BoundBins bins{-1};
-  float mg2 = 0.0f;  // pass A keeps what may reach tau after the margins
   if (HIST) {
-    bins = bound_bins(g.maxes, g.screen);
-    mg2 = 2.0f * margin_max(g);
+    bins = bound_bins(g.maxes, g.coarse);
     for (int b = t; b < 2048; b += 256) hist[b] = 0;
     if (t == 0) thr_s = 0u;
     __syncthreads();
   }
+  // |c| below `pre` is dropped at once: |c| + margin does not reach tau (pass
+  // B; 1 - 2^-20 absorbs the roundings of the comparisons), or the bound
+  // that `target` lower bounds counted so far lie above (pass A)
   const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
-  // |c| below `pre` is dropped at once.  Pass B: |c| + margin >= tau only
-  // when |c| >= tau - mg_max, and tau (1 - 2^-20) absorbs the roundings of
-  // both comparisons.  Pass A: `pre` follows the bound that this workgroup
-  // or another already holds `target` values above.
-  float pre = HIST ? 0.0f : fmaf(tau, 1.0f - 0x1p-20f, -g.mg_max);
+  const float mg_max = HIST ? margin_max(g) : g.mg_max;
+  float pre = HIST ? -mg_max : fmaf(tau, 1.0f - 0x1p-20f, -mg_max);
   // Work items (a row panel x a run of column tiles) in segment-major
   // order; each XCD takes a contiguous share, so that the workgroups of one
   // L2 stream the same columns at the same time.
@@ -137,10 +138,25 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
     if (P == kFP8 && wv < TB / 2)
       lds_load4(a.sb + tl * (TB * 32) + wv * 64 + lane, sdst + wv * 64);
   };
-  // the kept values of one 64 x 32 block
+  // Survivors wait in the wave's LDS queue until 64 are there, so that the
+  // shared list's counter takes an atomic per 33 or more of them: one each
+  // serialises at 12 ns a survivor (30,000 x 30,000 x 256 sparse columns in
+  // bf16: 622 us, 388 with the queue).
+  int qn = 0;
+  auto flush = [&]() {
+    if (qn == 0) return;
+    unsigned long long at = 0;
+    if (lane == 0) at = atomicAdd(g.ccount, (unsigned long long)qn);
+    at = __shfl(at, 0, 64) + (unsigned)lane;
+    if (lane < qn && (int64_t)at < g.ccap) {
+      g.ckey[at] = qkey[wv][lane];
+      g.cval[at] = qval[wv][lane];
+    }
+    qn = 0;
+  };
+  // the kept values of one 64 x 32 block (the whole wave)
   auto emit = [&](const f16v& c0, const f16v& c1, int64_t j) {
-    if (j >= g.n) return;
-    const VecInfo vb = g.ib[j];
+    const VecInfo vb = g.ib[j < g.n ? j : g.n - 1];
     // an opaque copy of the lane's first row: without it the 32 rows'
     // addresses are computed ahead of the tile loop and spill
     int row = 4 * rg;
@@ -150,26 +166,30 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
         const float c = u ? c1[e] : c0[e];
-        if (!(fabsf(c) >= pre)) continue;
+        bool keep = fabsf(c) >= pre;
+        if (!__any(keep)) continue;
         const int64_t i = i0 + (u * 32 + 8 * (e >> 2) + (e & 3) + row);
-        if (i >= g.m_rows) continue;
+        keep = keep && j < g.n && i < g.m_rows;
         float mg = 0.0f;
-        if (!g.screen) {
-          const VecInfo va = g.ia[i * g.a_stride_rows];
-          mg = g.kappa * va.n2 * vb.n2 +
-               g.onepu * (va.eta * vb.n1 + vb.eta * va.n1) +
-               g.d_f * va.eta * vb.eta;
-        }
+        if (keep && !g.screen)
+          mg = pair_margin(g.kappa, g.onepu, g.d_f,
+                           g.ia[i * g.a_stride_rows], vb);
         if (HIST) {
-          const float low = fabsf(c) - mg;
-          if (low > 0.0f) atomicAdd(&hist[bins.bin(low)], 1u);
-        } else if (fabsf(c) + mg >= tau) {
-          const unsigned long long p = atomicAdd(g.ccount, 1ull);
-          if ((int64_t)p < g.ccap) {
-            g.ckey[p] = (uint64_t)(i * g.m_key) * (uint64_t)g.n + (uint64_t)j;
-            g.cval[p] = c;
-          }
+          if (keep) count_bounds(bins, c, mg, hist);
+          continue;
         }
+        keep = keep && fabsf(c) + mg >= tau;
+        const uint64_t who = __ballot(keep);
+        const int cnt = __popcll(who);
+        if (cnt == 0) continue;
+        if (qn + cnt > 64) flush();
+        if (keep) {
+          const int at = qn + __popcll(who & ((1ull << lane) - 1));
+          qkey[wv][at] = (uint64_t)(i * g.m_key) * (uint64_t)g.n +
+                         (uint64_t)j;
+          qval[wv][at] = c;
+        }
+        qn += cnt;
       }
   };
   auto compute = [&](const char* buf, const int* sc, int64_t tl) {
@@ -212,7 +232,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
 #pragma unroll
       for (int e = 0; e < 16; ++e)
         mx = fmaxf(fmaxf(mx, fabsf(c0[e])), fabsf(c1[e]));
-      if (mx >= pre) {
+      if (__any(mx >= pre)) {
         emit(c0, c1, tl * (TB * 32) + cb * 32 + rl);
         // emit's loads end here, for the reason given in load_a
         __builtin_amdgcn_s_waitcnt(0x0f70);
@@ -234,15 +254,16 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
                                   __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     if (wv == 0) {
-      const int top = 2047 - 32 * lane;
+      const int per = bins.count() / 64;
+      const int hi = bins.count() - 1 - per * lane;
       unsigned sum = 0;
-      for (int b = top; b > top - 32; --b) sum += hist[b];
+      for (int b = hi; b > hi - per; --b) sum += hist[b];
       const unsigned incl = wave_incl_scan(sum);
       const uint64_t reach = __ballot((int64_t)incl >= a.target);
       if (reach && lane == __builtin_ctzll(reach)) {
         unsigned acc = incl - sum;
-        int b = top;
-        for (; b > top - 31; --b) {
+        int b = hi;
+        for (; b > hi - per + 1; --b) {
           acc += hist[b];
           if ((int64_t)acc >= a.target) break;
         }
@@ -252,7 +273,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
     __syncthreads();
     for (int b = t; b < 2048; b += 256) hist[b] = 0;
     __syncthreads();
-    pre = __uint_as_float(thr_s) - mg2;
+    pre = __uint_as_float(thr_s) - mg_max;
   };
   if (item < hi) {
     locate(item);
@@ -262,7 +283,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
     bool more = true;
     // one tile: wait for its loads, start the next tile's into the other
     // buffer (every wave has left that one at the barrier), compute
-    auto step = [&](char* cur, int* scur, char* oth, int* soth) {
+    auto step = [&](char* cur, int* icur, char* oth, int* ioth) {
       const int64_t tl = tile;
       int64_t nitem = item, ntile = tile + 1, ni0 = i0, nend = tend;
       if (ntile == tend) {
@@ -280,8 +301,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       }
       __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): this wave's loads
       __syncthreads();
-      if (more) fetch(ntile, oth, soth);
-      compute(cur, scur, tl);
+      if (more) fetch(ntile, oth, ioth);
+      compute(cur, icur, tl);
       ++done;
       if (HIST && (done & (done - 1)) == 0) raise();
       if (more) {
@@ -305,6 +326,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
     __syncthreads();
     for (int b = t; b < 2048; b += 256)
       if (hist[b]) atomicAdd(&g.hist[b], hist[b]);
+  } else {
+    flush();
   }
 }
 

@@ -162,7 +162,7 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
   const char* Bb = (const char*)g.B;
   const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
   BoundBins bins{-1};
-  if (HIST) bins = bound_bins(g.maxes, g.screen);
+  if (HIST) bins = bound_bins(g.maxes, g.coarse);
   const int64_t G = gridDim.x;  // a multiple of 8
   const int64_t v = (int64_t)(blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
   // this thread's 4 x 16 bytes of each operand's stage: rows (t >> 3) +
@@ -341,13 +341,10 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
           const VecInfo va = g.ia[i * g.a_stride_rows];
           const VecInfo vb = g.ib[j];
           const float mg = g.screen ? 0.0f
-                                    : g.kappa * va.n2 * vb.n2 +
-                                      g.onepu * (va.eta * vb.n1 +
-                                                 vb.eta * va.n1) +
-                                      g.d_f * va.eta * vb.eta;
+                                    : pair_margin(g.kappa, g.onepu, g.d_f,
+                                                  va, vb);
           if (HIST) {
-            const float lo = fabsf(c) - mg;
-            if (lo > 0.0f) atomicAdd(&hist[bins.bin(lo)], 1u);
+            count_bounds(bins, c, mg, hist);
           } else if (fabsf(c) + mg >= tau) {
             const unsigned long long p = atomicAdd(g.ccount, 1ull);
             if ((int64_t)p < g.ccap) {
@@ -417,19 +414,20 @@ __global__ __launch_bounds__(1024) void k_vecinfo_max(const VecInfo* va,
 }
 
 // One wave over pass A's histogram: tau_bits = the lower edge of the bin
-// holding the t-th largest bound, from the top (0 when fewer than t bounds
-// are positive), and est = the subset's pairs that pass B's filter may
-// keep, those whose lower bound is at least tau - 2 mg_max.  (One thread
-// walking the 2048 bins took 54 us.)
+// holding the t-th largest lower bound, from the top (0 when fewer than t
+// are positive), and est = the subset's pairs that pass B's filter will
+// keep: those whose upper bound (screening: value) reaches that bin.  (One
+// thread walking the 2048 bins took 54 us.)
 __global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g, int64_t t,
                                                unsigned* tau_bits,
                                                unsigned long long* est) {
   const int lane = threadIdx.x;
-  const BoundBins bins = bound_bins(g.maxes, g.screen);
-  // lane l: bins 2047 - 32 l down to 2016 - 32 l
-  const int hi = 2047 - 32 * lane;
+  const BoundBins bins = bound_bins(g.maxes, g.coarse);
+  // lane l: `per` bins from the top
+  const int per = bins.count() / 64;
+  const int hi = bins.count() - 1 - per * lane;
   unsigned long long sum = 0;
-  for (int b = hi; b > hi - 32; --b) sum += g.hist[b];
+  for (int b = hi; b > hi - per; --b) sum += g.hist[b];
   const unsigned long long incl = wave_incl_scan(sum);
   const uint64_t reach = __ballot((int64_t)incl >= t);
   const int src = reach ? __builtin_ctzll(reach) : 63;
@@ -437,20 +435,18 @@ __global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g, int64_t t,
   if (reach && lane == src) {
     unsigned long long acc = incl - sum;
     found = hi;
-    for (; found > hi - 31; --found) {
+    for (; found > hi - per + 1; --found) {
       acc += g.hist[found];
       if ((int64_t)acc >= t) break;
     }
   }
   found = __shfl(found, src, 64);
-  const unsigned tb = bins.edge(found);
-  const float low = __uint_as_float(tb) - 2.0f * margin_max(g);
-  const int bl = low > 0.0f ? bins.bin(low) : 0;
+  const unsigned* up = bins.fine0 < 0 ? g.hist : g.hist + kUpperBins;
   unsigned long long in = 0;
-  for (int b = hi; b > hi - 32; --b) in += b >= bl ? g.hist[b] : 0u;
+  for (int b = hi; b > hi - per; --b) in += b >= found ? up[b] : 0u;
   in = wave_sum(in);
   if (lane == 0) {
-    *tau_bits = tb;
+    *tau_bits = bins.edge(found);
     *est = in;
   }
 }
@@ -619,6 +615,7 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   // computed value, keep the t_screen largest, re-rank those in fp32
   const bool screen = prec != kF32 && cap_hint > 0;
   a.screen = screen ? 1 : 0;
+  a.coarse = a.screen;
   a.mg_max = 0.0f;
   // pass A over every stride-th row of A
   const int64_t stride = m >= 128 * 64 ? 64 : (m >= 128 * 8 ? 8 : 1);
@@ -636,6 +633,14 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
     else launch_gemm<kFP8>(a, hist_pass, st);
     return hipGetLastError();
   };
+  // pass A's subset holds about 1/stride of the pairs
+  const int64_t target = screen ? (cap_hint + stride - 1) / stride : t;
+  auto pass_a = [&]() -> hipError_t {
+    const hipError_t r = gemm(true, target);
+    if (r == hipSuccess)
+      k_bf_tau<<<1, 64, 0, st>>>(a, target, tau_bits, est);
+    return r;
+  };
   if (tau_user >= 0.0f) {
     // a threshold given by the caller (a lower bound it knows for the t-th
     // largest |c|): pass B keeps every pair that may reach it
@@ -645,25 +650,32 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
         hipSuccess)
       return e;
   } else {
-    // pass A's subset holds about 1/stride of the pairs
-    const int64_t target =
-        screen ? (cap_hint + stride - 1) / stride : t;
-    if ((e = gemm(true, target)) != hipSuccess) return e;
-    k_bf_tau<<<1, 64, 0, st>>>(a, target, tau_bits, est);
+    if ((e = pass_a()) != hipSuccess) return e;
   }
   (void)hipEventRecord(ev[1], st);
   // the largest margin over all pairs, for pass B's pre-test, and pass A's
   // estimate of its survivors
   unsigned long long sub = 0;
   {
-    unsigned mxb[18];
-    if ((e = hipMemcpyAsync(mxb, maxes, sizeof mxb, hipMemcpyDeviceToHost,
-                            st)) != hipSuccess ||
-        (e = hipStreamSynchronize(st)) != hipSuccess)
-      return e;
+    unsigned mxb[50];  // tau, then (+32) the maxima, (+48) the estimate
+    auto read = [&]() -> hipError_t {
+      const hipError_t r = hipMemcpyAsync(mxb, tau_bits, sizeof mxb,
+                                          hipMemcpyDeviceToHost, st);
+      return r != hipSuccess ? r : hipStreamSynchronize(st);
+    };
+    if ((e = read()) != hipSuccess) return e;
+    if (tau_user < 0.0f && !a.coarse && mxb[0] == 0) {
+      // fewer than t bounds above the finer bins' range (200 octaves under
+      // the largest possible |c|): the bins over all floats
+      a.coarse = 1;
+      if ((e = launch_fill_u64((uint64_t*)hist, 1024, 0ull, st)) !=
+              hipSuccess ||
+          (e = pass_a()) != hipSuccess || (e = read()) != hipSuccess)
+        return e;
+    }
     float f[8];
-    memcpy(f, mxb, sizeof f);
-    memcpy(&sub, mxb + 16, 8);
+    memcpy(f, mxb + 32, sizeof f);
+    memcpy(&sub, mxb + 48, 8);
     const double mgm = screen ? 0.0
                               : (double)a.kappa * f[0] * f[4] +
                                     (double)a.onepu * (f[2] * f[5] + f[6] * f[1]) +

@@ -38,6 +38,30 @@ def test_bins_over_the_exponent_range(gpu, prec, span):
     assert np.array_equal(c, c_ex)
 
 
+@pytest.mark.parametrize("prec", [0, 1, 2])
+def test_a_bound_below_every_finer_bin(gpu, prec):
+    # one huge pair of vectors, all others 2^-240 of their product: the t-th
+    # bound lies below the certified filter's bins, and it takes those that
+    # cover all floats
+    g = np.random.default_rng(7)
+    m, n, d, t = 140, 70, 12, 50
+    A = g.integers(1, 9, size=(m, d)).astype(np.float32)
+    B = g.integers(1, 9, size=(n, d)).astype(np.float32)
+    A *= np.float32(2.0 ** -60)
+    B *= np.float32(2.0 ** -60)
+    A[0] *= np.float32(2.0 ** 120)
+    B[0] *= np.float32(2.0 ** 120)
+    # the huge vectors' products with the others are left out: disjoint halves
+    A[0, d // 2:] = 0.0
+    B[0, d // 2:] = 0.0
+    A[1:, :d // 2] = 0.0
+    B[1:, :d // 2] = 0.0
+    k, c, _ = run(A, B, t, prec)
+    k_ex, c_ex = oracle.bruteforce_dense(A, B, t)
+    assert np.array_equal(k, k_ex)
+    assert np.array_equal(c, c_ex)
+
+
 @pytest.mark.parametrize("prec", [0, 1])
 @pytest.mark.parametrize("sampled", [True, False])
 def test_more_survivors_than_the_first_list(gpu, prec, sampled):
