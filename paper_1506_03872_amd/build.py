@@ -35,6 +35,7 @@ FLAGS = [
 # so its epilogue reads them without a copy out of the accumulation file
 EXTRA = {
     "bruteforce.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+    "bf_panel_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "bf_panel_bf16.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
     "bf_panel_fp8.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
 }

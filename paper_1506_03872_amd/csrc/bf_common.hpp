@@ -212,6 +212,8 @@ hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
 hipError_t launch_panel(const GemmArgs& a, int prec, int64_t d, bool hist,
                         int64_t target, const int* sb, hipStream_t st);
 // per-precision launches (one file each); grid 0: as many workgroups as fit
+hipError_t launch_panel_f32(const PanelArgs& a, int ns, bool hist,
+                            int64_t grid, hipStream_t st);
 hipError_t launch_panel_bf16(const PanelArgs& a, int ns, bool hist,
                              int64_t grid, hipStream_t st);
 hipError_t launch_panel_fp8(const PanelArgs& a, int ns, bool hist,

@@ -7,12 +7,16 @@
 namespace mad {
 
 // The panel kernel keeps K in registers: up to 16 steps of 16 bytes per lane
-// and 32 rows (K = 256 in bf16, 512 in fp8: 128 VGPRs for 64 rows).  Longer
-// vectors, and fp32, whose MFMAs take 64 cycles per 256 bytes of operand and
-// are not short of LDS bandwidth, stay with the LDS-tiled kernel.
+// for 64 rows (K = 256 in bf16, 512 in fp8: 128 VGPRs), in fp32 up to 32
+// steps (K = 256), for 32 rows from 20 on.  Longer vectors stay with the
+// LDS-tiled kernel.
 int panel_steps(int prec, int64_t d) {
   if (prec == kBF16 && d <= 256) return (int)((d + 15) / 16);
   if (prec == kFP8 && d <= 512) return (int)((d + 63) / 64) * 2;
+  if (prec == kF32 && d <= 256) {
+    const int ns = (int)((d + 7) / 8);
+    return ns <= 20 ? ns : (ns + 1) / 2 * 2;  // even step counts are built
+  }
   return 0;
 }
 
@@ -22,8 +26,9 @@ int64_t panel_bytes(int prec, int64_t d, int64_t rows) {
 
 // Fragment order: 16 bytes of lane l = 32 g + r of step s of the 32 vectors
 // from 32 b, at ((b NS + s) 64 + l) 16: vector 32 b + r, coordinates 16 s +
-// 8 g + 0..7 (bf16) or 64 (s / 2) + 32 g + 16 (s % 2) + 0..15 (fp8), which is
-// the MFMA operand of that lane.  A workgroup takes 32 vectors: it reads
+// 8 g + 0..7 (bf16), 64 (s / 2) + 32 g + 16 (s % 2) + 0..15 (fp8) or 8 s + 4
+// g + 0..3 (fp32), which is the MFMA operand of that lane (fp32: its q-th
+// MFMA takes coordinates 8 s + q and 8 s + 4 + q).  A workgroup takes 32 vectors: it reads
 // them into LDS, 8 lanes sum each one's norms, and every thread converts
 // 16-byte pieces in the order they are stored.  Vectors past the last are
 // zeros.  (A wave per vector for the norms, as in k_prep, spends its time
@@ -78,7 +83,12 @@ __global__ __launch_bounds__(256) void k_prep_panel(const float* X,
     const float* x = xs + r * ld;
     const float sc = scale_s[r];
     i4v w = {0, 0, 0, 0};
-    if (P == kBF16) {
+    if (P == kF32) {
+      const int k0 = s * 8 + gk * 4;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        w[q] = __float_as_int(k0 + q < d ? x[k0 + q] : 0.0f);
+    } else if (P == kBF16) {
       const int k0 = s * 16 + gk * 8;
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -103,7 +113,10 @@ hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
   const int ns = panel_steps(prec, d);
   const unsigned g = (unsigned)((rows + 127) / 128 * 4);
   const size_t lds = 32 * 4 * (size_t)(d | 1);  // d <= 512: 64.1 KB
-  if (prec == kBF16)
+  if (prec == kF32)
+    k_prep_panel<kF32><<<g, 256, lds, st>>>(X, rows, (int)d, ns, (char*)out,
+                                            info, scale);
+  else if (prec == kBF16)
     k_prep_panel<kBF16><<<g, 256, lds, st>>>(X, rows, (int)d, ns, (char*)out,
                                              info, scale);
   else
@@ -123,8 +136,9 @@ hipError_t launch_panel(const GemmArgs& g, int prec, int64_t d, bool hist,
   int64_t grid = 0;
   if (const char* ev = getenv("MAD_BF_GRID")) grid = atoll(ev) / 8 * 8;
   const int ns = panel_steps(prec, d);
-  return prec == kBF16 ? launch_panel_bf16(a, ns, hist, grid, st)
-                       : launch_panel_fp8(a, ns, hist, grid, st);
+  return prec == kF32    ? launch_panel_f32(a, ns, hist, grid, st)
+         : prec == kBF16 ? launch_panel_bf16(a, ns, hist, grid, st)
+                         : launch_panel_fp8(a, ns, hist, grid, st);
 }
 
 }  // namespace mad

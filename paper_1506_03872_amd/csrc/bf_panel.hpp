@@ -1,6 +1,6 @@
 // bf_panel.hpp -- the brute force's GEMM for short vectors: each wave keeps
-// its 64 rows of A in registers for all of K and streams the columns of B
-// through LDS.
+// its 64 (or 32) rows of A in registers for all of K and streams the columns
+// of B through LDS.
 //
 // What bounds a GEMM of K <= 256 here is not the matrix cores but feeding
 // them: with both operands of a 64 x 64 wave tile read from LDS, each MFMA
@@ -8,8 +8,11 @@
 // the LDS's 128 bytes per cycle; bf16 and fp8 stood at 0.29 of peak.  With
 // the rows of A in registers (K x 64 rows: 128 VGPRs at K = 256 in bf16) a
 // fragment of B serves two MFMAs, so LDS reads take half its rate, and a
-// stage is a whole column tile (64 or 128 columns, all of K): one barrier
-// per 32 or more MFMAs of each wave.
+// stage is a whole column tile (32 to 128 columns, all of K): one barrier
+// per 32 or more MFMAs of each wave.  fp32, whose MFMAs take 64 cycles per
+// 256 bytes of operand, is not short of LDS; it gains from the finer padding
+// of K (to 8 instead of 32), the conflict-free reads and the rarer barriers
+// (65133 x 71567 x 150: 12.2 ms in LDS tiles, 10.4 here, 135 TFLOP/s).
 //
 // Both copies are stored in fragment order: the 1 KB that a wave's MFMA
 // operand takes (32 vectors x one K step, 16 bytes per lane) is contiguous,
@@ -23,12 +26,19 @@
 namespace mad {
 
 typedef int i4v __attribute__((ext_vector_type(4)));
-
-constexpr int kPanelRows = 256;  // rows of A per workgroup (4 waves x 64)
+typedef float f4v __attribute__((ext_vector_type(4)));
 
 // column blocks of 32 per tile: about 16 KB up to 8 steps, so that LDS (two
 // buffers per workgroup) allows as many workgroups per CU as the registers
-constexpr int panel_tile_blocks(int ns) { return ns <= 4 ? 4 : 2; }
+constexpr int panel_tile_blocks(int ns) {
+  return ns <= 4 ? 4 : ns <= 16 ? 2 : 1;
+}
+
+// blocks of 32 rows per wave: two while the rows fit in about 150 registers
+constexpr int panel_row_blocks(int ns) { return ns <= 19 ? 2 : 1; }
+
+// rows of A per workgroup (4 waves)
+constexpr int panel_rows(int ns) { return 128 * panel_row_blocks(ns); }
 
 // bytes [16 lane, 16 lane + 16) of dst (wave-uniform) from src (per lane)
 __device__ __forceinline__ void lds_load16(const char* src, char* dst) {
@@ -46,6 +56,7 @@ __device__ __forceinline__ void lds_load4(const int* src, int* dst) {
 // one MFMA operand per lane: step s of a block's fragments (two steps in fp8)
 template <int P> struct PanelFrag { typedef bf8v T; };
 template <> struct PanelFrag<kFP8> { typedef i8v T; };
+template <> struct PanelFrag<kF32> { typedef f4v T; };
 
 template <int P>
 __device__ __forceinline__ typename PanelFrag<P>::T frag_at(const i4v* p,
@@ -54,16 +65,37 @@ __device__ __forceinline__ typename PanelFrag<P>::T frag_at(const i4v* p,
     const i4v x = p[2 * s * 64], y = p[(2 * s + 1) * 64];
     return __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
   } else {
-    return __builtin_bit_cast(bf8v, p[s * 64]);
+    return __builtin_bit_cast(typename PanelFrag<P>::T, p[s * 64]);
+  }
+}
+
+// c += a b over one step's coordinates (fp32: four MFMAs of two coordinates,
+// one of each lane half)
+template <int P>
+__device__ __forceinline__ f16v panel_mma(const typename PanelFrag<P>::T& a,
+                                          const typename PanelFrag<P>::T& b,
+                                          f16v c, int sa, int sb) {
+  if constexpr (P == kFP8) {
+    return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0,
+                                                           sa, 0, sb);
+  } else if constexpr (P == kBF16) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+  } else {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[q], b[q], c, 0, 0, 0);
+    return c;
   }
 }
 
 // NS: steps of 16 bytes per lane (bf16: 16 coordinates and one MFMA each;
-// fp8: 32 coordinates, one MFMA per two steps).  HIST: pass A.
+// fp8: 32 coordinates, one MFMA per two steps; fp32: 8 coordinates, four
+// MFMAs each).  HIST: pass A.
 template <int P, int NS, bool HIST>
 __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   constexpr int TB = panel_tile_blocks(NS);
-  constexpr int NM = P == kFP8 ? NS / 2 : NS;  // MFMAs per 32 x 32 block
+  constexpr int RB = panel_row_blocks(NS);
+  constexpr int NM = P == kFP8 ? NS / 2 : NS;  // operands per 32 vectors
   constexpr int kTile = TB * NS * 1024;        // bytes of a column tile
   __shared__ __attribute__((aligned(16))) char buf0[kTile];
   __shared__ __attribute__((aligned(16))) char buf1[kTile];
@@ -101,18 +133,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   const char* Ab = (const char*)g.A;
   const char* Bb = (const char*)g.B;
   typedef typename PanelFrag<P>::T frag_t;
-  frag_t fa[2][NM];
+  frag_t fa[RB][NM];
   int sa[2] = {127, 127};
   int64_t i0 = 0, tile = 0, tend = 0;
   auto locate = [&](int64_t it) {
     const int64_t seg = it / a.panels;
-    i0 = (it - seg * a.panels) * kPanelRows + wv * 64;
+    i0 = (it - seg * a.panels) * panel_rows(NS) + wv * (32 * RB);
     tile = seg * a.seg;
     tend = tile + a.seg < a.tiles_n ? tile + a.seg : a.tiles_n;
   };
   auto load_a = [&]() {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < RB; ++u) {
       int64_t i = i0 + u * 32 + rl;
       i = (i < g.m_rows ? i : g.m_rows - 1) * g.a_stride_rows;
       const i4v* p = (const i4v*)(Ab + (i >> 5) * (NS * 1024)) + rg * 32 +
@@ -154,18 +186,18 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
     }
     qn = 0;
   };
-  // the kept values of one 64 x 32 block (the whole wave)
-  auto emit = [&](const f16v& c0, const f16v& c1, int64_t j) {
+  // the kept values of one block of the wave's rows x 32 columns
+  auto emit = [&](const f16v (&acc)[RB], int64_t j) {
     const VecInfo vb = g.ib[j < g.n ? j : g.n - 1];
     // an opaque copy of the lane's first row: without it the 32 rows'
     // addresses are computed ahead of the tile loop and spill
     int row = 4 * rg;
     asm volatile("" : "+v"(row));
 #pragma unroll
-    for (int u = 0; u < 2; ++u)
+    for (int u = 0; u < RB; ++u)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const float c = u ? c1[e] : c0[e];
+        const float c = acc[u][e];
         bool keep = fabsf(c) >= pre;
         if (!__any(keep)) continue;
         const int64_t i = i0 + (u * 32 + 8 * (e >> 2) + (e & 3) + row);
@@ -199,7 +231,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       const i4v* fb = (const i4v*)(buf + cb * (NS * 1024)) + lane;
       int sb = 127;
       if (P == kFP8) sb = sc[cb * 32 + rl];
-      f16v c0, c1;
+      f16v acc[RB];
       // kAhead operands are in flight ahead of the MFMAs that take them, in
       // the order written (the barriers keep it: left alone, the compiler
       // reads two fragments at a time into the same registers and waits
@@ -212,28 +244,22 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       for (int s = 0; s < NM; ++s) {
         __builtin_amdgcn_sched_barrier(0);
         const frag_t x = b[s % kAhead];
-        if constexpr (P == kFP8) {
-          c0 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-              fa[0][s], x, s == 0 ? zero : c0, 0, 0, 0, sa[0], 0, sb);
-          c1 = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(
-              fa[1][s], x, s == 0 ? zero : c1, 0, 0, 0, sa[1], 0, sb);
-        } else {
-          c0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              fa[0][s], x, s == 0 ? zero : c0, 0, 0, 0);
-          c1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              fa[1][s], x, s == 0 ? zero : c1, 0, 0, 0);
-        }
+#pragma unroll
+        for (int u = 0; u < RB; ++u)
+          acc[u] = panel_mma<P>(fa[u][s], x, s == 0 ? zero : acc[u], sa[u],
+                                sb);
         if (s + kAhead < NM) b[s % kAhead] = frag_at<P>(fb, s + kAhead);
       }
       __builtin_amdgcn_sched_barrier(0);
-      // one max of |c| over the lane's 32 values; the per-value work runs
-      // only in waves where a lane reaches `pre`
+      // one max of |c| over the lane's values; the per-value work runs only
+      // in waves where a lane reaches `pre`
       float mx = 0.0f;
 #pragma unroll
       for (int e = 0; e < 16; ++e)
-        mx = fmaxf(fmaxf(mx, fabsf(c0[e])), fabsf(c1[e]));
+#pragma unroll
+        for (int u = 0; u < RB; ++u) mx = fmaxf(mx, fabsf(acc[u][e]));
       if (__any(mx >= pre)) {
-        emit(c0, c1, tl * (TB * 32) + cb * 32 + rl);
+        emit(acc, tl * (TB * 32) + cb * 32 + rl);
         // emit's loads end here, for the reason given in load_a
         __builtin_amdgcn_s_waitcnt(0x0f70);
       }
@@ -331,9 +357,9 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   }
 }
 
-// workgroups that fill the chip: what registers and LDS let a CU hold
+// workgroups that a CU holds (registers and LDS)
 template <int P, int NS, bool HIST>
-unsigned panel_grid() {
+unsigned panel_per_cu() {
   static const unsigned per_cu = [] {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
@@ -342,29 +368,40 @@ unsigned panel_grid() {
       n = 2;
     return (unsigned)n;
   }();
-  return 256 * per_cu;
+  return per_cu;
 }
 
 template <int P, int NS, bool HIST>
 hipError_t launch_panel_one(PanelArgs a, int64_t grid, hipStream_t st) {
-  if (grid <= 0) grid = panel_grid<P, NS, HIST>();
-  constexpr int tn = panel_tile_blocks(NS) * 32;
+  const unsigned per_cu = panel_per_cu<P, NS, HIST>();
+  if (grid <= 0) grid = 256 * (int64_t)per_cu;
+  constexpr int TB = panel_tile_blocks(NS);
+  constexpr int tn = TB * 32;
   a.tiles_n = (a.g.n + tn - 1) / tn;
-  a.panels = (a.g.m_rows + kPanelRows - 1) / kPanelRows;
-  // Column tiles per item: up to 2048 columns, so that loading the rows of A
-  // (once per item) is a few percent of it, but a dozen items or more per
-  // workgroup, so that the last round is short.  With fewer than a dozen
-  // tiles per workgroup, one item each (pass A at 1563 x 1e5 x 100 in fp8:
-  // 94 us, against 119 with one-tile items, each loading its rows of A).
-  int64_t seg = a.tiles_n * a.panels / (grid * 12);
-  if (seg > 2048 / tn) seg = 2048 / tn;
-  if (seg < 1) {
-    const int64_t per = grid / a.panels > 1 ? grid / a.panels : 1;
-    seg = (a.tiles_n + per - 1) / per;
-    if (seg > 12) seg = 12;
+  a.panels = (a.g.m_rows + panel_rows(NS) - 1) / panel_rows(NS);
+  // Column tiles per item: the least of rounds x (tiles + the rows' load),
+  // where a workgroup does its items one after another.  Loading the rows
+  // takes about 2.5 us, a tile its MFMAs' cycles on the SIMDs it shares.
+  // (Items of one tile, which the fewest rounds lose least by when each
+  // workgroup has a dozen tiles, spend most of their time on the rows: pass
+  // A at 1018 x 71567 x 150 in fp32 530 us, 258 by this rule.)  Up to 4096 columns:
+  // the workgroups of an XCD stream the same columns, 2 MB at K = 256.
+  constexpr int cycles =
+      panel_row_blocks(NS) * TB *
+      (P == kF32 ? NS * 4 * 64 : P == kFP8 ? NS / 2 * 64 : NS * 32);
+  const double load = 2.5 / (cycles * (double)per_cu / 2200.0);
+  double best = 0.0;
+  a.seg = 1;
+  for (int64_t seg = 1; seg <= 4096 / tn && seg <= a.tiles_n; ++seg) {
+    const int64_t items = a.panels * ((a.tiles_n + seg - 1) / seg);
+    const double cost =
+        (double)((items + grid - 1) / grid) * ((double)seg + load);
+    if (seg == 1 || cost < best) {
+      best = cost;
+      a.seg = seg;
+    }
   }
-  a.seg = seg;
-  a.items = a.panels * ((a.tiles_n + seg - 1) / seg);
+  a.items = a.panels * ((a.tiles_n + a.seg - 1) / a.seg);
   k_gemm_panel<P, NS, HIST><<<(unsigned)grid, 256, 0, st>>>(a);
   return hipGetLastError();
 }

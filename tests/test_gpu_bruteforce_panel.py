@@ -1,5 +1,5 @@
-"""GPU checks of the brute force's register-panel GEMM (bf16 up to d = 256,
-fp8 up to d = 512) at the edges of its steps, tiles and row panels, against
+"""GPU checks of the brute force's register-panel GEMM (fp32 and bf16 up to d
+= 256, fp8 up to d = 512) at the edges of its steps, tiles and row panels, against
 the oracle's exhaustive answer.  Inputs are small integers (exact in every
 precision, and so are their sums), so the answers must be equal."""
 import numpy as np
@@ -9,19 +9,21 @@ import oracle
 
 pytestmark = pytest.mark.gpu
 
-# d at the edges of the 16- and 64-coordinate steps, of the change of tile
-# width (bf16 128 | 129, fp8 256 | 257) and of the kernel's range (bf16 256 |
-# 257, fp8 512 | 513); rows and columns at the edges of the 64-row wave, the
-# 256-row panel and the 64- and 128-column tiles
+# d at the edges of the 8-, 16- and 64-coordinate steps, of the change of tile
+# width (fp32 128 | 129, bf16 64 | 65, fp8 128 | 129), of fp32's rows per wave
+# (152 | 153) and even steps (160 | 161), and of the kernel's range (256 | 257,
+# fp8 512 | 513); rows and columns at the edges of the 32- and 64-row waves,
+# the 128- and 256-row panels and the 32- to 128-column tiles
 SHAPES = [(1, 1, 1), (31, 33, 15), (64, 65, 16), (257, 127, 17),
           (255, 129, 63), (256, 128, 64), (513, 300, 65), (70, 1030, 100),
-          (300, 257, 128), (300, 64, 129), (511, 190, 241), (260, 255, 256),
+          (300, 257, 128), (300, 64, 129), (257, 131, 9), (258, 97, 152),
+          (129, 161, 153), (127, 95, 160), (385, 33, 161), (511, 190, 241), (260, 255, 256),
           (130, 200, 257), (140, 190, 512), (140, 190, 513),
           # many work items per workgroup, and a sampled first pass
           (9000, 3001, 40)]
 
 
-@pytest.mark.parametrize("prec", [1, 2])
+@pytest.mark.parametrize("prec", [0, 1, 2])
 @pytest.mark.parametrize("shape", SHAPES)
 def test_panel_edges(gpu, prec, shape):
     import torch
