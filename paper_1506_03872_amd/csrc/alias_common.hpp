@@ -21,6 +21,32 @@ __device__ __forceinline__ uint64_t exact_u52(double x) {
          ((1ull << 52) - 1);
 }
 
+// F of a prefix P of a table of total T: floor(2^K RN(P / T)), the same
+// integer as with the IEEE division, for all prefixes of one table.  With
+// t = 2^-K T (exact, so RN(P / t) = 2^K RN(P / T)), z = RN(1 / t) and zl the
+// reciprocal's remainder, q = RN(P z + RN(P zl)) is within 0.51 ulp of P / t,
+// hence faithful; then r = P - q t is exact in one fma and RN(q + r z) is the
+// correctly rounded quotient (Markstein, "Computation of elementary functions
+// on the IBM RISC System/6000 processor", IBM J. Res. Dev. 34, 1990; the
+// two-word reciprocal of a divisor known in advance is Brisebarre, Muller and
+// Raina's, IEEE Trans. Comput. 53, 2004).  Every magnitude here stays within
+// 2^+-1000 (weights are products of at most three FP32 magnitudes and their
+// sums), so nothing underflows.  Four FP64 operations an item instead of a
+// division and a scaling (some 14): the table builders are bound by the
+// instructions they issue.
+struct Quotient {
+  double t, z, zl;
+  __device__ __forceinline__ Quotient(double T, int K) {
+    t = ldexp(T, -K);
+    z = 1.0 / t;
+    zl = fma(-z, t, 1.0) * z;
+  }
+  __device__ __forceinline__ double operator()(double P) const {
+    const double q = fma(P, z, P * zl);
+    return floor(fma(fma(-q, t, P), z, q));
+  }
+};
+
 // One wave builds the alias table of one table from its quanta qv (lane
 // holds slots lane*SPL ..) and sign bits sg; LDS scratch Ld/He (2^L u64
 // each) and Hi (2^L u32) belongs to this wave.  Every wave of the block

@@ -573,6 +573,7 @@ __global__ __launch_bounds__(256) void k_ragged_alias(
   char* et = (char*)ent + so * esz;
   if (mine && !live)  // dead table: never sampled, entries zero
     zero_entries(et, esz, lane, Np, 64);
+  const Quotient cdf(live ? T : 1.0, K);
   uint64_t F[SPL];
   uint32_t sg[SPL];
 #pragma unroll
@@ -583,7 +584,7 @@ __global__ __launch_bounds__(256) void k_ragged_alias(
     if (live && r < N) {
       const uint64_t raw = Ld[r];
       const double lr = __longlong_as_double((long long)(raw & kQMask));
-      F[s] = (uint64_t)floor(ldexp((Ec[r / kRun] + lr) / T, K));
+      F[s] = exact_u52(cdf(Ec[r / kRun] + lr));
       sg[s] = (uint32_t)(raw >> 63);
     }
   }
@@ -740,7 +741,7 @@ __global__ __launch_bounds__(256) void k_big_quanta(const BigInfo* big,
   const int64_t r0 = g0 - B.so;  // table-relative slot
   const double T = tot[B.s];
   const bool live = T > 0.0;
-  const int K = B.L + kCapBits;
+  const Quotient cdf(live ? T : 1.0, B.L + kCapBits);
   const double* E = sc.E + B.eoff;
   const uint64_t* Lb = sc.Lb + B.so;
   Quad a{0, 0, 0, 0};
@@ -748,7 +749,7 @@ __global__ __launch_bounds__(256) void k_big_quanta(const BigInfo* big,
   if (live && r0 > 0 && r0 - 1 < B.N) {
     const double Pp = E[(r0 - 1) / kRun] +
                       __longlong_as_double((long long)(Lb[r0 - 1] & kQMask));
-    Fp = (uint64_t)floor(ldexp(Pp / T, K));
+    Fp = (uint64_t)cdf(Pp);
   }
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
@@ -758,7 +759,7 @@ __global__ __launch_bounds__(256) void k_big_quanta(const BigInfo* big,
       const uint64_t raw = Lb[r];
       const double Pv = E[r / kRun] +
                         __longlong_as_double((long long)(raw & kQMask));
-      const uint64_t F = (uint64_t)floor(ldexp(Pv / T, K));
+      const uint64_t F = (uint64_t)cdf(Pv);
       qq = (F - Fp) | (raw & ~kQMask);
       Fp = F;
     }

@@ -248,7 +248,8 @@ __global__ void k_quantize(W w, int64_t S, int64_t N, int64_t R, int L,
   const int64_t r0 = c * kRun;
   const int64_t r1 = N < r0 + kRun ? N : r0 + kRun;
   // the prefix before this run is exactly E_c (end of the previous run)
-  uint64_t Fprev = c == 0 ? 0ull : (uint64_t)floor(ldexp(e / T, K));
+  const Quotient cdf(T, K);
+  uint64_t Fprev = c == 0 ? 0ull : (uint64_t)cdf(e);
   uint64_t* qs = q + (seg << L);
   double l = 0.0;
   for (int64_t g0 = r0; g0 < r1; g0 += kRowGroup) {
@@ -266,7 +267,7 @@ __global__ void k_quantize(W w, int64_t S, int64_t N, int64_t R, int L,
       if (r >= r1) continue;
       l = r == r0 ? v[u] : l + v[u];
       const double P = e + l;
-      const uint64_t F = (uint64_t)floor(ldexp(P / T, K));
+      const uint64_t F = (uint64_t)cdf(P);
       qs[r] = (F - Fprev) | ((uint64_t)sg[u] << 63);
       Fprev = F;
     }
@@ -399,6 +400,7 @@ __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
         for (int r = lane; r < Np; r += 64) ent[(seg << L) + r] = 0ull;
       // F_r exact in FP64 (K <= 40 here); slots past the items keep F of
       // the last item, 2^K, so their quanta are zero
+      const Quotient cdf(live ? T : 1.0, K);
       uint64_t F[SPL];
       uint32_t sg[SPL];
 #pragma unroll
@@ -409,7 +411,7 @@ __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
         if (live && r < N) {
           const uint64_t raw = lb[tb * ld + r];
           const double lr = __longlong_as_double((long long)(raw & kQMask));
-          F[s] = exact_u52(floor(ldexp((Ec[r / kRun] + lr) / T, K)));
+          F[s] = exact_u52(cdf(Ec[r / kRun] + lr));
           sg[s] = (uint32_t)(raw >> 63);
         }
       }
@@ -885,15 +887,14 @@ __global__ __launch_bounds__(64) void k_col_walk(
   const int64_t seg = s0 + tc;
   const double T = tot[seg];
   const bool live = T > 0.0;
-  const double Tq = live ? T : 1.0;  // dead tables: no item is taken
-  const int K = L + kCapBits;
+  const Quotient cdf(live ? T : 1.0, L + kCapBits);  // dead: no item is taken
   const int64_t r0 = c * kRun;
   const int64_t r1 = N < r0 + kRun ? N : r0 + kRun;  // items of this run
   const int64_t R = (N + kRun - 1) / kRun;
   const double Ec = live && c < R ? E[c * S + seg] : 0.0;
   // F of the item before the run: floor(2^K E_c / T), 0 in the first run
   const bool first = !(live && c > 0 && c < R);
-  const double Fstart = first ? 0.0 : floor(ldexp(Ec / T, K));
+  const double Fstart = first ? 0.0 : cdf(Ec);
   uint64_t Fp = (uint64_t)Fstart;
   double Fpd = Fstart;
   uint64_t nl = 0, nh = 0, da = 0, ea = 0;
@@ -940,7 +941,7 @@ __global__ __launch_bounds__(64) void k_col_walk(
         const float x = live && r < r1 ? xv[u] : 0.0f;
         const double w = SCALE ? fabs((double)x) * sv[u] : fabs((double)x);
         l = l + w;
-        const double F = floor(ldexp((Ec + l) / Tq, K));
+        const double F = cdf(Ec + l);
         const double q = F - Fpd;
         Fpd = F;
         const bool light = q < kCapD;
@@ -959,7 +960,7 @@ __global__ __launch_bounds__(64) void k_col_walk(
                                : fabs((double)xv[u]);
         const double lw = r == r0 ? w : l + w;
         l = ok ? lw : l;
-        const uint64_t F = (uint64_t)floor(ldexp((Ec + l) / Tq, K));
+        const uint64_t F = (uint64_t)cdf(Ec + l);
         const uint64_t q = ok ? F - Fp : 0ull;
         Fp = ok ? F : Fp;
         const uint32_t sg = ok ? sign_bit(xv[u]) : 0u;
@@ -1047,14 +1048,13 @@ __global__ __launch_bounds__(64) void k_col_lists(
   const int64_t seg = s0 + tc;
   const double T = tot[seg];
   const bool live = T > 0.0;
-  const double Tq = live ? T : 1.0;  // dead tables: no item is taken
-  const int K = L + kCapBits;
+  const Quotient cdf(live ? T : 1.0, L + kCapBits);  // dead: no item is taken
   const int64_t r0 = c * kRun;
   const int64_t r1 = N < r0 + kRun ? N : r0 + kRun;  // items of this run
   const int64_t R = (N + kRun - 1) / kRun;
   const double Ec = live && c < R ? E[c * S + seg] : 0.0;
   const bool first = !(live && c > 0 && c < R);
-  double Fp = first ? 0.0 : floor(ldexp(Ec / T, K));
+  double Fp = first ? 0.0 : cdf(Ec);
   const Quad o = bs[tc * B + c];
   uint32_t nl = (uint32_t)o.nl, nh = (uint32_t)o.nh;  // below 2^L
   double da = (double)o.sd;  // exact: below 2^52
@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(64) void k_col_lists(
       const float x = live && r < r1 ? xv[u] : 0.0f;
       const double w = SCALE ? fabs((double)x) * sv[u] : fabs((double)x);
       l = l + w;
-      const double F = floor(ldexp((Ec + l) / Tq, K));
+      const double F = cdf(Ec + l);
       const double q = F - Fp;
       Fp = F;
       const bool light = q < kCapD;

@@ -1,0 +1,45 @@
+"""GPU parity of the tables over the range of FP32 magnitudes: the builders
+divide every prefix by its table's total through a reciprocal held once, and
+the integer CDF has to be the IEEE division's for subnormal and huge weights,
+for products of three of them (the stage-0 weights) and for totals whose
+significand is all ones.  Bar: every table equal to the oracle's."""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def matrix(g, rows, d, lo, hi):
+    x = np.ldexp(g.uniform(1.0, 2.0, (rows, d)),
+                 g.integers(lo, hi, (rows, d))) * g.choice([-1, 1], (rows, d))
+    return x.astype(np.float32)
+
+
+# sizes at the edges of the builders: one wave (<= 512 slots, 1 to 8 a lane),
+# the exact FP64 walk (up to 2^21 slots) and the stored quanta (long rows)
+@pytest.mark.parametrize("m,n,d", [(64, 65, 33), (200, 511, 129),
+                                   (600, 1025, 70), (70, 40, 1100)])
+@pytest.mark.parametrize("lo,hi", [(-149, -120), (90, 110), (-60, 60),
+                                   (-1, 0)])
+def test_quotient(gpu, m, n, d, lo, hi):
+    import torch
+
+    import paper_1506_03872_amd as mad
+    g = np.random.default_rng(m + lo + 200)
+    if lo == -1:  # totals just below a power of two
+        A = np.full((m, d), 1.0, np.float32)
+        B = np.full((n, d), 1.0, np.float32)
+        A[:, -1] = B[:, -1] = np.float32(1 - 2.0 ** -24)
+        A[-1] = B[-1] = np.float32(1 - 2.0 ** -24)
+    else:
+        A, B = matrix(g, m, d, lo, hi), matrix(g, n, d, lo, hi)
+    gp = mad.Plan.dense(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda())
+    op = oracle.Plan.dense(A, B)
+    for which, seg in ([(0, 0)] + [(w, k) for w in (1, 2)
+                                   for k in (0, 1, d // 2, d - 1)]
+                       + [(3, i) for i in (0, m // 2, m - 1)]):
+        got, want = gp.table(which, seg), op.table(which, seg)
+        assert np.array_equal(got[0], want[0]), (which, seg)
+        assert np.array_equal(got[1], want[1]), (which, seg)
