@@ -105,9 +105,8 @@ __device__ __forceinline__ uint32_t sign_bit(float x) {
 __host__ __device__ inline int fix_exponent(float bmax, int64_t s) {
   int e;
   (void)frexpf(bmax, &e);
-  int64_t v = s > 2 ? s : 2;
-  int ls = 0;
-  while ((int64_t(1) << ls) < v) ++ls;
+  const int64_t v = s > 2 ? s : 2;
+  const int ls = 64 - __builtin_clzll((unsigned long long)v - 1);  // ceil log2
   return 62 - e - ls;
 }
 
