@@ -47,6 +47,40 @@ struct Quotient {
   }
 };
 
+// One lane's walk of a run: cnt weights (sign bit in bit 63) become the
+// run-local prefixes, summed left to right, each with its item's sign bit;
+// returns the run's total.  The next eight weights are read while these are
+// added.
+__device__ __forceinline__ double walk_run(uint64_t* row, int cnt) {
+  double l = 0.0;  // weights are >= +0, so 0 + w is w
+  uint64_t nx[8];
+#pragma unroll
+  for (int u = 0; u < 8; ++u) nx[u] = row[u < cnt ? u : cnt - 1];
+  int r0 = 0;
+  for (; r0 + 8 <= cnt; r0 += 8) {
+    uint64_t x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      x[u] = nx[u];
+      const int r = r0 + 8 + u;
+      nx[u] = row[r < cnt ? r : cnt - 1];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      l = l + __longlong_as_double((long long)(x[u] & kQMask));
+      row[r0 + u] = (uint64_t)__double_as_longlong(l) | (x[u] & ~kQMask);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 8; ++u) {
+    if (r0 + u < cnt) {
+      l = l + __longlong_as_double((long long)(nx[u] & kQMask));
+      row[r0 + u] = (uint64_t)__double_as_longlong(l) | (nx[u] & ~kQMask);
+    }
+  }
+  return l;
+}
+
 // One wave builds the alias table of one table from its quanta qv (lane
 // holds slots lane*SPL ..) and sign bits sg; LDS scratch Ld/He (2^L u64
 // each) and Hi (2^L u32) belongs to this wave.  Every wave of the block
@@ -97,19 +131,27 @@ __device__ void wave_alias(const uint64_t (&qv)[SPL], const uint32_t (&sg)[SPL],
     da = sd_in - sd;
     ea = se_in - se;
   }
+  // a slot appends to its own list and, as the lists together hold Np
+  // entries, one entry of ~0 to the other, which fills both to Np
   uint32_t mypos[SPL];
+  uint64_t key[SPL];
 #pragma unroll
   for (int s = 0; s < SPL; ++s) {
     const int r = lane * SPL + s;
     mypos[s] = 0;
+    key[s] = 0;
     if (active && r < Np) {
       if (qv[s] < kCap) {
+        key[s] = da;
         da += kCap - qv[s];
         Ld[lp] = da;
+        He[NH + lp] = ~0ull;
         mypos[s] = lp++;
       } else {
         ea += qv[s] - kCap;
+        key[s] = ea + 1;
         He[hp] = ea;
+        Ld[NL + hp] = ~0ull;
         Hi[hp] = (uint32_t)r | (sg[s] << 31);
         mypos[s] = hp++;
       }
@@ -117,23 +159,27 @@ __device__ void wave_alias(const uint64_t (&qv)[SPL], const uint32_t (&sg)[SPL],
   }
   __syncthreads();
   // Each slot searches the other list once, with the same branch-free
-  // lower bound (a uniform loop of L + 1 halving steps): a light the first
-  // heavy whose inclusive excess reaches its exclusive deficit Dx, i.e.
-  // the count of heavies with He < Dx; a heavy the first light whose
-  // inclusive deficit exceeds its excess Eh, i.e. the count of lights with
-  // Ld < Eh + 1.
+  // lower bound of L halving steps (the other list has at most Np - 1 of
+  // the entries; the ~0 after them need no check against its length): a
+  // light the first heavy whose inclusive excess reaches its exclusive
+  // deficit Dx, i.e. the count of heavies with He < Dx; a heavy the first
+  // light whose inclusive deficit exceeds its excess Eh, i.e. the count of
+  // lights with Ld < Eh + 1.
 #pragma unroll
   for (int s = 0; s < SPL; ++s) {
     const int r = lane * SPL + s;
     const bool ok = active && r < Np;
     const bool light = qv[s] < kCap;
-    const uint64_t own = ok ? (light ? Ld[mypos[s]] : He[mypos[s]]) : 0ull;
-    const uint64_t key = light ? own - (kCap - qv[s]) : own + 1;
     const uint64_t* lst = light ? He : Ld;
-    const uint32_t n = ok ? (light ? NH : NL) : 0u;
     uint32_t lo = 0;
-    for (uint32_t step = (uint32_t)Np; step > 0; step >>= 1)
-      if (lo + step <= n && lst[lo + step - 1] < key) lo += step;
+    if (SPL > 1) {  // Np = 64 SPL
+#pragma unroll
+      for (uint32_t step = 32 * SPL; step > 0; step >>= 1)
+        if (lst[lo + step - 1] < key[s]) lo += step;
+    } else {
+      for (uint32_t step = (uint32_t)Np >> 1; step > 0; step >>= 1)
+        if (lst[lo + step - 1] < key[s]) lo += step;
+    }
     if (!ok) continue;
     if (light) {
       const uint32_t a = NH ? Hi[lo < NH ? lo : NH - 1]
@@ -141,7 +187,7 @@ __device__ void wave_alias(const uint64_t (&qv)[SPL], const uint32_t (&sg)[SPL],
       emit(r, (uint32_t)qv[s], sg[s], a & kLow31, a >> 31);
     } else if (lo < NL && mypos[s] + 1 < NH) {
       const uint32_t a = Hi[mypos[s] + 1];
-      emit(r, (uint32_t)(own + kCap - Ld[lo]), sg[s], a & kLow31, a >> 31);
+      emit(r, (uint32_t)(key[s] - 1 + kCap - Ld[lo]), sg[s], a & kLow31, a >> 31);
     } else {
       emit(r, 0u, sg[s], (uint32_t)r, sg[s]);
     }

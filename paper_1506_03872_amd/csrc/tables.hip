@@ -304,9 +304,9 @@ static hipError_t uniform_quanta(W w, int64_t S, int64_t N, int L,
 // 256-thread block (small_tables picks TB for the LDS budget):
 //   phase 1  the block loads its tables' weights (with the sign bits in
 //            bit 63; weights are >= 0) into LDS together; then lanes of wave
-//            0, one per table, walk the items left to right and overwrite
-//            them with the run-local prefixes l_r (sign bits kept); the
-//            totals of the runs of kRun items go to LDS as well;
+//            0, one per run of kRun items of a table, walk the items left to
+//            right and overwrite them with the run-local prefixes l_r (sign
+//            bits kept); the runs' totals go to LDS as well;
 //   phase 2  each wave takes a table at a time: E_c and T from the run
 //            totals in the two-level order (E_0 = 0, E_{c+1} = E_c + l of
 //            run c's last item, T = E_R), then per slot in parallel P_r =
@@ -314,6 +314,10 @@ static hipError_t uniform_quanta(W w, int64_t S, int64_t N, int L,
 //            floor(2^K P_r / T) and q_r = F_r - F_{r-1} (F of the slot
 //            before a lane's first comes from the previous lane), and the
 //            alias table from the quanta in registers.
+// Bound by its vector instructions (some 500 a table of 150 items) and the
+// serial walk; 1e5 tables of 96 / 150 / 256 items take 87 / 131 / 280 us,
+// their bytes at 4.7 TB/s 31 / 56 / 65 us.  (One lane per table and blocks of
+// four tables took 137 / 290 / 1098 us.)
 // Padding slots and dead tables get q = 0.
 template <int SPL, class W>
 __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
@@ -322,7 +326,7 @@ __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
                                                       uint64_t* ent) {
   extern __shared__ uint64_t smem64[];
   const int Np = 1 << L;
-  const int ld = Np + 1;  // row stride of the prefixes (bank spread)
+  const int ld = (int)N | 1;  // row stride of the prefixes (bank spread)
   const int R = (int)((N + kRun - 1) / kRun);
   uint64_t* lb = smem64;                        // TB x ld
   double* rt = (double*)(smem64 + TB * ld);     // TB x 4 run totals
@@ -361,24 +365,13 @@ __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
                       ((uint64_t)sv[u] << 63);
     }
     __syncthreads();
-    if (wv == 0 && lane < ntab) {
-      uint64_t* row = lb + lane * ld;
-      double l = 0.0;
-      for (int r0 = 0; r0 < N; r0 += 8) {
-        uint64_t x[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) x[u] = row[r0 + u < N ? r0 + u : N - 1];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          const int r = r0 + u;
-          if (r < N) {
-            const double wr = __longlong_as_double((long long)(x[u] & kQMask));
-            l = r % kRun == 0 ? wr : l + wr;
-            row[r] = (uint64_t)__double_as_longlong(l) | (x[u] & ~kQMask);
-            if (r % kRun == kRun - 1 || r == N - 1) rt[lane * 4 + r / kRun] = l;
-          }
-        }
-      }
+    // the run-local prefixes, one lane per (table, run): at most 16 x 4
+    if (wv == 0 && lane < ntab * R) {
+      const int tb = lane / R, c = lane - tb * R;
+      rt[tb * 4 + c] = walk_run(lb + tb * ld + c * kRun,
+                                (int)N - c * kRun < (int)kRun
+                                    ? (int)N - c * kRun
+                                    : (int)kRun);
     }
     __syncthreads();
     // ---- phase 2 -----------------------------------------------------------
@@ -436,19 +429,23 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
                                uint64_t* ent, hipStream_t st) {
   if (S <= 0 || N <= 0) return hipSuccess;
   const int Np = 1 << L;
-  // the most tables per block (a power of two, 4 .. 64) within the LDS
-  // budget; about 32 KB measured best (MAD_SMALL_LDS overrides it for
-  // tuning)
+  // the most tables per block (4, 8 or 16) within the LDS budget: the serial
+  // walk takes one wave as long for 16 tables as for one (1e5 tables of 150
+  // items, one lane a table: 290 us with 4, 197 with 8, 184 with 16; of 96
+  // items 106 us with 16, 122 with 32, where fewer blocks share a CU).  MAD_SMALL_LDS overrides
+  // the budget for tuning.  Fewer where the tables would not give every CU
+  // two blocks (1000 tables of 50 items: 17 -> 9.6 us).
   static const size_t budget = [] {
     const char* e = getenv("MAD_SMALL_LDS");
-    const long v = e ? atol(e) : 32768;
-    return (size_t)(v >= 4096 && v <= 65536 ? v : 32768);
+    const long v = e ? atol(e) : 40960;
+    return (size_t)(v >= 4096 && v <= 65536 ? v : 40960);
   }();
-  auto lds_for = [Np](int tb) {
-    return ((size_t)tb * (Np + 1) + (size_t)tb * 4 + (size_t)Np * 10) * 8;
+  auto lds_for = [Np, N](int tb) {
+    return ((size_t)tb * (size_t)(N | 1) + (size_t)tb * 4 + (size_t)Np * 10) *
+           8;
   };
-  int TB = 64;
-  while (TB > 4 && lds_for(TB) > budget) TB /= 2;
+  int TB = 16;
+  while (TB > 4 && (lds_for(TB) > budget || S < (int64_t)TB * 512)) TB /= 2;
   const size_t lds = lds_for(TB);
   const unsigned blocks = grid_for(S, TB);
   if (Np <= 64)

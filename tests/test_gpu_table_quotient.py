@@ -43,3 +43,24 @@ def test_quotient(gpu, m, n, d, lo, hi):
         got, want = gp.table(which, seg), op.table(which, seg)
         assert np.array_equal(got[0], want[0]), (which, seg)
         assert np.array_equal(got[1], want[1]), (which, seg)
+
+
+# blocks of 4, 8 and 16 tables (from 4096 and 8192 tables on) of one to four
+# runs of 128 items, the last block and the last run full and not
+@pytest.mark.parametrize("m,d", [(4095, 128), (4100, 127), (8192, 129),
+                                 (8205, 100), (8209, 8), (4099, 257),
+                                 (4096, 512), (300, 385)])
+def test_blocks_of_tables(gpu, m, d):
+    import torch
+
+    import paper_1506_03872_amd as mad
+    g = np.random.default_rng(m + d)
+    A = g.standard_normal((m, d)).astype(np.float32)
+    A[m - 2] = 0.0  # a dead table
+    B = g.standard_normal((7, d)).astype(np.float32)
+    gp = mad.Plan.dense(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda())
+    op = oracle.Plan.dense(A, B)
+    for i in (0, 1, 15, 16, m // 2, m - 17, m - 3, m - 2, m - 1):
+        got, want = gp.table(3, i), op.table(3, i)
+        assert np.array_equal(got[0], want[0]), i
+        assert np.array_equal(got[1], want[1]), i
