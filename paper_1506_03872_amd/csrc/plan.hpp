@@ -61,7 +61,7 @@ struct DenseTables {
   // joined back into the caller's stream
   hipStream_t side = nullptr;
   hipEvent_t fork = nullptr, join = nullptr;
-  // T0 (of at most 512 slots) is built on `aux` as soon as the T1 and T2
+  // T0 (of at most 4096 slots) is built on `aux` as soon as the T1 and T2
   // totals exist (events t1tot, t2tot), beside the rest of T1 and T2; the
   // sampler's first order passes then run on `aux` too (order_done), once
   // the previous sampling launch is done with the order buffers (sampled).
@@ -83,7 +83,7 @@ hipError_t launch_check_symmetric(const float* A, int64_t m, int* flag,
                                   hipStream_t st);
 
 // MIPS: per-query stage-0 tables (S = nq tables over d coordinates, weight
-// |q_k| v_k); scratch only when 2^ceil(log2 d) > 512
+// |q_k| v_k); scratch only when 2^ceil(log2 d) > 4096
 size_t query_tables_scratch_bytes(int64_t nq, int64_t d);
 hipError_t query_tables_build(const float* Q, int64_t nq, int64_t d,
                               const double* v, Family& T0q, void* scratch,
@@ -324,7 +324,7 @@ hipError_t launch_sample_csr_debug(const CsrTables& t, uint64_t seed,
                                    uint64_t qid, int64_t l0, int64_t count,
                                    int F, int32_t* k, int32_t* i, int32_t* j,
                                    int32_t* kp, int64_t* inc, hipStream_t st);
-// stage-0 table over explicit weights (any size); scratch for 2^L > 512
+// stage-0 table over explicit weights (any size); scratch for 2^L > 4096
 size_t stage0_scratch_bytes(int64_t N);
 hipError_t stage0_table_build(const double* w, int64_t N, Family& T,
                               void* scratch, size_t scratch_bytes,

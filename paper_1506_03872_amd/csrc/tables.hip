@@ -432,9 +432,10 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
   // the most tables per block (4, 8 or 16) within the LDS budget: the serial
   // walk takes one wave as long for 16 tables as for one (1e5 tables of 150
   // items, one lane a table: 290 us with 4, 197 with 8, 184 with 16; of 96
-  // items 106 us with 16, 122 with 32, where fewer blocks share a CU).  MAD_SMALL_LDS overrides
-  // the budget for tuning.  Fewer where the tables would not give every CU
-  // two blocks (1000 tables of 50 items: 17 -> 9.6 us).
+  // items 106 us with 16, 122 with 32, where fewer blocks share a CU).
+  // MAD_SMALL_LDS overrides the budget for tuning.  Fewer where the tables
+  // would not give every CU two blocks (1000 tables of 50 items: 17 -> 9.6
+  // us).
   static const size_t budget = [] {
     const char* e = getenv("MAD_SMALL_LDS");
     const long v = e ? atol(e) : 40960;
@@ -459,6 +460,21 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
   return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// Tables of 2^L = 1024 .. 4096 slots, one workgroup of 2^L / 4 threads per
+// table, entirely on chip in the steps of the small tables: weights into LDS,
+// one lane per run of kRun items walks its prefixes, E_c and T, then each
+// thread F and the quanta of four slots in registers, the two lists by a scan
+// over the workgroup, and one search per slot.  X is read once and the
+// entries are written once, in slot order; the pipeline of the larger tables
+// (seven kernels with the lists in memory) took 95 us for 50 tables of 1000
+// items, mostly launches and their gaps, where this takes 12.  All tables of a
+// 1000 x 1000 x 50 plan 272 -> 120 us, of 4096 x 4096 x 1024 468 -> 277, of
+// 1e5 x 600 x 1000 (rows) 5.2 -> 3.0 ms.  4096 slots are the most whose
+// prefixes and lists fit the LDS (80 KB).
+// ---------------------------------------------------------------------------
+constexpr int kOnChipL = 12;
+
 // Workgroups go to the 8 XCDs in turn; this remaps block b so that each
 // XCD takes a contiguous run of logical blocks (when the grid is a
 // multiple of 8), which keeps neighbouring blocks' writes to a shared line,
@@ -468,7 +484,7 @@ __device__ __forceinline__ int64_t xcd_block() {
   return nbk % 8 == 0 ? (b % 8) * (nbk / 8) + b / 8 : b;
 }
 
-// large tables (2^L >= 1024 slots): blocks of 1024 slots (256 threads x 4)
+// large tables (2^L > 4096 slots): blocks of 1024 slots (256 threads x 4)
 // never straddle a table
 constexpr int kAliasBlk = 1024;
 
@@ -702,13 +718,22 @@ static size_t alias_scratch_bytes(int64_t slots, int64_t tables) {
          (size_t)(slots / kMergeBlk + tables) * 8 + 256;
 }
 
-// tables of 2^L >= 1024 slots from stored quanta, in batches of tables that
+// tables of Np slots whose scratch fits `bytes` (alias_scratch_bytes grows by
+// the same amount for each table)
+static int64_t alias_tables_in(size_t bytes, int64_t Np) {
+  const size_t none = alias_scratch_bytes(0, 0);
+  return bytes < none ? 0
+                      : (int64_t)((bytes - none) /
+                                  (alias_scratch_bytes(Np, 1) - none));
+}
+
+// tables of 2^L > 4096 slots from stored quanta, in batches of tables that
 // fit the scratch
 static hipError_t alias_large(const uint64_t* q, const double* tot, int64_t S,
                               int L, uint64_t* ent, void* scratch,
                               size_t scratch_bytes, hipStream_t st) {
   const int64_t Np = int64_t(1) << L;
-  int64_t per = (int64_t)(scratch_bytes / (alias_scratch_bytes(Np, 1)));
+  int64_t per = alias_tables_in(scratch_bytes, Np);
   if (per < 1) return hipErrorOutOfMemory;
   for (int64_t s0 = 0; s0 < S; s0 += per) {
     const int64_t ns = S - s0 < per ? S - s0 : per;
@@ -747,7 +772,7 @@ static hipError_t build_alias(const uint64_t* q, const double* tot, int64_t S,
 }
 
 // ---------------------------------------------------------------------------
-// Column families of 2^L >= 1024 slots without stored prefixes or quanta.
+// Column families of 2^L > 4096 slots without stored prefixes or quanta.
 // The prefixes are recomputed from X, which is cheaper than writing and
 // reading them back:
 //   run totals   per table and run of kRun items, the left-to-right sum;
@@ -844,6 +869,173 @@ __global__ __launch_bounds__(256) void k_col_runoffsets(const double* rtot,
     __syncthreads();
   }
   if (threadIdx.x == 0) tot[seg] = e;
+}
+
+template <int L, class W>
+__global__ __launch_bounds__(1 << (L - 2)) void k_mid_tables(
+    W w, int64_t N, double* tot, uint64_t* ent) {
+  constexpr int Np = 1 << L, THREADS = Np / 4, kW = THREADS / 64;
+  constexpr int K = L + kCapBits;
+  constexpr int kRunLd = kRun + 1;  // run stride: the walks' lanes on 64 banks
+  constexpr int kRuns = Np / kRun;
+  extern __shared__ uint64_t smem64[];
+  uint64_t* pre = smem64;                      // kRuns x kRunLd, then Ld
+  uint64_t* Ld = smem64;                       // Np
+  uint64_t* He = smem64 + kRuns * kRunLd;      // Np
+  uint32_t* Hi = (uint32_t*)(He + Np);         // Np
+  __shared__ double Es[kRuns + 1], rt[kRuns];
+  __shared__ uint32_t wnl[kW];
+  __shared__ uint64_t wsd[kW];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  const int64_t seg = xcd_block();
+  const int n = (int)N, R = (n + kRun - 1) / kRun;
+  double x[4];
+  uint32_t sx[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = tid + u * THREADS;
+    x[u] = r < n ? w(seg, r) : 0.0;
+    sx[u] = r < n ? w.sgn(seg, r) : 0u;
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = tid + u * THREADS;
+    pre[r / kRun * kRunLd + r % kRun] =
+        (uint64_t)__double_as_longlong(x[u]) | ((uint64_t)sx[u] << 63);
+  }
+  __syncthreads();
+  if (tid < R)
+    rt[tid] = walk_run(pre + tid * kRunLd, n - tid * (int)kRun < (int)kRun
+                                               ? n - tid * (int)kRun
+                                               : (int)kRun);
+  __syncthreads();
+  if (tid == 0) {
+    double E = 0.0;
+    for (int c = 0; c < R; ++c) {
+      Es[c] = E;
+      E = E + rt[c];
+    }
+    Es[R] = E;
+    tot[seg] = E;
+  }
+  __syncthreads();
+  const double T = Es[R];
+  uint64_t* et = ent + (seg << L);
+  if (!(T > 0.0)) {  // dead table: never sampled, entries zero
+#pragma unroll
+    for (int u = 0; u < 4; ++u) et[tid + u * THREADS] = 0ull;
+    return;
+  }
+  // F in FP64 (K <= 43, exact); slots past the items keep F = 2^K
+  const Quotient cdf(T, K);
+  const auto F_of = [&](int r, uint64_t raw) {
+    return r < n ? exact_u52(cdf(Es[r / kRun] + __longlong_as_double(
+                                                    (long long)(raw & kQMask))))
+                 : (uint64_t)1 << K;
+  };
+  const int r0 = tid * 4;
+  uint64_t q[4];
+  uint32_t sg[4];
+  uint64_t Fp = 0, Fb;
+  if (r0 > 0)
+    Fp = F_of(r0 - 1, pre[(r0 - 1) / kRun * kRunLd + (r0 - 1) % kRun]);
+  Fb = Fp;  // the sum of the quanta before this thread
+  uint32_t nl = 0;
+  uint64_t sd = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = r0 + u;
+    const uint64_t raw = pre[r / kRun * kRunLd + r % kRun];
+    const uint64_t F = F_of(r, raw);
+    sg[u] = r < n ? (uint32_t)(raw >> 63) : 0u;
+    q[u] = F - Fp;
+    Fp = F;
+    if (q[u] < kCap) {
+      ++nl;
+      sd += kCap - q[u];
+    }
+  }
+  const uint32_t nl_in = wave_scan_dpp(nl);
+  const uint64_t sd_in = wave_scan_dpp(sd);
+  if (lane == 63) {
+    wnl[wv] = nl_in;
+    wsd[wv] = sd_in;
+  }
+  __syncthreads();  // (the prefixes are read; the lists may take their place)
+  uint32_t lp = nl_in - nl, NL = 0;
+  uint64_t da = sd_in - sd;
+#pragma unroll
+  for (int v = 0; v < kW; ++v) {
+    lp += v < wv ? wnl[v] : 0u;
+    da += v < wv ? wsd[v] : 0ull;
+    NL += wnl[v];
+  }
+  // the excess before the thread from the deficit before it: the sum of
+  // (C - q) over the r0 slots before is r0 C - Fb
+  const uint32_t NH = (uint32_t)Np - NL;
+  uint32_t hp = (uint32_t)r0 - lp;
+  uint64_t ea = da - (uint64_t)r0 * kCap + Fb;
+  // own list, and one ~0 in the other, which fills both to Np entries
+  uint64_t key[4];
+  uint32_t pos[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    if (q[u] < kCap) {
+      key[u] = da;
+      da += kCap - q[u];
+      Ld[lp] = da;
+      He[NH + lp] = ~0ull;
+      pos[u] = lp++;
+    } else {
+      ea += q[u] - kCap;
+      key[u] = ea + 1;
+      He[hp] = ea;
+      Ld[NL + hp] = ~0ull;
+      Hi[hp] = (uint32_t)(r0 + u) | (sg[u] << 31);
+      pos[u] = hp++;
+    }
+  }
+  __syncthreads();
+  // one search of the other list per slot, as in wave_alias
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int r = r0 + u;
+    const bool light = q[u] < kCap;
+    const uint64_t* lst = light ? He : Ld;
+    uint32_t lo = 0;
+#pragma unroll
+    for (uint32_t step = Np / 2; step > 0; step >>= 1)
+      if (lst[lo + step - 1] < key[u]) lo += step;
+    if (light) {
+      const uint32_t a = NH ? Hi[lo < NH ? lo : NH - 1]
+                            : (uint32_t)r | (sg[u] << 31);
+      et[r] = pack_entry((uint32_t)q[u], sg[u], a & kLow31, a >> 31);
+    } else if (lo < NL && pos[u] + 1 < NH) {
+      const uint32_t a = Hi[pos[u] + 1];
+      et[r] = pack_entry((uint32_t)(key[u] - 1 + kCap - Ld[lo]), sg[u],
+                         a & kLow31, a >> 31);
+    } else {
+      et[r] = pack_entry(0u, sg[u], (uint32_t)r, sg[u]);
+    }
+  }
+}
+
+// tables of at most 2^kOnChipL slots: no scratch
+template <class W>
+static hipError_t onchip_tables(W w, int64_t S, int64_t N, int L, double* tot,
+                                uint64_t* ent, hipStream_t st) {
+  if (L <= 9) return small_tables(w, S, N, L, tot, ent, st);
+  if (S <= 0 || N <= 0) return hipSuccess;
+  const int Np = 1 << L;
+  const size_t lds =
+      (size_t)(Np / kRun) * (kRun + 1) * 8 + (size_t)Np * 8 + (size_t)Np * 4;
+  if (L == 10)
+    k_mid_tables<10, W><<<(unsigned)S, Np / 4, lds, st>>>(w, N, tot, ent);
+  else if (L == 11)
+    k_mid_tables<11, W><<<(unsigned)S, Np / 4, lds, st>>>(w, N, tot, ent);
+  else
+    k_mid_tables<12, W><<<(unsigned)S, Np / 4, lds, st>>>(w, N, tot, ent);
+  return hipGetLastError();
 }
 
 // One wave per (slot run c, 64 consecutive tables of [s0, s0 + ns)), lane
@@ -1150,8 +1342,7 @@ static hipError_t col_tables(const float* X, int64_t d, const double* scale,
   p = (char*)(bs + S * B);
   const size_t left = scratch_bytes - (size_t)(p - (char*)scratch);
   // tables per batch of alias lists
-  const size_t per_tab = alias_scratch_bytes(Np, 1);
-  int64_t per = (int64_t)(left / per_tab);
+  const int64_t per = alias_tables_in(left, Np);
   if (per < 1) return hipErrorOutOfMemory;
   const int64_t tiles = (S + 63) / 64;
   if (scale)
@@ -1368,8 +1559,8 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
                               bool check, DeviceBuffer& scratch_buf,
                               hipStream_t st) {
   const int64_t m = t.m, n = t.n, d = t.d;
-  // scratch: for a row family (T3, T0) of 2^L > 512 slots its quanta, run
-  // sums and alias lists; for a column family (T1, T2) of 2^L > 512 slots
+  // scratch: for a row family (T3, T0) of 2^L > 4096 slots its quanta, run
+  // sums and alias lists; for a column family (T1, T2) of 2^L > 4096 slots
   // its run data and statistics and alias lists.  Alias lists are batched
   // to at most 2^26 slots (at least one table).
   auto alias_for = [](const Family& f) {
@@ -1381,19 +1572,19 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
   // main region: row families and T1; side region (B given): T2
   size_t need = 1024;
   for (const Family* f : {&t.T3, &t.T0})
-    if (f->L > 9) {
+    if (f->L > kOnChipL) {
       const size_t b = (size_t)(f->S << f->L) * 8 +
                        run_doubles(f->S, f->N) * 8 + alias_for(*f) + 1024;
       if (b > need) need = b;
     }
-  if (t.T1.L > 9) {
+  if (t.T1.L > kOnChipL) {
     const size_t b = col_tables_fixed_bytes(t.T1.S, t.T1.N, t.T1.L) +
                      alias_for(t.T1) + 1024;
     if (b > need) need = b;
   }
   need = (need + 255) & ~(size_t)255;
   size_t need_side = 0;
-  if (B && t.T2.L > 9)
+  if (B && t.T2.L > kOnChipL)
     need_side = col_tables_fixed_bytes(t.T2.S, t.T2.N, t.T2.L) +
                 alias_for(t.T2) + 1024;
   hipError_t e = dev_alloc(scratch_buf, need + need_side);
@@ -1438,15 +1629,15 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
   hipStream_t sd = one_stream ? st : t.side;
   if (B && !one_stream && (e = hipEventRecord(t.fork, st)) != hipSuccess)
     return e;
-  // T0 on the aux stream (it needs no scratch when it has at most 512
+  // T0 on the aux stream (it needs no scratch when it has at most 4096
   // slots), started by the T1 and T2 totals
-  const bool t0_aux = B && !one_stream && t.T0.L <= 9;
+  const bool t0_aux = B && !one_stream && t.T0.L <= kOnChipL;
   t.t0_aux = 0;
   // T3[i]: k' given i, weight |a_k'i|; totals na_i (the draw of k' in
   // Alg. 3)
   // (enqueued before the B side so that this stream has work at once)
-  if (t.T3.L <= 9) {
-    e = small_tables(WRowAbs{A, d}, m, d, t.T3.L, t.T3.tot, t.T3.ent, st);
+  if (t.T3.L <= kOnChipL) {
+    e = onchip_tables(WRowAbs{A, d}, m, d, t.T3.L, t.T3.tot, t.T3.ent, st);
   } else {
     e = uniform_quanta(WRowAbs{A, d}, m, d, t.T3.L, t.T3.tot, q, runbuf, st);
     if (e == hipSuccess)
@@ -1470,8 +1661,8 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
       k_binary_bitmap<<<(unsigned)blocks, 256, 0, sd>>>(B, n * d, t.bbits,
                                                         t.bad + 6);
     }
-    if (t.T2.L <= 9) {
-      e = small_tables(WColAbs{B, d, nullptr}, d, n, t.T2.L, t.T2.tot,
+    if (t.T2.L <= kOnChipL) {
+      e = onchip_tables(WColAbs{B, d, nullptr}, d, n, t.T2.L, t.T2.tot,
                        t.T2.ent, sd);
       if (e == hipSuccess && t0_aux) e = hipEventRecord(t.t2tot, sd);
     } else {
@@ -1486,8 +1677,8 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
 
   // T1[k]: i given k, weight |a_ki| na_i; totals v_k
   if (e == hipSuccess) {
-    if (t.T1.L <= 9) {
-      e = small_tables(WColAbs{A, d, t.na}, d, m, t.T1.L, t.T1.tot, t.T1.ent,
+    if (t.T1.L <= kOnChipL) {
+      e = onchip_tables(WColAbs{A, d, t.na}, d, m, t.T1.L, t.T1.tot, t.T1.ent,
                        st);
       if (e == hipSuccess && t0_aux) e = hipEventRecord(t.t1tot, st);
     } else {
@@ -1504,7 +1695,7 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
       return e;
     k_stage0_weights<<<grid_for(d, 256), 256, 0, t.aux>>>(t.nb, t.v, d,
                                                           t.om);
-    if ((e = small_tables(WExplicit{t.om}, 1, d, t.T0.L, t.T0.tot, t.T0.ent,
+    if ((e = onchip_tables(WExplicit{t.om}, 1, d, t.T0.L, t.T0.tot, t.T0.ent,
                           t.aux)) != hipSuccess ||
         (e = hipEventRecord(t.t0done, t.aux)) != hipSuccess)
       return e;
@@ -1519,8 +1710,8 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
   if (e != hipSuccess || !B || t.t0_aux) return e;
   if (e == hipSuccess) {
     k_stage0_weights<<<grid_for(d, 256), 256, 0, st>>>(t.nb, t.v, d, t.om);
-    if (t.T0.L <= 9) {
-      e = small_tables(WExplicit{t.om}, 1, d, t.T0.L, t.T0.tot, t.T0.ent, st);
+    if (t.T0.L <= kOnChipL) {
+      e = onchip_tables(WExplicit{t.om}, 1, d, t.T0.L, t.T0.tot, t.T0.ent, st);
     } else {
       e = uniform_quanta(WExplicit{t.om}, 1, d, t.T0.L, t.T0.tot, q, runbuf,
                          st);
@@ -1535,11 +1726,11 @@ hipError_t dense_tables_build(DenseTables& t, const float* A, const float* B,
 // ---------------------------------------------------------------------------
 // MIPS stage-0 tables: one table per query over the d coordinates with
 // weight |q_k| v_k (a one-vector B has ||B_k*||_1 = |q_k|, so this is
-// nb_k v_k of the general plan).  Scratch is used only when 2^L > 512.
+// nb_k v_k of the general plan).  Scratch is used only when 2^L > 4096.
 // ---------------------------------------------------------------------------
 size_t query_tables_scratch_bytes(int64_t nq, int64_t d) {
   const int L = ceil_log2_host(d);
-  if (L <= 9) return 256;  // small tables need no scratch
+  if (L <= kOnChipL) return 256;  // tables built on chip need none
   const int64_t slots = nq << L;
   int64_t batch = slots < ((int64_t)1 << 26) ? slots : ((int64_t)1 << 26);
   if (batch < ((int64_t)1 << L)) batch = (int64_t)1 << L;
@@ -1551,7 +1742,8 @@ hipError_t query_tables_build(const float* Q, int64_t nq, int64_t d,
                               const double* v, Family& T0q, void* scratch,
                               size_t scratch_bytes, hipStream_t st) {
   const WQuery w{Q, d, v};
-  if (T0q.L <= 9) return small_tables(w, nq, d, T0q.L, T0q.tot, T0q.ent, st);
+  if (T0q.L <= kOnChipL)
+    return onchip_tables(w, nq, d, T0q.L, T0q.tot, T0q.ent, st);
   char* p = (char*)scratch;
   uint64_t* q = (uint64_t*)p; p += (size_t)(nq << T0q.L) * 8;
   double* runbuf = (double*)p; p += run_doubles(nq, d) * 8;
@@ -1571,7 +1763,7 @@ hipError_t stage0_table_build(const double* w, int64_t N, Family& T,
                               void* scratch, size_t scratch_bytes,
                               hipStream_t st) {
   const WExplicit wf{w};
-  if (T.L <= 9) return small_tables(wf, 1, N, T.L, T.tot, T.ent, st);
+  if (T.L <= kOnChipL) return onchip_tables(wf, 1, N, T.L, T.tot, T.ent, st);
   char* p = (char*)scratch;
   uint64_t* q = (uint64_t*)p; p += (size_t)8 << T.L;
   double* runbuf = (double*)p; p += run_doubles(1, N) * 8;

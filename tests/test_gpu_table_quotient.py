@@ -64,3 +64,34 @@ def test_blocks_of_tables(gpu, m, d):
         got, want = gp.table(3, i), op.table(3, i)
         assert np.array_equal(got[0], want[0]), i
         assert np.array_equal(got[1], want[1]), i
+
+
+# tables of 1024 to 4096 slots (a workgroup each) and the sizes beside them,
+# as columns of either side and as rows (whose stage 0 has the same length);
+# runs full and not, dead tables, and a table of one item
+@pytest.mark.parametrize("m,n,d", [(513, 1024, 9), (1025, 2048, 9),
+                                   (2049, 4096, 9), (4095, 4097, 9),
+                                   (640, 769, 65), (5, 7, 513), (5, 7, 1024),
+                                   (5, 7, 2047), (5, 7, 4096), (5, 7, 4097)])
+def test_mid_tables(gpu, m, n, d):
+    import torch
+
+    import paper_1506_03872_amd as mad
+    g = np.random.default_rng(m + d)
+    A = g.standard_normal((m, d)).astype(np.float32)
+    B = g.standard_exponential((n, d)).astype(np.float32) ** 3
+    A[:, 1] = 0.0  # a dead column
+    A[2] = 0.0     # a dead row
+    B[:, 2] = 0.0
+    B[n // 2, 2] = -3.0  # one item
+    gp = mad.Plan.dense(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda())
+    op = oracle.Plan.dense(A, B)
+    for which, seg in ([(0, 0)] + [(w, k) for w in (1, 2)
+                                   for k in (0, 1, 2, 3, d - 1)]
+                       + [(3, i) for i in (0, 2, m - 1)]):
+        got, want = gp.table(which, seg), op.table(which, seg)
+        assert np.array_equal(got[0], want[0]), (which, seg)
+        assert np.array_equal(got[1], want[1]), (which, seg)
+    r = gp.topk(t=20, s=50_000, t_prime=200, seed=3)
+    k, x, _ = gp.scores()
+    assert len(k) and int(r["i"].max()) < m
