@@ -64,3 +64,10 @@ def test_a_bin_that_overflows_its_table(gpu, prec):
     A, Q, _ = workloads.mips(60000, 16, 2, seed=5)
     A[8192:] *= 1e-6
     check(A, Q, [8192, 60000], [10**6, 10**6], 5, prec=prec)
+
+
+@pytest.mark.parametrize("d", [513, 2049, 4096])
+def test_the_widest_vectors(gpu, d):
+    # stage-0 tables of up to 4096 slots beside a unit's samples in LDS
+    A, Q, _ = workloads.mips(300, d, 3, seed=d)
+    check(A, Q, [1000, 5000, 20000], [10**6, 10**6, 20], 3)
