@@ -217,7 +217,9 @@ int mad_topk(const float* A, int64_t m, const float* B, int64_t n, int64_t d,
              int64_t t, int64_t s, int64_t t_prime, uint64_t seed,
              mad_pair* out, int64_t* n_out, void* stream);
 
-/* Release a plan and its device memory (synchronises the device first). */
+/* Release a plan and its device memory (synchronises the device first).  Up
+ * to 2 GiB of what destroyed plans held is kept for the next plan's tables
+ * and given back to the device when an allocation needs it. */
 void mad_plan_destroy(mad_plan* plan);
 
 /* ---------------------------------------------------------------------------
@@ -253,7 +255,8 @@ int mad_plan_phase_ms(mad_plan* plan, double* ms, int n);
  * cores: every pair's a_i . b_j, top t by |c| (ties by (i, j) ascending),
  * the role of the exact baseline of Sec. 5.3.  The m x n product is never
  * stored: a GEMM over every 64th row of A (or 8th / all rows when m is
- * small) gives a threshold, a second GEMM keeps only the pairs whose
+ * small) gives a threshold and an estimate of how many pairs will reach it,
+ * which sizes the list; a second GEMM keeps only the pairs whose
  * computed value plus an a-priori error bound reaches it, and those
  * survivors are re-ranked with fp32 dot products (the same arithmetic as
  * the sampled path's verification).
@@ -366,7 +369,7 @@ int mips_plan_create(const float* A, int64_t m, int64_t d, uint32_t flags,
  * s = s_per_query[q], t' = tprime_per_query[q], the same t and seed, and
  * Philox counter word 1 = q: its own stage-0 table (weight |q_k| v_k), its
  * own fixed-point exponent F_q from max|q_k| and s_q, scores keyed by i.
- * A score shares a 64-bit slot with its key, so F_q is the general plan's
+ * A score may share a 64-bit slot with its key, so F_q is the general plan's
  * exponent minus kb, the bit length of m (the scores stay exact).
  *   Q                  (device) nq x d fp32 row-major; 0 <= nq < 2^31
  *   s_per_query        (host) nq budgets, 0 <= s_q < 2^31
@@ -376,10 +379,12 @@ int mips_plan_create(const float* A, int64_t m, int64_t d, uint32_t flags,
  *                      query q by |c| (ties by i ascending), j = q
  *   n_out              (device) nq int64: pairs written for each query;
  *                      -1 for a query holding NaN or Inf
- * The launches of a batch (per-query exponents and stage-0 tables, the
- * clearing of the score tables, one persistent sampling launch over chunks
- * of every query's samples, one postprocessing launch with a workgroup per
- * query) are captured once into a HIP graph, which later calls with the
+ * The launches of a batch (per-query exponents and stage-0 tables; for
+ * queries of at most 2^18 samples one sampling launch over units of at most
+ * 4096 samples, each ordered by ranges of i, and one that sums each range in
+ * LDS; for larger ones the clearing of a score table in memory and a
+ * persistent sampling launch over chunks; one postprocessing launch with a
+ * workgroup per query) are captured once into a HIP graph, which later calls with the
  * same Q, out, n_out, seed and budgets replay on `stream`.  A new budget
  * vector re-plans the batch (host work, uploads and allocation: the call
  * then synchronises).  With MAD_FLAG_TIMING the launches run directly,
@@ -396,8 +401,8 @@ int mips_topk_batch(mad_plan* plan, const float* Q, int64_t nq,
 int mips_get_config(mad_plan* plan, int* chunk, int* unroll, int* grid);
 int mips_set_config(mad_plan* plan, int chunk, int unroll, int grid);
 
-/* Score-table slots per possible key of a query (2, 4 or 8; default 2):
- * query q's open-addressing table holds factor * max(min(s_q, m), 512)
+/* Score-table slots per possible key of a query of more than 2^18 samples
+ * (2, 4 or 8; default 2): query q's open-addressing table in memory holds factor * max(min(s_q, m), 512)
  * slots rounded up to a power of two.  A larger table passes fewer taken
  * slots per insert but takes longer to clear and to scan; results never
  * change.  A new factor re-plans the next batch. */
