@@ -406,8 +406,8 @@ static size_t t0_lds_bytes(const DenseTables& t) {
 constexpr int kOrdU = 16;
 constexpr int kOrdPer = 256 * kOrdU;
 // Some kOrdGroups groups (up to twice as many): the counts of every k are
-// written, scanned down their column and read once per group (2.7e8 samples
-// of 256 k: all passes 4.5 -> 3.2 ms against a group per tile).  Finer bins,
+// written, scanned down their column and read once per group (3e8 samples of
+// 256 k: all passes 4.5 -> 3.2 ms against a group per tile).  Finer bins,
 // (k, top bits of j's slot), so that a part of an 8 MB row T2[k] stays in the
 // L2, took 1.8 ms off the sampling of 3e8 and put 1.4 on the order.
 constexpr int64_t kOrdGroups = 8192;

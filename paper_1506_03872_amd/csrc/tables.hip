@@ -315,9 +315,9 @@ static hipError_t uniform_quanta(W w, int64_t S, int64_t N, int L,
 //            before a lane's first comes from the previous lane), and the
 //            alias table from the quanta in registers.
 // Bound by its vector instructions (some 500 a table of 150 items) and the
-// serial walk; 1e5 tables of 96 / 150 / 256 items take 87 / 131 / 280 us,
-// their bytes at 4.7 TB/s 31 / 56 / 65 us.  (One lane per table and blocks of
-// four tables took 137 / 290 / 1098 us.)
+// serial walk; 1e5 tables of 100 items, 65,133 of 150 and 1e5 of 256 take 87,
+// 131 and 280 us, their bytes at 4.7 TB/s 30, 37 and 65 us.  (One lane per
+// table and blocks of four tables took 137, 290 and 1098 us.)
 // Padding slots and dead tables get q = 0.
 template <int SPL, class W>
 __global__ __launch_bounds__(256) void k_small_tables(W w, int64_t S,
@@ -430,11 +430,11 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
   if (S <= 0 || N <= 0) return hipSuccess;
   const int Np = 1 << L;
   // the most tables per block (4, 8 or 16) within the LDS budget: the serial
-  // walk takes one wave as long for 16 tables as for one (1e5 tables of 150
-  // items, one lane a table: 290 us with 4, 197 with 8, 184 with 16; of 96
-  // items 106 us with 16, 122 with 32, where fewer blocks share a CU).
+  // walk takes one wave as long for 16 tables as for one (65,133 tables of 150
+  // items, one lane a table: 290 us with 4, 197 with 8, 184 with 16; 1e5 of
+  // 100 items 106 us with 16, 122 with 32, where fewer blocks share a CU).
   // MAD_SMALL_LDS overrides the budget for tuning.  Fewer where the tables
-  // would not give every CU two blocks (1000 tables of 50 items: 17 -> 9.6
+  // would not give every CU two blocks (1000 tables of 64 items: 17 -> 9.6
   // us).
   static const size_t budget = [] {
     const char* e = getenv("MAD_SMALL_LDS");
@@ -467,7 +467,7 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
 // thread F and the quanta of four slots in registers, the two lists by a scan
 // over the workgroup, and one search per slot.  X is read once and the
 // entries are written once, in slot order; the pipeline of the larger tables
-// (seven kernels with the lists in memory) took 95 us for 50 tables of 1000
+// (seven kernels with the lists in memory) took 95 us for 64 tables of 1000
 // items, mostly launches and their gaps, where this takes 12.  All tables of a
 // 1000 x 1000 x 50 plan 272 -> 120 us, of 4096 x 4096 x 1024 468 -> 277, of
 // 1e5 x 600 x 1000 (rows) 5.2 -> 3.0 ms.  4096 slots are the most whose
