@@ -303,8 +303,8 @@ int mad_bruteforce_topk(const float* A, int64_t m, const float* B, int64_t n,
  * as for mad_plan_topk, x = 0.
  *   CSR arrays as for mad_plan_create_csr (device; validated, MAD_EINVAL
  *   when malformed or non-finite).  heavy: number of heavy coordinates, 0
- *   to take the fewest (a multiple of 64) that leave at most 2^30 light
- *   wedges; MAD_EUNSUPPORTED when that needs more than 4096.
+ *   to take as many as are expected fastest of those numbers that leave at
+ *   most 2^30 light wedges; MAD_EUNSUPPORTED when that needs more than 4096.
  *   out, n_out (device) as for mad_plan_topk; stats (host, optional).
  * Memory: dense copies of 4 (m + n) H bytes and about 40 bytes per light
  * wedge.  Synchronises; keeps a process-wide workspace between calls.

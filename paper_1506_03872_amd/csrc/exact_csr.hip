@@ -110,8 +110,17 @@ __global__ __launch_bounds__(256) void k_wedge_hist(const uint32_t* dA,
 
 // The cut: of the bins that leave at most kMaxLightWedges light wedges and
 // 1 to kMaxHeavy heavy coordinates, the one with the least expected time,
-// col_ns per heavy coordinate (a column of the dense product) and wedge_ns
-// per light wedge.  cut = -1 when there is none (or no wedge at all).
+// col_ns per column of the dense product (the heavy coordinates, padded to a
+// K step of the GEMM that takes them) and wedge_ns per light wedge.  Between
+// cuts of one padded width the deepest wins, so that no column is left to
+// padding: at 1e6 x 1e6 over 1e5 coordinates 477 heavy ones leave 3.0e7 light
+// candidates to the re-rank, 509 leave 1.4e5 in the same product.  cut = -1
+// when there is none (or no wedge at all).
+struct ColumnPad {
+  int panel, panel_step;  // widest K of the register-panel GEMM, its K step
+  int step;               // K step of the GEMM for longer vectors
+};
+
 struct SplitCut {
   int64_t cut, live;
   int64_t wedges;
@@ -120,6 +129,7 @@ struct SplitCut {
 __global__ __launch_bounds__(256) void k_split_cut(const SplitHist* h,
                                                    double col_ns,
                                                    double wedge_ns,
+                                                   ColumnPad pad,
                                                    SplitCut* out) {
   __shared__ unsigned long long ws[4], cs[4];
   __shared__ double best[256];
@@ -155,7 +165,10 @@ __global__ __launch_bounds__(256) void k_split_cut(const SplitHist* h,
     if (light > (unsigned long long)kMaxLightWedges ||
         hc > (unsigned long long)kMaxHeavy)
       continue;
-    const double cost = col_ns * (double)hc + wedge_ns * (double)light;
+    const unsigned long long step =
+        hc <= (unsigned long long)pad.panel ? pad.panel_step : pad.step;
+    const double cost = col_ns * (double)((hc + step - 1) / step * step) +
+                        wedge_ns * (double)light;
     if (cost < best[t]) {
       best[t] = cost;
       at[t] = b;
@@ -395,6 +408,12 @@ static double split_col_ns(int prec, int64_t m, int64_t n) {
 }
 constexpr double kWedgeNs = 0.07;
 
+static ColumnPad column_pad(int prec) {
+  return prec == 0   ? ColumnPad{256, 8, 32}
+         : prec == 1 ? ColumnPad{256, 16, 64}
+                     : ColumnPad{512, 64, 128};
+}
+
 // device_split: cut the coordinates on the device at the least expected
 // time; *again = true when the other rule has to be used (no such cut, or
 // fewer than t pairs with c != 0 found among the heavy candidates, where the
@@ -472,7 +491,7 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
     int64_t* part = tot + 16;
     k_wedge_hist<<<grid_of(d, 256 * 8, 256), 256, 0, st>>>(dA, dB, d, hist);
     k_split_cut<<<1, 256, 0, st>>>(hist, split_col_ns(prec, m, n), kWedgeNs,
-                                   cut);
+                                   column_pad(prec), cut);
     k_split_count<<<(unsigned)tiles, 256, 0, st>>>(dA, dB, d, cut, part);
     if ((e = launch_scan_parts(part, tiles, kSplitVals, tot, st)) !=
         hipSuccess)
