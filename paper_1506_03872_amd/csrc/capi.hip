@@ -6,7 +6,6 @@
 #include <string.h>
 
 #include <algorithm>
-#include <memory>
 #include <mutex>
 #include <new>
 #include <string>
@@ -94,8 +93,19 @@ struct MipsState {
   bool ran = false;
 };
 
+// the current device, -1 when there is none
+static int current_device() {
+  int dev = -1;
+  if (hipGetDevice(&dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return -1;
+  }
+  return dev;
+}
+
 struct mad_plan {
   int kind = 0;  // 0 dense MAD, 1 MIPS database, 2 sparse (CSR) MAD
+  int dev = current_device();  // where it was made and its tables lie
   const float* A = nullptr;
   const float* B = nullptr;
   int64_t m = 0, n = 0, d = 0;
@@ -159,13 +169,9 @@ static const float* plan_bmax(const mad_plan* p) {
   return p->kind == 2 ? p->ct.bmax : p->dt.bmax;
 }
 
-// Waits for the device: the plan's memory goes to the free list, from which
-// another plan may take it for any stream.
-static void plan_free_all(mad_plan* p) {
-  const bool idle = hipDeviceSynchronize() == hipSuccess;
-  std::unique_ptr<mad::PoolScope> pool(idle ? new (std::nothrow)
-                                                  mad::PoolScope()
-                                            : nullptr);
+// idle_dev: as for PoolScope
+static void plan_release(mad_plan* p, int idle_dev) {
+  const mad::PoolScope pool(idle_dev);
   mips_free(p->mips);
   p->mips = nullptr;
   mad::dense_tables_free(p->dt);
@@ -191,6 +197,18 @@ static void plan_free_all(mad_plan* p) {
       (void)hipEventDestroy(e);
       e = nullptr;
     }
+}
+
+// Waits for the plan's device, which need not be the caller's current one:
+// the plan's memory goes to that device's free list, from which another plan
+// may take it for any stream.
+static void plan_free_all(mad_plan* p) {
+  const int cur = current_device();
+  const bool away = p->dev >= 0 && cur >= 0 && cur != p->dev;
+  const bool here = !away || hipSetDevice(p->dev) == hipSuccess;
+  const bool idle = here && hipDeviceSynchronize() == hipSuccess;
+  plan_release(p, idle ? p->dev : -1);
+  if (away) (void)hipSetDevice(cur);
 }
 
 static int check_bad_inputs(mad_plan* p, hipStream_t st) {

@@ -30,10 +30,11 @@ void mem_free(void* p);  // p may be null
 hipError_t dev_alloc(DeviceBuffer& b, size_t bytes);
 void dev_free(DeviceBuffer& b);
 
-// While one is alive on a thread, what that thread frees is kept for later
-// allocations.  Only after the device has been synchronised.
+// While one is alive on a thread, the blocks of device `idle_dev` that the
+// thread frees are kept for later allocations on that device (-1: none).
+// Only after that device has been synchronised.
 struct PoolScope {
-  PoolScope();
+  explicit PoolScope(int idle_dev);
   ~PoolScope();
 };
 
