@@ -217,10 +217,16 @@ int mad_topk(const float* A, int64_t m, const float* B, int64_t n, int64_t d,
              int64_t t, int64_t s, int64_t t_prime, uint64_t seed,
              mad_pair* out, int64_t* n_out, void* stream);
 
-/* Release a plan and its device memory (synchronises the device first).  Up
- * to 2 GiB of what destroyed plans held is kept for the next plan's tables
- * and given back to the device when an allocation needs it. */
+/* Release a plan and its device memory (synchronises the plan's device
+ * first).  Up to 2 GiB of what destroyed plans held is kept for the next
+ * plan's tables.  It goes back to the device when an allocation of this
+ * library fails, and by mad_trim_memory; another allocator in the process
+ * that runs out does not get it back by itself. */
 void mad_plan_destroy(mad_plan* plan);
+
+/* Give back to the device what destroyed plans left for later ones; returns
+ * its bytes.  Live plans keep theirs.  Any thread may call it at any time. */
+int64_t mad_trim_memory(void);
 
 /* ---------------------------------------------------------------------------
  * Plan statistics of the last mad_plan_topk (host outputs, synchronises):

@@ -37,6 +37,7 @@ EXPORTS = (
     "mad_plan_get_option", "mad_accumulate_noalloc",
     "mad_bruteforce_topk_csr", "mad_debug_lowp_screen",
     "mips_get_table_factor", "mips_set_table_factor", "mips_autotune_cache",
+    "mad_trim_memory",
 )
 
 
@@ -70,6 +71,8 @@ def lib():
                                _u64, _P, _P, _P]
         L.mad_plan_destroy.argtypes = [_P]
         L.mad_plan_destroy.restype = None
+        L.mad_trim_memory.argtypes = []
+        L.mad_trim_memory.restype = _i64
         L.mad_plan_stats.argtypes = [_P, _P, _P, _P, _P, _P]
         L.mad_debug_table.argtypes = [_P, C.c_int, _i64, _P, _P, _P, _i64, _P]
         L.mad_debug_norms.argtypes = [_P, _P, _P, _P, _P]
@@ -574,6 +577,13 @@ def probe_memory(kind, buf, nops, seed=0, stream=None):
     import torch
     _check(lib().mad_probe_memory(kind, _dev(buf, torch.int64, "buf"),
                                   buf.numel(), nops, seed, _stream(stream)))
+
+
+def trim_memory():
+    """Give the device memory that destroyed plans left for later ones (up
+    to 2 GiB) back to the device, for instance to another allocator in the
+    process that has run out; returns its bytes."""
+    return lib().mad_trim_memory()
 
 
 def topk(A, B, t, s, t_prime, seed=0, stream=None):

@@ -410,6 +410,8 @@ void mad_plan_destroy(mad_plan* p) {
   delete p;
 }
 
+int64_t mad_trim_memory(void) { return (int64_t)mad::mem_trim(); }
+
 // How X is built (result-invariant): from per-sample pairs by partitioned
 // accumulation (default), or in an open-addressing hash table updated by the
 // sampler with atomics (process default MAD_ACCUM=hash; per plan through

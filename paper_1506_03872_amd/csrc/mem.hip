@@ -48,6 +48,8 @@ hipError_t mem_alloc(void** out, size_t bytes) {
 
 void mem_free(void* p) { pool().release(p, t_idle_dev); }
 
+size_t mem_trim() { return pool().trim(); }
+
 hipError_t dev_alloc(DeviceBuffer& b, size_t bytes) {
   if (b.bytes >= bytes && b.p) return hipSuccess;
   dev_free(b);

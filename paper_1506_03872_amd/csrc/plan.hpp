@@ -27,6 +27,7 @@ struct DeviceBuffer {
 // ---- mem.hip -------------------------------------------------------------
 hipError_t mem_alloc(void** out, size_t bytes);
 void mem_free(void* p);  // p may be null
+size_t mem_trim();       // the free list back to the device; its bytes
 hipError_t dev_alloc(DeviceBuffer& b, size_t bytes);
 void dev_free(DeviceBuffer& b);
 
