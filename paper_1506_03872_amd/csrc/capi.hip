@@ -61,6 +61,12 @@ int64_t next_pow2(int64_t v) {
 
 // MIPS batch state: per-query layout, workspace, the captured launch graph
 // and the tuned launch shape
+// a run of the batch's units and (query, bin) items whose words are in
+// memory together
+struct MipsGroup {
+  int64_t unit0, units, item0, items;
+};
+
 struct MipsState {
   mad::Family T0q;  // stage-0 table per query (capacity nq_cap tables)
   int64_t nq_cap = 0;
@@ -69,7 +75,8 @@ struct MipsState {
   // layout of the prepared batch
   std::vector<int64_t> s, tp;
   int64_t nq = -1, t = -1;
-  int64_t hslots = 0, nchunks = 0, nunits = 0, nitems = 0, unit = 1;
+  int64_t hslots = 0, nchunks = 0, unit = 1;
+  std::vector<MipsGroup> groups;
   int chunk_prepared = -1, slots_prepared = -1;
   // launch shape and score-table slots per possible key (result-invariant)
   int chunk = 4096, unroll = 4, grid = 2048, slots = 2;
@@ -1404,7 +1411,8 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
     if (s[q] <= mad::kMaxPartBudget) total += s[q];
   int64_t words = 64;
   while (words < 1024 && total / words > 2048) words *= 2;
-  int64_t hs = 0, cs = 0, ss = 0, po = 0, oo = 0;
+  int64_t hs = 0, cs = 0, ss = 0;
+  int64_t tables = 0;  // what tables in memory would take instead of words
   for (int64_t q = 0; q < nq; ++q) {
     mad::MipsQuery& x = qi[(size_t)q];
     memset(&x, 0, sizeof x);
@@ -1426,10 +1434,7 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
              (((m - 1) >> x.shift) + 1) * words < sq)
         --x.shift;
       x.bins = (int)((m - 1) >> x.shift) + 1;
-      x.poff = po;
-      x.ooff = oo;
-      po += (sq + 1) / 2 * 2;
-      oo += (sq + unit - 1) / unit * (x.bins + 1);
+      tables += 8 * next_pow2(2 * (pairs > 512 ? pairs : 512));
     } else if (sq > 0) {  // a table in memory
       const int64_t hcap =
           next_pow2((int64_t)ms->slots * (pairs > 512 ? pairs : 512));
@@ -1452,8 +1457,58 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
     return s[a] > s[b];
   });
   std::vector<mad::MipsChunk> ch, un;
+  std::vector<mad::MipsItem> items;
+  std::vector<MipsGroup> groups;
+  // The words and offsets of one group of queries are in memory at a time:
+  // a word per sample is more than a table when a query's budget is several
+  // times m (2000 queries of 2^18 samples on 1000 vectors: 4.2 GB of words,
+  // 33 MB of tables).  A group takes what its batch's tables would have
+  // taken, at least kMipsPartBytes (128 queries of the largest budget, far
+  // more workgroups than the chip holds), and at most kMipsGroupItems items,
+  // each a workgroup of one launch.
+  const int64_t part_bytes =
+      tables > mad::kMipsPartBytes ? tables : mad::kMipsPartBytes;
+  // queries of the open group by log2(finest ranges per bin)
+  std::vector<int32_t> by_width[mad::kMaxBinsLog + 1];
+  const int fine = lm > mad::kMaxBinsLog ? lm - mad::kMaxBinsLog : 0;
+  MipsGroup grp = {0, 0, 0, 0};
+  int64_t po = 0, oo = 0, pmax = 0, omax = 0;
+  const auto close_group = [&]() {
+    // items by range of i: of the finest ranges, those at which a query's
+    // bin starts
+    for (int64_t r = 0; r <= (m - 1) >> fine; ++r)
+      for (int f = 0;
+           f <= mad::kMaxBinsLog && (r & ((int64_t(1) << f) - 1)) == 0; ++f)
+        for (int32_t q : by_width[f])
+          items.push_back(mad::MipsItem{q, (int32_t)(r >> f)});
+    for (std::vector<int32_t>& v : by_width) v.clear();
+    grp.units = (int64_t)un.size() - grp.unit0;
+    grp.items = (int64_t)items.size() - grp.item0;
+    if (grp.units > 0) groups.push_back(grp);
+    grp = {(int64_t)un.size(), 0, (int64_t)items.size(), 0};
+    pmax = po > pmax ? po : pmax;
+    omax = oo > omax ? oo : omax;
+    po = oo = 0;
+  };
+  int64_t gitems = 0;
   for (int32_t q : order) {
-    const bool part = qi[(size_t)q].bins != 0;
+    mad::MipsQuery& x = qi[(size_t)q];
+    const bool part = x.bins != 0;
+    if (part) {
+      const int64_t wq = (s[q] + 1) / 2 * 2;
+      const int64_t oq = (s[q] + unit - 1) / unit * (x.bins + 1);
+      if (po > 0 && (8 * (po + wq) + 2 * (oo + oq) > part_bytes ||
+                     gitems + x.bins > mad::kMipsGroupItems)) {
+        close_group();
+        gitems = 0;
+      }
+      x.poff = po;
+      x.ooff = oo;
+      po += wq;
+      oo += oq;
+      gitems += x.bins;
+      by_width[x.shift - fine].push_back(q);
+    }
     const int64_t step = part ? unit : ms->chunk;
     for (int64_t l0 = 0; l0 < s[q]; l0 += step) {
       mad::MipsChunk c;
@@ -1463,20 +1518,7 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
       (part ? un : ch).push_back(c);
     }
   }
-  // items by range of i: of the finest ranges, those at which a query's
-  // bin starts
-  std::vector<mad::MipsItem> items;
-  // queries by log2(finest ranges per bin)
-  std::vector<int32_t> by_width[mad::kMaxBinsLog + 1];
-  const int fine = lm > mad::kMaxBinsLog ? lm - mad::kMaxBinsLog : 0;
-  for (int32_t q : order)
-    if (qi[(size_t)q].bins)
-      by_width[qi[(size_t)q].shift - fine].push_back(q);
-  for (int64_t r = 0; r <= (m - 1) >> fine; ++r)
-    for (int f = 0;
-         f <= mad::kMaxBinsLog && (r & ((int64_t(1) << f) - 1)) == 0; ++f)
-      for (int32_t q : by_width[f])
-        items.push_back(mad::MipsItem{q, (int32_t)(r >> f)});
+  close_group();
   (void)hipDeviceSynchronize();
   mips_drop_graph(ms);
   hipError_t e = hipSuccess;
@@ -1496,8 +1538,8 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
       (e = mad::dev_alloc(ms->units, (un.size() + 1) * sizeof(mad::MipsChunk))) != hipSuccess ||
       (e = mad::dev_alloc(ms->items, (items.size() + 1) * sizeof(mad::MipsItem))) != hipSuccess ||
       (e = mad::dev_alloc(ms->hash, (size_t)(hs + 1) * 8)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->part, (size_t)(po + 2) * 8)) != hipSuccess ||
-      (e = mad::dev_alloc(ms->offs, (size_t)(oo + 1) * 2)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->part, (size_t)(pmax + 2) * 8)) != hipSuccess ||
+      (e = mad::dev_alloc(ms->offs, (size_t)(omax + 1) * 2)) != hipSuccess ||
       (e = mad::dev_alloc(ms->qcnt, nqa * sizeof(mad::MipsCount))) != hipSuccess ||
       (e = mad::dev_alloc(ms->cw, (size_t)(cs + 1) * 8)) != hipSuccess ||
       (e = mad::dev_alloc(ms->sw, (size_t)(ss + 1) * 8)) != hipSuccess ||
@@ -1530,8 +1572,7 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
   ms->t = t;
   ms->hslots = hclear;
   ms->nchunks = (int64_t)ch.size();
-  ms->nunits = (int64_t)un.size();
-  ms->nitems = (int64_t)items.size();
+  ms->groups = std::move(groups);
   ms->unit = unit;
   ms->chunk_prepared = ms->chunk;
   ms->slots_prepared = ms->slots;
@@ -1571,10 +1612,10 @@ static mad::MipsArgs mips_args(mad_plan* p, const float* Q, uint64_t seed,
   a.hslot = (uint64_t*)ms->hash.p;
   a.kb = mips_key_bits(p->m);
   a.units = (const mad::MipsChunk*)ms->units.p;
-  a.nunits = ms->nunits;
+  a.nunits = 0;
   a.unit = ms->unit;
   a.items = (const mad::MipsItem*)ms->items.p;
-  a.nitems = ms->nitems;
+  a.nitems = 0;
   a.part = (uint64_t*)ms->part.p;
   a.offs = (uint16_t*)ms->offs.p;
   a.qcnt = (mad::MipsCount*)ms->qcnt.p;
@@ -1632,12 +1673,23 @@ static hipError_t mips_enqueue(mad_plan* p, const mad::MipsArgs& a,
     return e;
   if (events) record(p, 3, st);
   if ((e = mad::launch_sample_mips(a, ms->unroll, ms->grid, st)) !=
-          hipSuccess ||
-      (e = mad::launch_sample_mips_part(a, ms->unroll, ms->grid, st)) !=
-          hipSuccess)
+      hipSuccess)
     return e;
-  if (events) record(p, 4, st);
-  if ((e = mad::launch_mips_bins(a, st)) != hipSuccess) return e;
+  if (ms->groups.empty() && events) record(p, 4, st);
+  for (size_t g = 0; g < ms->groups.size(); ++g) {
+    const MipsGroup& grp = ms->groups[g];
+    mad::MipsArgs b = a;
+    b.units += grp.unit0;
+    b.nunits = grp.units;
+    b.items += grp.item0;
+    b.nitems = grp.items;
+    if ((e = mad::launch_sample_mips_part(b, ms->unroll, ms->grid, st)) !=
+        hipSuccess)
+      return e;
+    // (with several groups the sampling phase ends at the last one's)
+    if (events && g + 1 == ms->groups.size()) record(p, 4, st);
+    if ((e = mad::launch_mips_bins(b, st)) != hipSuccess) return e;
+  }
   if ((e = mad::launch_mips_post(a, st)) != hipSuccess) return e;
   if (events) record(p, 5, st);
   return hipSuccess;

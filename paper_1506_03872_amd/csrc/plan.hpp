@@ -372,6 +372,10 @@ constexpr int kMipsUnit = 4096;
 constexpr int kMaxBinsLog = 9;
 constexpr int kMaxBins = 1 << kMaxBinsLog;
 constexpr int64_t kMaxPartBudget = int64_t(1) << 18;
+// least bytes of words and offsets that the queries of one group may take,
+// and most (query, bin) items of a group, each a workgroup of one launch
+constexpr int64_t kMipsPartBytes = int64_t(1) << 28;
+constexpr int64_t kMipsGroupItems = int64_t(1) << 20;
 
 // a contiguous range of one query's samples
 struct MipsChunk {
@@ -410,8 +414,9 @@ struct MipsArgs {
   // of k_mips_bins
   uint64_t* hslot;
   int kb;
-  // queries summed in LDS: units of at most `unit` samples, the (query, bin)
-  // items by range of i, the units' words and bin offsets, the key counts
+  // queries summed in LDS, of one group: units of at most `unit` samples, the
+  // (query, bin) items by range of i, the units' words and bin offsets; the
+  // key counts of all queries
   const MipsChunk* units;
   int64_t nunits, unit;
   const MipsItem* items;
