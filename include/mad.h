@@ -387,7 +387,7 @@ int mips_plan_create(const float* A, int64_t m, int64_t d, uint32_t flags,
  *                      -1 for a query holding NaN or Inf
  * The launches of a batch (per-query exponents and stage-0 tables; for
  * queries of at most 2^18 samples one sampling launch over units of at most
- * 4096 samples, each ordered by ranges of i, and one that sums each range in
+ * 4096 samples, each ordered by a hash of i, and one that sums each bin in
  * LDS; for larger ones the clearing of a score table in memory and a
  * persistent sampling launch over chunks; one postprocessing launch with a
  * workgroup per query) are captured once into a HIP graph, which later calls with the

@@ -1398,9 +1398,6 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
   const int64_t m = p->m;
   std::vector<mad::MipsQuery> qi((size_t)nq);
   std::vector<int32_t> order((size_t)nq);
-  // bins are ranges of i: key i falls in bin i >> shift
-  int lm = 0;
-  while ((int64_t(1) << lm) < m) ++lm;
   const int64_t unit =
       ms->chunk < mad::kMipsUnit ? ms->chunk : mad::kMipsUnit;
   // samples per bin aimed at: up to 1024 (half the table of a bin), fewer in
@@ -1429,11 +1426,10 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
     x.soff = ss;
     x.scap = x.ccap < tpe ? x.ccap : tpe;
     if (sq > 0 && sq <= mad::kMaxPartBudget) {  // summed in LDS
-      x.shift = lm;
-      while (x.shift > 0 && lm - x.shift < mad::kMaxBinsLog &&
-             (((m - 1) >> x.shift) + 1) * words < sq)
-        --x.shift;
-      x.bins = (int)((m - 1) >> x.shift) + 1;
+      while (x.lb < mad::kMaxBinsLog && (int64_t(1) << x.lb) < m &&
+             (words << x.lb) < sq)
+        ++x.lb;
+      x.bins = 1 << x.lb;
       tables += 8 * next_pow2(2 * (pairs > 512 ? pairs : 512));
     } else if (sq > 0) {  // a table in memory
       const int64_t hcap =
@@ -1468,19 +1464,16 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
   // each a workgroup of one launch.
   const int64_t part_bytes =
       tables > mad::kMipsPartBytes ? tables : mad::kMipsPartBytes;
-  // queries of the open group by log2(finest ranges per bin)
+  // queries of the open group by log2(finest bins per bin)
   std::vector<int32_t> by_width[mad::kMaxBinsLog + 1];
-  const int fine = lm > mad::kMaxBinsLog ? lm - mad::kMaxBinsLog : 0;
   MipsGroup grp = {0, 0, 0, 0};
   int64_t po = 0, oo = 0, pmax = 0, omax = 0;
   const auto close_group = [&]() {
-    // items by range of i: of the finest ranges, those at which a query's
-    // bin starts
-    for (int64_t r = 0; r <= (m - 1) >> fine; ++r)
-      for (int f = 0;
-           f <= mad::kMaxBinsLog && (r & ((int64_t(1) << f) - 1)) == 0; ++f)
+    // items by bin: of the finest bins, those at which a query's bin starts
+    for (int32_t r = 0; r < mad::kMaxBins; ++r)
+      for (int f = 0; f <= mad::kMaxBinsLog && (r & ((1 << f) - 1)) == 0; ++f)
         for (int32_t q : by_width[f])
-          items.push_back(mad::MipsItem{q, (int32_t)(r >> f)});
+          items.push_back(mad::MipsItem{q, r >> f});
     for (std::vector<int32_t>& v : by_width) v.clear();
     grp.units = (int64_t)un.size() - grp.unit0;
     grp.items = (int64_t)items.size() - grp.item0;
@@ -1507,7 +1500,7 @@ static int mips_prepare(mad_plan* p, int64_t nq, const int64_t* s,
       po += wq;
       oo += oq;
       gitems += x.bins;
-      by_width[x.shift - fine].push_back(q);
+      by_width[mad::kMaxBinsLog - x.lb].push_back(q);
     }
     const int64_t step = part ? unit : ms->chunk;
     for (int64_t l0 = 0; l0 < s[q]; l0 += step) {

@@ -21,7 +21,7 @@
 //   k_mips_query_info   per query: fixed-point exponent, finiteness;
 //   k_sample_mips_part  persistent: workgroups walk a list of units (up to
 //                       4096 consecutive samples of one query), order a
-//                       unit's words by bin (a range of i) in LDS and store
+//                       unit's words by bin (of a hash of i) in LDS and store
 //                       them in a row with the bins' offsets;
 //   k_mips_bins         one workgroup per (query, bin): the bin's words of
 //                       all units into a table in LDS, its distinct keys
@@ -255,6 +255,19 @@ hipError_t launch_sample_mips(const MipsArgs& a, int unroll, int grid,
 // ---------------------------------------------------------------------------
 constexpr int kPartThreads = 512;
 
+// Bin of key i, one of 2^lb: the top bits of a hash, so that every bin gets
+// its share of the samples wherever the weight of the database lies, and a
+// query's bins are unions of the bins of a query that has more.  (Ranges of
+// i, on 1e6 x 128 rows ordered by norms falling as i^-0.5: most samples in a
+// few bins, 22.9 ms for 4096 queries of 1e3 to 1e5 samples, 4.7 on the same
+// rows in random order; 4.7 in either order with the hash.)  The factors are
+// odd, near 2^32 over the golden ratio and over the square root of 2.
+__device__ __forceinline__ uint32_t mips_bin(uint32_t i, int lb) {
+  uint32_t h = i * 0x9E3779B1u;
+  h = (h ^ (h >> 15)) * 0xB504F333u;
+  return (uint32_t)(((uint64_t)h << lb) >> 32);
+}
+
 size_t mips_part_lds_bytes(int L0, int64_t d) {
   return (size_t)8 * kMipsUnit + mips_sample_lds_bytes(L0, d);
 }
@@ -295,7 +308,7 @@ __global__ __launch_bounds__(kPartThreads) void k_sample_mips_part(
         words[e] = closed[u] ? ((uint64_t)inc[u] << a.kb) |
                                    ((uint64_t)key[u] + 1)
                              : 0ull;
-        if (closed[u]) atomicAdd(&cur[key[u] >> qi.shift], 1u);
+        if (closed[u]) atomicAdd(&cur[mips_bin(key[u], qi.lb)], 1u);
         nclosed += closed[u];
       }
     }
@@ -329,8 +342,8 @@ __global__ __launch_bounds__(kPartThreads) void k_sample_mips_part(
 #pragma unroll
     for (int r = 0; r < kPer; ++r)
       if (w[r])
-        words[atomicAdd(&cur[((uint32_t)(w[r] & kmask) - 1u) >> qi.shift],
-                        1u)] = w[r];
+        words[atomicAdd(
+            &cur[mips_bin((uint32_t)(w[r] & kmask) - 1u, qi.lb)], 1u)] = w[r];
     __syncthreads();
     // regions start on 16 bytes and hold an even number of words: the pair
     // after an odd total is not read
@@ -398,16 +411,16 @@ __device__ __forceinline__ void mips_dots(const float* const (&ar)[kVerU],
 // into an open-addressing table in LDS, then its distinct keys out, those
 // with x > 0 from the front of the query's region and the rest from its
 // back.  A bin expects at most about 1024 words and the table has 2048
-// slots; words that do not fit (a bin that a skewed database fills) are
+// slots; words that do not fit (keys that the hash puts in one bin) are
 // taken in halves, quarters, ... of the keys' hashes, each in a pass of its
 // own.  What bounds it is a chain of eight or so memory latencies per item,
 // so it wants workgroups in flight more than slots: 2.51 ms at 4096 queries
 // of 1e3 to 1e5 samples on 1e6 x 128, 3.49 ms with 4096 slots.
 //
-// The items go through the ranges of i in order, all queries of a range
-// together, so that the rows a range verifies (1/128 of the database for a
-// query of 1e5 samples: 4 MB at 1e6 x 128) are shared in L2 by the queries
-// instead of being fetched for each.
+// The items go through the bins in order, all queries of a bin together, so
+// that the rows a bin verifies (1/128 of the database for a query of 1e5
+// samples: 4 MB at 1e6 x 128) are shared in L2 by the queries instead of
+// being fetched for each.
 // ---------------------------------------------------------------------------
 constexpr int kBinThreads = 256;
 constexpr int kBinSlots = 2048;  // 16 KB: 8 workgroups on a CU

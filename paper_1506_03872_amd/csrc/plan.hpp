@@ -346,9 +346,9 @@ struct MipsQuery {
   uint32_t hmask;  // table capacity - 1 (a power of two minus one)
   int F;           // fixed-point exponent (device)
   int live;        // 1: finite query (device)
-  int bins;        // ranges of i its words are ordered by (0: its scores
-                   // are kept in a table of hmask + 1 slots)
-  int shift;       // bin of key i: i >> shift
+  int bins;        // bins its words are ordered by (0: its scores are kept
+                   // in a table of hmask + 1 slots)
+  int lb;          // log2 bins; bin of key i: mips_bin(i, lb)
   int pad;
   int64_t poff;    // first word in MipsArgs::part
   int64_t ooff;    // first offset in MipsArgs::offs (bins + 1 per unit)
@@ -415,7 +415,7 @@ struct MipsArgs {
   uint64_t* hslot;
   int kb;
   // queries summed in LDS, of one group: units of at most `unit` samples, the
-  // (query, bin) items by range of i, the units' words and bin offsets; the
+  // (query, bin) items by bin, the units' words and bin offsets; the
   // key counts of all queries
   const MipsChunk* units;
   int64_t nunits, unit;
