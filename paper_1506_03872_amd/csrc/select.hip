@@ -1020,14 +1020,17 @@ struct PairOut {
 // whole set, a thread per other element and a ballot per comparison, so t
 // elements take t / 16 workgroups and t / 256 rounds each.  (A thread per
 // element, walking the set in LDS, left 4 workgroups in a chain of t LDS
-// reads: 73 us at t = 1000, 10 us now.)
+// reads: 73 us at t = 1000, 10 us now.)  From t = 2e5 on the instructions of
+// the comparisons bound it: |c| alone is compared, as an integer, and the
+// keys only in rounds where some |c| is equal (re-rank of 20,000 x 20,000 x 64
+// with t = 4e5: 62.7 -> 19.1 ms, 30 when most |c| are equal; 8e5: 243 -> 67).
 constexpr int kSortElems = 16;
 
 __global__ __launch_bounds__(256) void k_final_sort(
     const uint64_t* fkey, const uint64_t* fx, const float* fc,
     const int64_t* counts, int64_t tcap, int64_t n, const float* bmax,
     int64_t s_for_F, int x_shift, PairOut* out, int64_t* n_out) {
-  __shared__ float ea[kSortElems];
+  __shared__ uint32_t ea[kSortElems];
   __shared__ uint64_t ek[kSortElems];
   __shared__ unsigned long long rank[kSortElems];
   const int64_t nf = counts[kCntFinal] < tcap ? counts[kCntFinal] : tcap;
@@ -1037,24 +1040,34 @@ __global__ __launch_bounds__(256) void k_final_sort(
   const int t = threadIdx.x, lane = t & 63;
   if (t < kSortElems) {
     const bool in = e0 + t < nf;
-    ea[t] = in ? fabsf(fc[e0 + t]) : 0.0f;
+    ea[t] = in ? __float_as_uint(fabsf(fc[e0 + t])) : 0u;
     ek[t] = in ? fkey[e0 + t] : 0ull;
     rank[t] = 0ull;
   }
   __syncthreads();
-  unsigned long long before[kSortElems] = {};
+  uint32_t before[kSortElems] = {};  // at most a quarter of nf each
   for (int64_t o0 = 0; o0 < nf; o0 += 256) {
+    // past the end: |c| = 0 and the largest key, before no element
     const bool in = o0 + t < nf;
-    const float ao = in ? fabsf(fc[o0 + t]) : 0.0f;
-    const uint64_t ko = in ? fkey[o0 + t] : 0ull;
+    const uint32_t ao = in ? __float_as_uint(fabsf(fc[o0 + t])) : 0u;
+    uint64_t tie = 0;
 #pragma unroll
-    for (int u = 0; u < kSortElems; ++u)
-      before[u] += __popcll(
-          __ballot(in && (ao > ea[u] || (ao == ea[u] && ko < ek[u]))));
+    for (int u = 0; u < kSortElems; ++u) {
+      before[u] += (uint32_t)__popcll(__ballot(ao > ea[u]));
+      tie |= __ballot(ao == ea[u]);
+    }
+    if (tie) {
+      const uint64_t ko = in ? fkey[o0 + t] : ~0ull;
+#pragma unroll
+      for (int u = 0; u < kSortElems; ++u)
+        before[u] += (uint32_t)__popcll(__ballot(ao == ea[u]) &
+                                        __ballot(ko < ek[u]));
+    }
   }
   if (lane == 0)
 #pragma unroll
-    for (int u = 0; u < kSortElems; ++u) atomicAdd(&rank[u], before[u]);
+    for (int u = 0; u < kSortElems; ++u)
+      atomicAdd(&rank[u], (unsigned long long)before[u]);
   __syncthreads();
   if (t < kSortElems && e0 + t < nf) {
     const int F = (bmax ? fix_exponent(*bmax, s_for_F) : 0) + x_shift;
