@@ -113,9 +113,7 @@ __global__ __launch_bounds__(256) void k_wedge_hist(const uint32_t* dA,
 // col_ns per column of the dense product (the heavy coordinates, padded to a
 // K step of the GEMM that takes them) and wedge_ns per light wedge.  Between
 // cuts of one padded width the deepest wins, so that no column is left to
-// padding: at 1e6 x 1e6 over 1e5 coordinates 477 heavy ones leave 3.0e7 light
-// candidates to the re-rank, 509 leave 1.4e5 in the same product.  cut = -1
-// when there is none (or no wedge at all).
+// padding.  cut = -1 when there is none (or no wedge at all).
 struct ColumnPad {
   int panel, panel_step;  // widest K of the register-panel GEMM, its K step
   int step;               // K step of the GEMM for longer vectors
@@ -282,26 +280,36 @@ __global__ __launch_bounds__(256) void k_split_fill(
 
 // one thread per vector: its heavy entries into column pos[k] of a dense
 // row (zero-filled before), and the L2 norms of its heavy and of its light
-// entries (x, y of nhl), rounded up
+// entries (x, y of nhl), rounded up; *lmost = the most light entries of a
+// vector (cleared before)
 __global__ void k_split_rows(const int64_t* ptr, const int32_t* idx,
                              const float* val, int64_t rows,
                              const int32_t* pos, int64_t H, float* dense,
-                             float2* nhl) {
+                             float2* nhl, unsigned* lmost) {
   const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= rows) return;
-  double sh = 0.0, sl = 0.0;
-  for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
-    const float v = val[e];
-    const int32_t p = pos[idx[e]];
-    if (p >= 0) {
-      dense[r * H + p] = v;
-      sh += (double)v * v;
-    } else {
-      sl += (double)v * v;
+  unsigned light = 0;
+  if (r < rows) {
+    double sh = 0.0, sl = 0.0;
+    for (int64_t e = ptr[r]; e < ptr[r + 1]; ++e) {
+      const int32_t p = pos[idx[e]];
+      const float v = val[e];
+      if (p >= 0) {
+        dense[r * H + p] = v;
+        sh += (double)v * v;
+      } else {
+        sl += (double)v * v;
+        ++light;
+      }
     }
+    nhl[r] = make_float2((float)(sqrt(sh) * (1.0 + 1e-6)),
+                         (float)(sqrt(sl) * (1.0 + 1e-6)));
   }
-  nhl[r] = make_float2((float)(sqrt(sh) * (1.0 + 1e-6)),
-                       (float)(sqrt(sl) * (1.0 + 1e-6)));
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const unsigned o = __shfl_xor(light, off, 64);
+    light = light > o ? light : o;
+  }
+  if ((threadIdx.x & 63) == 0 && light > *lmost) atomicMax(lmost, light);
 }
 
 // the light coordinates' lists of vectors (any order inside a list)
@@ -374,8 +382,8 @@ __global__ void k_light_prune(const uint64_t* okey, const int64_t* oval,
     const int64_t j = (int64_t)(key - (uint64_t)i * (uint64_t)n);
     const double x = fabs(ldexp((double)oval[e], -F));
     // fp32 products err by at most 2^-24 of sum |a_ik b_jk| <= ||a^L||
-    // ||b^L||, the fixed-point sum by 2^-F per wedge (wslack = W 2^-F
-    // bounds them all), the heavy part by ||a^H|| ||b^H||
+    // ||b^L||, the fixed-point sum by 2^-F per wedge of the pair (wslack
+    // bounds that), the heavy part by ||a^H|| ||b^H||
     const float2 a = na[i], b = nb[j];  // heavy, light norm
     const double ub = x + 1e-5 * (double)a.y * b.y + wslack +
                       (double)a.x * b.x * (1.0 + 1e-5);
@@ -605,7 +613,10 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
   float* taval = (float*)(tarow + la);
   uint32_t* tbrow = (uint32_t*)(taval + la);
   float* tbval = (float*)(tbrow + lb);
-  float* lmax = (float*)((char*)w.misc.p + 512);  // of A's, of B's lists
+  // largest |value| of A's and of B's light lists, then the most light
+  // entries of a vector on either side
+  float* lmax = (float*)((char*)w.misc.p + 512);
+  unsigned* lmost = (unsigned*)(lmax + 2);
   {
     FillBatch f{};
     f.count = 4;
@@ -616,13 +627,15 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
     f.p[2] = (uint64_t*)curA;
     f.n[2] = d;
     f.p[3] = (uint64_t*)lmax;
-    f.n[3] = 1;
+    f.n[3] = 2;
     if ((e = launch_fill_multi(f, st)) != hipSuccess) return e;
   }
   k_split_rows<<<grid_of(m, 256, 1u << 30), 256, 0, st>>>(
-      in.a_ptr, in.a_idx, in.a_val, m, dpos, Hc, (float*)w.ah.p, na);
+      in.a_ptr, in.a_idx, in.a_val, m, dpos, Hc, (float*)w.ah.p, na,
+      lmost);
   k_split_rows<<<grid_of(n, 256, 1u << 30), 256, 0, st>>>(
-      in.b_ptr, in.b_idx, in.b_val, n, dpos, Hc, (float*)w.bh.p, nb);
+      in.b_ptr, in.b_idx, in.b_val, n, dpos, Hc, (float*)w.bh.p, nb,
+      lmost + 1);
   k_light_lists<<<grid_of(m, 256, 1u << 30), 256, 0, st>>>(
       in.a_ptr, in.a_idx, in.a_val, m, dpos, dtaptr, curA, tarow, taval);
   k_light_lists<<<grid_of(n, 256, 1u << 30), 256, 0, st>>>(
@@ -716,17 +729,24 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
                      0, st>>>((const int32_t*)w.lk.p,
                               (const int64_t*)w.wpre.p, nl, W, dtaptr, tarow,
                               taval, dtbptr, tbrow, tbval, n, lkeys, lvals);
-    // fixed point: |products| < 2^(ea + eb), at most W of them per pair
-    float hmax[2];
-    if ((e = hipMemcpyAsync(hmax, lmax, sizeof hmax, hipMemcpyDeviceToHost,
-                            st)) != hipSuccess ||
+    // fixed point: |products| < 2^(ea + eb), and a pair has no more of them
+    // than either vector has light entries.  (With W, the wedges of all
+    // pairs, in its place the slack W 2^-F, which grows as W^2, passed tau
+    // at 5.4e8 wedges of lognormal values: 5.4e7 pairs to re-rank at 3e5 x
+    // 3e5 and 192 columns, 257 now, and past 2^27 of them an error.)
+    struct {
+      float amax, bmax;
+      unsigned most[2];
+    } h;
+    if ((e = hipMemcpyAsync(&h, lmax, sizeof h, hipMemcpyDeviceToHost, st)) !=
+            hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
       return e;
-    const float amax = hmax[0], bmax = hmax[1];
+    const int64_t per_pair = h.most[0] < h.most[1] ? h.most[0] : h.most[1];
     int ea = 0, eb = 0, lw = 0;
-    (void)frexpf(amax, &ea);
-    (void)frexpf(bmax, &eb);
-    while ((int64_t(1) << lw) < W) ++lw;
+    (void)frexpf(h.amax, &ea);
+    (void)frexpf(h.bmax, &eb);
+    while ((int64_t(1) << lw) < per_pair) ++lw;
     const int F = 62 - ea - eb - lw;
     uint64_t* okey = (uint64_t*)w.acc.p;
     int64_t* oval = (int64_t*)(okey + W);
@@ -740,7 +760,8 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
     if ((e = launch_fill_u64((uint64_t*)ucnt, 1, 0ull, st)) != hipSuccess)
       return e;
     k_light_prune<<<grid_of(W, 256 * 8, 8192), 256, 0, st>>>(
-        okey, oval, lcnt + 1, F, ldexp((double)W, -F), n, na, nb, tau_use,
+        okey, oval, lcnt + 1, F, ldexp((double)per_pair, -F), n, na, nb,
+        tau_use,
         ukeys + heavy_cand, ucnt, lcap);
     unsigned long long got = 0;
     if ((e = hipMemcpyAsync(&got, ucnt, 8, hipMemcpyDeviceToHost, st)) !=
@@ -818,7 +839,9 @@ hipError_t bruteforce_topk_csr(const CsrView& in, int64_t m, int64_t n,
     const hipError_t e =
         topk_csr_run(in, m, n, d, nnzA, nnzB, prec, t, 0, true, &again, out,
                      n_out, stats, st);
-    if (e != hipSuccess || !again) return e;
+    // (more candidates than there is room for at this cut: there may be
+    // fewer at the host's)
+    if (e != hipErrorOutOfMemory && (e != hipSuccess || !again)) return e;
   }
   return topk_csr_run(in, m, n, d, nnzA, nnzB, prec, t, heavy_req, false,
                       &again, out, n_out, stats, st);
