@@ -85,6 +85,7 @@ struct GemmArgs {
   float onepu;     // 1 + u
   float d_f;       // d (for the eta * eta term)
   // pass A
+  int64_t target;  // rank of the bound that tau is taken at
   unsigned* hist;
   const unsigned* maxes;  // n2, n1, eta maxima of A, then (+4) of B
   int screen;      // 1: no error margin (screening by the computed value)
@@ -184,6 +185,49 @@ __device__ __forceinline__ float margin_max(const GemmArgs& g) {
   return pair_margin(g.kappa, g.onepu, g.d_f, a, b) * (1.0f + 1e-5f);
 }
 
+// Pass A, all 256 threads: hands the workgroup's counts (`hist`, in LDS) over
+// and returns `pre`: |c| below it reaches neither the bound that g.target of
+// all counts so far lie above nor, with its margin, the final tau.  (A bound
+// from the workgroup's own values alone stays far below the final one: nearly
+// every 64 x 32 block then held a value above it, 2.4 ms instead of 1.0 at
+// 1563 x 1e6 x 256 in bf16; no bound, two LDS atomics a pair: 60.5 ms instead
+// of 39.9 at 15,625 x 1e6 x 512.)
+__device__ __forceinline__ float raise_bound(const GemmArgs& g,
+                                             const BoundBins& bins,
+                                             float mg_max, unsigned* hist,
+                                             unsigned* thr) {
+  const int t = threadIdx.x, lane = t & 63;
+  __syncthreads();
+  for (int b = t; b < 2048; b += 256)
+    if (hist[b]) atomicAdd(&g.hist[b], hist[b]);
+  // a count read too early only leaves the bound lower
+  for (int b = t; b < 2048; b += 256)
+    hist[b] = __hip_atomic_load(&g.hist[b], __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_AGENT);
+  __syncthreads();
+  if (t < 64) {
+    const int per = bins.count() / 64;
+    const int hi = bins.count() - 1 - per * lane;
+    unsigned sum = 0;
+    for (int b = hi; b > hi - per; --b) sum += hist[b];
+    const unsigned incl = wave_incl_scan(sum);
+    const uint64_t reach = __ballot((int64_t)incl >= g.target);
+    if (reach && lane == __builtin_ctzll(reach)) {
+      unsigned acc = incl - sum;
+      int b = hi;
+      for (; b > hi - per + 1; --b) {
+        acc += hist[b];
+        if ((int64_t)acc >= g.target) break;
+      }
+      *thr = bins.edge(b);
+    }
+  }
+  __syncthreads();
+  for (int b = t; b < 2048; b += 256) hist[b] = 0;
+  __syncthreads();
+  return __uint_as_float(*thr) - mg_max;
+}
+
 // E8M0 byte of a vector's power-of-two inverse scale (the MFMA multiplies
 // the products of a lane's 32-element K block by 2^(byte - 127) per operand)
 __device__ __forceinline__ int e8m0_of(float inv_s) {
@@ -198,7 +242,6 @@ struct PanelArgs {
   int64_t panels;    // row panels
   int64_t seg;       // column tiles per work item
   int64_t items;     // panels x segments
-  int64_t target;    // pass A: rank of the bound that tau is taken at
   const int* sb;     // fp8: E8M0 bytes of B's vectors (padded rows too)
 };
 
@@ -210,7 +253,7 @@ int64_t panel_bytes(int prec, int64_t d, int64_t rows);
 hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
                          void* out, VecInfo* info, int* scale, hipStream_t st);
 hipError_t launch_panel(const GemmArgs& a, int prec, int64_t d, bool hist,
-                        int64_t target, const int* sb, hipStream_t st);
+                        const int* sb, hipStream_t st);
 // per-precision launches (one file each); grid 0: as many workgroups as fit
 hipError_t launch_panel_f32(const PanelArgs& a, int ns, bool hist,
                             int64_t grid, hipStream_t st);

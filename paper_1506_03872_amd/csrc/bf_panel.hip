@@ -126,11 +126,10 @@ hipError_t panel_prepare(const float* X, int64_t rows, int64_t d, int prec,
 }
 
 hipError_t launch_panel(const GemmArgs& g, int prec, int64_t d, bool hist,
-                        int64_t target, const int* sb, hipStream_t st) {
+                        const int* sb, hipStream_t st) {
   PanelArgs a;
   a.g = g;
   a.sb = sb;
-  a.target = target;
   // MAD_BF_GRID overrides the workgroup count, a multiple of 8 (one share
   // per XCD); the result is the same
   int64_t grid = 0;

@@ -119,7 +119,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
   }
   // |c| below `pre` is dropped at once: |c| + margin does not reach tau (pass
   // B; 1 - 2^-20 absorbs the roundings of the comparisons), or the bound
-  // that `target` lower bounds counted so far lie above (pass A)
+  // that g.target lower bounds counted so far lie above (pass A)
   const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
   const float mg_max = HIST ? margin_max(g) : g.mg_max;
   float pre = HIST ? -mg_max : fmaf(tau, 1.0f - 0x1p-20f, -mg_max);
@@ -265,42 +265,6 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       }
     }
   };
-  // pass A: hand this workgroup's counts over, and take the bound that
-  // `target` of all counts so far lie above.  (A bound from the workgroup's
-  // own values alone stays far below the final one: nearly every 64 x 32
-  // block then held a value above it, 2.4 ms instead of 1.0 at 1563 x 1e6 x
-  // 256 in bf16.)
-  auto raise = [&]() {
-    __syncthreads();
-    for (int b = t; b < 2048; b += 256)
-      if (hist[b]) atomicAdd(&g.hist[b], hist[b]);
-    // a count read too early only leaves the bound lower
-    for (int b = t; b < 2048; b += 256)
-      hist[b] = __hip_atomic_load(&g.hist[b], __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
-    if (wv == 0) {
-      const int per = bins.count() / 64;
-      const int hi = bins.count() - 1 - per * lane;
-      unsigned sum = 0;
-      for (int b = hi; b > hi - per; --b) sum += hist[b];
-      const unsigned incl = wave_incl_scan(sum);
-      const uint64_t reach = __ballot((int64_t)incl >= a.target);
-      if (reach && lane == __builtin_ctzll(reach)) {
-        unsigned acc = incl - sum;
-        int b = hi;
-        for (; b > hi - per + 1; --b) {
-          acc += hist[b];
-          if ((int64_t)acc >= a.target) break;
-        }
-        thr_s = bins.edge(b);
-      }
-    }
-    __syncthreads();
-    for (int b = t; b < 2048; b += 256) hist[b] = 0;
-    __syncthreads();
-    pre = __uint_as_float(thr_s) - mg_max;
-  };
   if (item < hi) {
     locate(item);
     fetch(tile, buf0, sc0);
@@ -330,7 +294,8 @@ __global__ __launch_bounds__(256, 2) void k_gemm_panel(PanelArgs a) {
       if (more) fetch(ntile, oth, ioth);
       compute(cur, icur, tl);
       ++done;
-      if (HIST && (done & (done - 1)) == 0) raise();
+      if (HIST && (done & (done - 1)) == 0)
+        pre = raise_bound(g, bins, mg_max, hist, &thr_s);
       if (more) {
         tile = ntile;
         tend = nend;

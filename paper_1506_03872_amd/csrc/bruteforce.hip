@@ -147,10 +147,12 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
   __shared__ __attribute__((aligned(16))) char lds_a[2][kBM * kLdsStride];
   __shared__ __attribute__((aligned(16))) char lds_b[2][kBN * kLdsStride];
   __shared__ unsigned hist[HIST ? 2048 : 1];
+  __shared__ unsigned thr_s;
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int wr = wv >> 1, wc = wv & 1;
   if (HIST) {
     for (int b = t; b < 2048; b += 256) hist[b] = 0;
+    if (t == 0) thr_s = 0u;
     __syncthreads();
   }
   const int64_t tiles_m = (g.m_rows + kBM - 1) / kBM;
@@ -163,6 +165,12 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
   const float tau = HIST ? 0.0f : __uint_as_float(*g.tau_bits);
   BoundBins bins{-1};
   if (HIST) bins = bound_bins(g.maxes, g.coarse);
+  // |c| below `pre` is dropped at once: |c| + margin does not reach tau (pass
+  // B; 1 - 2^-20 absorbs the roundings of the comparisons), or the bound that
+  // g.target lower bounds counted so far lie above (pass A)
+  const float mg_max = HIST ? margin_max(g) : g.mg_max;
+  float pre = HIST ? -mg_max : fmaf(tau, 1.0f - 0x1p-20f, -mg_max);
+  unsigned done = 0;
   const int64_t G = gridDim.x;  // a multiple of 8
   const int64_t v = (int64_t)(blockIdx.x & 7) * (G >> 3) + (blockIdx.x >> 3);
   // this thread's 4 x 16 bytes of each operand's stage: rows (t >> 3) +
@@ -306,24 +314,18 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
       __syncthreads();
       cur ^= 1;
     }
-    // epilogue.  Pass B: |c| + margin >= tau only when |c| >= tau - mg_max,
-    // which almost no pair meets; those few compute the exact margin.
+    // epilogue: one max over the lane's 64 values first; the per-element
+    // work below, with the exact margin, runs only in waves where some lane
+    // reaches `pre`, which almost no pair does
     const int cl = lane & 31, rg = lane >> 5;
-    // tau (1 - 2^-20) - mg_max absorbs the roundings of both comparisons
-    const float pre = HIST ? 0.0f : fmaf(tau, 1.0f - 0x1p-20f, -g.mg_max);
-    // pass B: one max over the lane's 64 values first; the per-element
-    // work below runs only in waves where some lane passes
-    bool any = true;
-    if (!HIST) {
-      float mx = 0.0f;
+    float mx = 0.0f;
 #pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
+    for (int bi = 0; bi < 2; ++bi)
 #pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
+      for (int bj = 0; bj < 2; ++bj)
 #pragma unroll
-          for (int e = 0; e < 16; ++e) mx = fmaxf(mx, fabsf(acc[bi][bj][e]));
-      any = mx >= pre;
-    }
+        for (int e = 0; e < 16; ++e) mx = fmaxf(mx, fabsf(acc[bi][bj][e]));
+    const bool any = mx >= pre;
     if (any) {
 #pragma unroll
     for (int bj = 0; bj < 2; ++bj) {
@@ -336,7 +338,7 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
           const int64_t i = i0 + wr * 64 + bi * 32 + 8 * (e >> 2) + 4 * rg +
                             (e & 3);
           const float c = acc[bi][bj][e];
-          if (!HIST && !(fabsf(c) >= pre)) continue;
+          if (!(fabsf(c) >= pre)) continue;
           if (!(jok && i < g.m_rows)) continue;
           const VecInfo va = g.ia[i * g.a_stride_rows];
           const VecInfo vb = g.ib[j];
@@ -356,6 +358,9 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
       }
     }
     }
+    ++done;
+    if (HIST && (done & (done - 1)) == 0)
+      pre = raise_bound(g, bins, mg_max, hist, &thr_s);
     tile = next;
     i0 = ni0;
     j0 = nj0;
@@ -418,10 +423,11 @@ __global__ __launch_bounds__(1024) void k_vecinfo_max(const VecInfo* va,
 // are positive), and est = the subset's pairs that pass B's filter will
 // keep: those whose upper bound (screening: value) reaches that bin.  (One
 // thread walking the 2048 bins took 54 us.)
-__global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g, int64_t t,
+__global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g,
                                                unsigned* tau_bits,
                                                unsigned long long* est) {
   const int lane = threadIdx.x;
+  const int64_t t = g.target;
   const BoundBins bins = bound_bins(g.maxes, g.coarse);
   // lane l: `per` bins from the top
   const int per = bins.count() / 64;
@@ -625,20 +631,18 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   a.ckey = nullptr;
   a.ccap = 0;
   a.ccount = ccount;
-  auto gemm = [&](bool hist_pass, int64_t target) -> hipError_t {
-    if (panel)
-      return launch_panel(a, prec, d, hist_pass, target, eb8, st);
+  auto gemm = [&](bool hist_pass) -> hipError_t {
+    if (panel) return launch_panel(a, prec, d, hist_pass, eb8, st);
     if (prec == kF32) launch_gemm<kF32>(a, hist_pass, st);
     else if (prec == kBF16) launch_gemm<kBF16>(a, hist_pass, st);
     else launch_gemm<kFP8>(a, hist_pass, st);
     return hipGetLastError();
   };
   // pass A's subset holds about 1/stride of the pairs
-  const int64_t target = screen ? (cap_hint + stride - 1) / stride : t;
+  a.target = screen ? (cap_hint + stride - 1) / stride : t;
   auto pass_a = [&]() -> hipError_t {
-    const hipError_t r = gemm(true, target);
-    if (r == hipSuccess)
-      k_bf_tau<<<1, 64, 0, st>>>(a, target, tau_bits, est);
+    const hipError_t r = gemm(true);
+    if (r == hipSuccess) k_bf_tau<<<1, 64, 0, st>>>(a, tau_bits, est);
     return r;
   };
   if (tau_user >= 0.0f) {
@@ -711,7 +715,7 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
     a.ccap = cap;
     if ((e = launch_fill_u64((uint64_t*)ccount, 1, 0ull, st)) != hipSuccess)
       break;
-    if ((e = gemm(false, 0)) != hipSuccess) break;
+    if ((e = gemm(false)) != hipSuccess) break;
     if ((e = hipMemcpyAsync(&count, ccount, 8, hipMemcpyDeviceToHost, st)) !=
         hipSuccess) break;
     if ((e = hipStreamSynchronize(st)) != hipSuccess) break;
