@@ -110,13 +110,14 @@ __global__ __launch_bounds__(256) void k_wedge_hist(const uint32_t* dA,
 
 // The cut: of the bins that leave at most kMaxLightWedges light wedges and
 // 1 to kMaxHeavy heavy coordinates, the one with the least expected time,
-// col_ns per column of the dense product (the heavy coordinates, padded to a
-// K step of the GEMM that takes them) and wedge_ns per light wedge.  Between
-// cuts of one padded width the deepest wins, so that no column is left to
-// padding.  cut = -1 when there is none (or no wedge at all).
+// the column times of `pad` (the heavy coordinates, padded to a K step of the
+// GEMM that takes them) and wedge_ns per light wedge.  Between cuts of one
+// padded width the deepest wins, so that no column is left to padding.  cut =
+// -1 when there is none (or no wedge at all).
 struct ColumnPad {
   int panel, panel_step;  // widest K of the register-panel GEMM, its K step
   int step;               // K step of the GEMM for longer vectors
+  double panel_ns, ns;    // time of a column in each
 };
 
 struct SplitCut {
@@ -125,7 +126,6 @@ struct SplitCut {
 };
 
 __global__ __launch_bounds__(256) void k_split_cut(const SplitHist* h,
-                                                   double col_ns,
                                                    double wedge_ns,
                                                    ColumnPad pad,
                                                    SplitCut* out) {
@@ -163,9 +163,10 @@ __global__ __launch_bounds__(256) void k_split_cut(const SplitHist* h,
     if (light > (unsigned long long)kMaxLightWedges ||
         hc > (unsigned long long)kMaxHeavy)
       continue;
-    const unsigned long long step =
-        hc <= (unsigned long long)pad.panel ? pad.panel_step : pad.step;
-    const double cost = col_ns * (double)((hc + step - 1) / step * step) +
+    const bool panel = hc <= (unsigned long long)pad.panel;
+    const unsigned long long step = panel ? pad.panel_step : pad.step;
+    const double cost = (panel ? pad.panel_ns : pad.ns) *
+                            (double)((hc + step - 1) / step * step) +
                         wedge_ns * (double)light;
     if (cost < best[t]) {
       best[t] = cost;
@@ -407,19 +408,28 @@ struct ExactWork {
 };
 static ExactWork g_ex;
 
-// expected times of the split's two parts: a column of the dense product
-// (2 m n flops at the rates measured for the filter GEMM at K = 64 to 256)
-// and a light wedge (listed, summed and pruned: 70 ps at 4e7 wedges)
-static double split_col_ns(int prec, int64_t m, int64_t n) {
-  const double flops = prec == 0 ? 1.1e14 : prec == 1 ? 1.0e15 : 2.0e15;
-  return 2.0 * (double)m * (double)n / flops * 1e9;
+// expected times of the split's two parts: a column of the dense product (2 m
+// n flops) at the rates measured for the heavy part on each side of the widest
+// panel kernel's K, and a light wedge (listed, summed and pruned: 47 to 50 ps
+// at 1e7 to 5e8 wedges).  At 3e5 x 3e5: bf16 256 columns 28 ms (1.6e15), 320
+// 95 (0.61e15) and 768 192 (0.72e15), at 1e5 x 1e5 4.0 (1.3e15), 9.5 and
+// 23.5; fp32 0.14e15 and 0.13e15.  In fp8 the certified margins let whole
+// tiles through, and only what a column adds counts: 108 ms with 256 columns,
+// 160 with 512 (0.89e15), 222 with 640.
+static void split_col_ns(int prec, int64_t m, int64_t n, double* panel,
+                         double* longer) {
+  const double mn = 2.0 * (double)m * (double)n * 1e9;
+  *panel = mn / (prec == 0 ? 1.4e14 : prec == 1 ? 1.3e15 : 0.9e15);
+  *longer = mn / (prec == 0 ? 1.3e14 : prec == 1 ? 0.65e15 : 0.8e15);
 }
-constexpr double kWedgeNs = 0.07;
+constexpr double kWedgeNs = 0.05;
 
-static ColumnPad column_pad(int prec) {
-  return prec == 0   ? ColumnPad{256, 8, 32}
-         : prec == 1 ? ColumnPad{256, 16, 64}
-                     : ColumnPad{512, 64, 128};
+static ColumnPad column_pad(int prec, int64_t m, int64_t n) {
+  ColumnPad p = prec == 0   ? ColumnPad{256, 8, 32}
+                : prec == 1 ? ColumnPad{256, 16, 64}
+                            : ColumnPad{512, 64, 128};
+  split_col_ns(prec, m, n, &p.panel_ns, &p.ns);
+  return p;
 }
 
 // device_split: cut the coordinates on the device at the least expected
@@ -498,8 +508,8 @@ static hipError_t topk_csr_run(const CsrView& in, int64_t m, int64_t n,
     int64_t* tot = (int64_t*)((char*)cut + 64);
     int64_t* part = tot + 16;
     k_wedge_hist<<<grid_of(d, 256 * 8, 256), 256, 0, st>>>(dA, dB, d, hist);
-    k_split_cut<<<1, 256, 0, st>>>(hist, split_col_ns(prec, m, n), kWedgeNs,
-                                   column_pad(prec), cut);
+    k_split_cut<<<1, 256, 0, st>>>(hist, kWedgeNs, column_pad(prec, m, n),
+                                   cut);
     k_split_count<<<(unsigned)tiles, 256, 0, st>>>(dA, dB, d, cut, part);
     if ((e = launch_scan_parts(part, tiles, kSplitVals, tot, st)) !=
         hipSuccess)
