@@ -416,9 +416,10 @@ int mips_get_table_factor(mad_plan* plan, int* slots_per_key);
 int mips_set_table_factor(mad_plan* plan, int slots_per_key);
 
 /* Autotuner: runs the batch (arguments as mips_topk_batch) under a set of
- * launch shapes and table factors, `reps` timed replays each, keeps the
- * fastest in the plan and reports its time per batch in *best_ms (host,
- * optional).  Results are identical under every shape.  Synchronises.
+ * launch shapes and, when a query has more than 2^18 samples, longer chunks
+ * and table factors, `reps` timed replays each, keeps the fastest in the
+ * plan and reports its time per batch in *best_ms (host, optional).  Results
+ * are identical under every shape.  Synchronises.
  * With a choice file (mips_autotune_cache), a batch whose signature (the
  * device's architecture, m, d, nq, the sum and largest of the s_q, the
  * sum of the t'_q, t and the verification precision) is in the file takes

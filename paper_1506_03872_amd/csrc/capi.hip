@@ -1879,16 +1879,24 @@ int mips_autotune(mad_plan* p, const float* Q, int64_t nq,
     }
     return MAD_OK;
   };
-  // chunk and unroll at the default grid and table factor, then the grid,
-  // then the table factor
+  // Chunk and unroll at the default grid and table factor, then the grid,
+  // then the table factor.  Queries summed in LDS take their samples in units
+  // of the chunk, at most kMipsUnit, and have no table: longer chunks and the
+  // factors are tried only when a query has a table in memory.
+  bool in_memory = false;
+  for (int64_t q = 0; q < nq; ++q)
+    in_memory = in_memory || s_per_query[q] > mad::kMaxPartBudget;
   const int f0 = ms->slots;
-  for (int c : chunks)
+  for (int c : chunks) {
+    if (c > mad::kMipsUnit && !in_memory) continue;
     for (int u : unrolls)
       if ((rc = trial(c, u, 2048, f0)) != MAD_OK) break;
+    if (rc != MAD_OK) break;
+  }
   if (rc == MAD_OK)
     for (int g : grids)
       if (g != 2048 && (rc = trial(bc, bu, g, f0)) != MAD_OK) break;
-  if (rc == MAD_OK)
+  if (rc == MAD_OK && in_memory)
     for (int f : factors)
       if (f != f0 && (rc = trial(bc, bu, bg, f)) != MAD_OK) break;
   (void)hipEventDestroy(e0);
