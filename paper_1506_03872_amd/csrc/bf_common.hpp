@@ -191,7 +191,7 @@ __device__ __forceinline__ float margin_max(const GemmArgs& g) {
 // from the workgroup's own values alone stays far below the final one: nearly
 // every 64 x 32 block then held a value above it, 2.4 ms instead of 1.0 at
 // 1563 x 1e6 x 256 in bf16; no bound, two LDS atomics a pair: 60.5 ms instead
-// of 39.9 at 15,625 x 1e6 x 512.)
+// of 28.3 at 15,625 x 1e6 x 512.)
 __device__ __forceinline__ float raise_bound(const GemmArgs& g,
                                              const BoundBins& bins,
                                              float mg_max, unsigned* hist,

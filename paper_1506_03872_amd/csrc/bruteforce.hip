@@ -141,18 +141,23 @@ __device__ __forceinline__ void gemm_coords(int64_t tile, int64_t tiles_m,
 // EARLY: the next stage's loads are issued ahead of the current stage's
 // MFMAs (pays with at most four stages per tile; with longer K the loads
 // issued after the MFMAs measured faster)
+// (fp8's pass A would take 268 registers, and a CU then one workgroup.)
 template <int P, bool HIST, bool EARLY>
-__global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
+__global__ __launch_bounds__(256, P == kFP8 ? 2 : 1) void k_gemm_topk(
+    GemmArgs g) {
   using PT = PrecT<P>;
   __shared__ __attribute__((aligned(16))) char lds_a[2][kBM * kLdsStride];
   __shared__ __attribute__((aligned(16))) char lds_b[2][kBN * kLdsStride];
   __shared__ unsigned hist[HIST ? 2048 : 1];
-  __shared__ unsigned thr_s;
+  // the running bound is kept in the padding of a row: the 80 KB of the
+  // others are half of a CU's LDS, and four bytes more would leave it one
+  // workgroup (pass A at 1024 x 65,536 x 1024 in fp32: 1.60 ms, 2.09 then)
+  unsigned* thr = (unsigned*)(lds_a[0] + kRowBytes);
   const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
   const int wr = wv >> 1, wc = wv & 1;
   if (HIST) {
     for (int b = t; b < 2048; b += 256) hist[b] = 0;
-    if (t == 0) thr_s = 0u;
+    if (t == 0) *thr = 0u;
     __syncthreads();
   }
   const int64_t tiles_m = (g.m_rows + kBM - 1) / kBM;
@@ -338,7 +343,9 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
           const int64_t i = i0 + wr * 64 + bi * 32 + 8 * (e >> 2) + 4 * rg +
                             (e & 3);
           const float c = acc[bi][bj][e];
-          if (!(fabsf(c) >= pre)) continue;
+          // (pass A counts the others of the lane as well: they do no harm,
+          // and a test of each takes longer)
+          if (!HIST && !(fabsf(c) >= pre)) continue;
           if (!(jok && i < g.m_rows)) continue;
           const VecInfo va = g.ia[i * g.a_stride_rows];
           const VecInfo vb = g.ib[j];
@@ -358,9 +365,15 @@ __global__ __launch_bounds__(256) void k_gemm_topk(GemmArgs g) {
       }
     }
     }
+    // after 16, 64, 256, ... tiles while 16 or more are left: a raise takes
+    // as long as the bound saves in five to ten tiles, and an early bound
+    // saves little (pass A at 3125 x 2e5 x 512 in bf16, 76 tiles a workgroup:
+    // 2.25 ms, 2.49 with raises after 1 and 4 too; at 1024 x 65,536 x 257,
+    // eight tiles, 0.30 and 0.38)
     ++done;
-    if (HIST && (done & (done - 1)) == 0)
-      pre = raise_bound(g, bins, mg_max, hist, &thr_s);
+    if (HIST && (done & (done - 1)) == 0 && (done & 0x55555550u) &&
+        ntiles - tile > 16 * G)
+      pre = raise_bound(g, bins, mg_max, hist, thr);
     tile = next;
     i0 = ni0;
     j0 = nj0;

@@ -1,7 +1,7 @@
 """GPU checks of the running bound of the brute force's first pass: vectors
 longer than the register-panel GEMM takes (and, beside them, of its own
-lengths), with up to 16 tiles a workgroup, so that values are dropped by the
-bound before the histogram is whole.  Small integers: every product sum is
+lengths), with 127 tiles a workgroup where the launch has 64 of them, so that
+values are dropped by the bound before the histogram is whole.  Small integers: every product sum is
 exact, and the answers must be equal to the exhaustive ones."""
 import numpy as np
 import pytest
@@ -11,12 +11,16 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("prec,d", [(0, 257), (0, 40), (1, 270), (1, 256),
                                     (2, 520), (2, 512)])
-@pytest.mark.parametrize("m,n,t", [(1000, 130_001, 500), (130, 70_000, 1),
-                                   (9000, 20_000, 3000)])
-def test_answers_and_threshold(gpu, prec, d, m, n, t):
+@pytest.mark.parametrize("m,n,t,grid", [(1000, 130_001, 500, None),
+                                        (1000, 130_001, 500, "64"),
+                                        (130, 70_000, 1, "8"),
+                                        (9000, 20_000, 3000, None)])
+def test_answers_and_threshold(gpu, monkeypatch, prec, d, m, n, t, grid):
     import torch
 
     import paper_1506_03872_amd as mad
+    if grid:
+        monkeypatch.setenv("MAD_BF_GRID", grid)
     g = torch.Generator(device="cuda")
     g.manual_seed(d + m)
 
