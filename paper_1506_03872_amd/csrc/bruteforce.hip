@@ -138,11 +138,11 @@ __device__ __forceinline__ void gemm_coords(int64_t tile, int64_t tiles_m,
   j0 = (within / band_rows) * kBN;
 }
 
-// EARLY: the next stage's loads are issued ahead of the current stage's
-// MFMAs (pays with at most four stages per tile; with longer K the loads
-// issued after the MFMAs measured faster)
+// (Each stage's loads go where the compiler puts them, after the stage before
+// has issued its MFMAs: kept ahead of them they were slower at K = 512, 1.71
+// to 1.77 s against 1.44 to 1.59 at 1e6 x 1e6 in bf16.)
 // (fp8's pass A would take 268 registers, and a CU then one workgroup.)
-template <int P, bool HIST, bool EARLY>
+template <int P, bool HIST>
 __global__ __launch_bounds__(256, P == kFP8 ? 2 : 1) void k_gemm_topk(
     GemmArgs g) {
   using PT = PrecT<P>;
@@ -267,14 +267,6 @@ __global__ __launch_bounds__(256, P == kFP8 ? 2 : 1) void k_gemm_topk(
     // the tile's first MFMAs start from a zero C operand (no per-tile
     // clearing of the 64 accumulators); a tile always has a stage (Kp >= 1)
     f16v acc[2][2];
-    if (nst == 0) {
-#pragma unroll
-      for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 2; ++bj)
-#pragma unroll
-          for (int e = 0; e < 16; ++e) acc[bi][bj][e] = 0.0f;
-    }
     int cur = 0;
     for (int64_t st = 0; st < nst; ++st) {
       // the next stage, else the next tile's first, else (last tile) a
@@ -292,10 +284,6 @@ __global__ __launch_bounds__(256, P == kFP8 ? 2 : 1) void k_gemm_topk(
       } else {
         MAD_BF_GLOAD(li0, lj0, lkb)
       }
-      // keep the loads issued here, ahead of the MFMAs: without this the
-      // compiler sinks them into the LDS store below, behind the stage's
-      // MFMAs, and the stage then waits out a full memory latency
-      if constexpr (EARLY) asm volatile("" ::: "memory");
       const char* la = lds_a[cur] + (wr * 64) * kLdsStride;
       const char* lb = lds_b[cur] + (wc * 64) * kLdsStride;
       // the next K step's operands are read from LDS while the current
@@ -475,10 +463,6 @@ __global__ __launch_bounds__(64) void k_bf_tau(GemmArgs g,
 // ---------------------------------------------------------------------------
 struct BfWork {
   DeviceBuffer ac, bc, ia, ib, e8, misc, keys, vals, sel, selbuf, fin;
-  int64_t m = 0, n = 0, d = 0;
-  int prec = -1;
-  const float* A = nullptr;
-  const float* B = nullptr;
 };
 
 static BfWork g_bf;  // process-wide cache of the conversion workspace
@@ -500,15 +484,10 @@ static void launch_gemm(const GemmArgs& a, bool hist, hipStream_t st) {
   }
   if (grid < 8) grid = 8;
 
-  // early loads for tiles of at most four K stages (128-byte slices)
-  const bool early = a.Kp * PrecT<P>::EB <= 4 * kRowBytes;
-  if (hist) {
-    if (early) k_gemm_topk<P, true, true><<<(unsigned)grid, 256, 0, st>>>(a);
-    else k_gemm_topk<P, true, false><<<(unsigned)grid, 256, 0, st>>>(a);
-  } else {
-    if (early) k_gemm_topk<P, false, true><<<(unsigned)grid, 256, 0, st>>>(a);
-    else k_gemm_topk<P, false, false><<<(unsigned)grid, 256, 0, st>>>(a);
-  }
+  if (hist)
+    k_gemm_topk<P, true><<<(unsigned)grid, 256, 0, st>>>(a);
+  else
+    k_gemm_topk<P, false><<<(unsigned)grid, 256, 0, st>>>(a);
 }
 
 hipError_t lowp_prepare(const float* X, int64_t rows, int64_t d, int prec,
@@ -565,8 +544,6 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   const size_t bbytes = panel ? (size_t)panel_bytes(prec, d, n)
                               : (size_t)n * Kp * EB;
   BfWork& w = g_bf;
-  const bool fresh = w.m != m || w.n != n || w.d != d || w.prec != prec ||
-                     w.A != A || w.B != B;
   if ((e = dev_alloc(w.ac, abytes)) != hipSuccess) return e;
   if ((e = dev_alloc(w.bc, bbytes)) != hipSuccess) return e;
   // E8M0 scales of both sides' vectors (fp8 panels), padded rows too
@@ -579,8 +556,6 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   if ((e = dev_alloc(w.ia, (size_t)m * sizeof(VecInfo))) != hipSuccess) return e;
   if ((e = dev_alloc(w.ib, (size_t)n * sizeof(VecInfo))) != hipSuccess) return e;
   if ((e = dev_alloc(w.misc, 2048 * 4 + 512)) != hipSuccess) return e;
-  (void)fresh;
-  w.m = m; w.n = n; w.d = d; w.prec = prec; w.A = A; w.B = B;
   hipEvent_t ev[4];
   for (auto& x : ev) (void)hipEventCreate(&x);
   (void)hipEventRecord(ev[0], st);

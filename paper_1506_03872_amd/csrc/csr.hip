@@ -497,10 +497,6 @@ __device__ __forceinline__ void zero_entries(void* et, int esz, int64_t r0,
   }
 }
 
-__device__ __forceinline__ int spl_of(int L) {
-  return L <= 6 ? 1 : (L == 7 ? 2 : (L == 8 ? 4 : 8));
-}
-
 // ---------------------------------------------------------------------------
 // tables of 65 to 512 items, one wave per table of one slots-per-lane
 // class (every wave of the block runs every step: the block synchronises):
