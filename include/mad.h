@@ -390,11 +390,13 @@ int mips_plan_create(const float* A, int64_t m, int64_t d, uint32_t flags,
  * 4096 samples, each ordered by a hash of i, and one that sums each bin in
  * LDS; for larger ones the clearing of a score table in memory and a
  * persistent sampling launch over chunks; one postprocessing launch with a
- * workgroup per query) are captured once into a HIP graph, which later calls with the
- * same Q, out, n_out, seed and budgets replay on `stream`.  A new budget
- * vector re-plans the batch (host work, uploads and allocation: the call
- * then synchronises).  With MAD_FLAG_TIMING the launches run directly,
- * with phase events read by mad_plan_phase_ms.
+ * workgroup per query) are captured once into a HIP graph, which later calls
+ * with the same Q, out, n_out, seed and budgets replay on `stream`.  Where
+ * the budgets are several times m, the LDS-summed queries go through their
+ * two launches in groups, so that the workspace follows nq min(s_q, m) and
+ * not the samples.  A new budget vector re-plans the batch (host work,
+ * uploads and allocation: the call then synchronises).  With MAD_FLAG_TIMING
+ * the launches run directly, with phase events read by mad_plan_phase_ms.
  * ------------------------------------------------------------------------- */
 int mips_topk_batch(mad_plan* plan, const float* Q, int64_t nq,
                     const int64_t* s_per_query, const int64_t* tprime_per_query,
@@ -408,10 +410,10 @@ int mips_get_config(mad_plan* plan, int* chunk, int* unroll, int* grid);
 int mips_set_config(mad_plan* plan, int chunk, int unroll, int grid);
 
 /* Score-table slots per possible key of a query of more than 2^18 samples
- * (2, 4 or 8; default 2): query q's open-addressing table in memory holds factor * max(min(s_q, m), 512)
- * slots rounded up to a power of two.  A larger table passes fewer taken
- * slots per insert but takes longer to clear and to scan; results never
- * change.  A new factor re-plans the next batch. */
+ * (2, 4 or 8; default 2): query q's open-addressing table in memory holds
+ * factor * max(min(s_q, m), 512) slots rounded up to a power of two.  A
+ * larger table passes fewer taken slots per insert but takes longer to clear
+ * and to scan; results never change.  A new factor re-plans the next batch. */
 int mips_get_table_factor(mad_plan* plan, int* slots_per_key);
 int mips_set_table_factor(mad_plan* plan, int slots_per_key);
 

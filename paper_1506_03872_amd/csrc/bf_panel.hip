@@ -28,11 +28,12 @@ int64_t panel_bytes(int prec, int64_t d, int64_t rows) {
 // from 32 b, at ((b NS + s) 64 + l) 16: vector 32 b + r, coordinates 16 s +
 // 8 g + 0..7 (bf16), 64 (s / 2) + 32 g + 16 (s % 2) + 0..15 (fp8) or 8 s + 4
 // g + 0..3 (fp32), which is the MFMA operand of that lane (fp32: its q-th
-// MFMA takes coordinates 8 s + q and 8 s + 4 + q).  A workgroup takes 32 vectors: it reads
-// them into LDS, 8 lanes sum each one's norms, and every thread converts
-// 16-byte pieces in the order they are stored.  Vectors past the last are
-// zeros.  (A wave per vector for the norms, as in k_prep, spends its time
-// in 18 dependent shuffles a vector: 47 us against 21 at 1e5 x 100 in fp8.)
+// MFMA takes coordinates 8 s + q and 8 s + 4 + q).  A workgroup takes 32
+// vectors: it reads them into LDS, 8 lanes sum each one's norms, and every
+// thread converts 16-byte pieces in the order they are stored.  Vectors past
+// the last are zeros.  (A wave per vector for the norms, as in k_prep, spends
+// its time in 18 dependent shuffles a vector: 47 us against 21 at 1e5 x 100 in
+// fp8.)
 template <int P>
 __global__ __launch_bounds__(256) void k_prep_panel(const float* X,
                                                     int64_t rows, int d,

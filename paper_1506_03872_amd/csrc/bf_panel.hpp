@@ -349,8 +349,9 @@ hipError_t launch_panel_one(PanelArgs a, int64_t grid, hipStream_t st) {
   // takes about 2.5 us, a tile its MFMAs' cycles on the SIMDs it shares.
   // (Items of one tile, which the fewest rounds lose least by when each
   // workgroup has a dozen tiles, spend most of their time on the rows: pass
-  // A at 1018 x 71567 x 150 in fp32 530 us, 258 by this rule.)  Up to 4096 columns:
-  // the workgroups of an XCD stream the same columns, 2 MB at K = 256.
+  // A at 1018 x 71567 x 150 in fp32 530 us, 258 by this rule.)  Up to 4096
+  // columns: the workgroups of an XCD stream the same columns, 2 MB at K =
+  // 256.
   constexpr int cycles =
       panel_row_blocks(NS) * TB *
       (P == kF32 ? NS * 4 * 64 : P == kFP8 ? NS / 2 * 64 : NS * 32);

@@ -4,10 +4,11 @@
 // keeps a priority queue; here the GEMM epilogue filters against a bound).
 //
 //   pass A  GEMM over every 64th row of A; the epilogue histograms the lower
-//           bounds |c^| - margin(i,j) of the computed values (2048 monotone
-//           bins).  The lower edge tau of the bin holding the t-th largest
+//           bounds |c^| - margin(i,j) of the computed values and their upper
+//           bounds (1024 monotone bins each; screening: the values, 2048).
+//           The lower edge tau of the bin holding the t-th largest lower
 //           bound is <= the t-th largest |c| over all pairs, and the count of
-//           the bins that may reach tau sizes pass B's list.
+//           the upper bounds that may reach tau sizes pass B's list.
 //   pass B  GEMM over all pairs; the epilogue appends every pair with
 //           |c^| + margin(i,j) >= tau.  That set holds every pair of the
 //           exact top t.
@@ -680,8 +681,9 @@ hipError_t bruteforce_run(const float* A, int64_t m, const float* B,
   // room for what pass A's subset (1 / stride of the rows) lets expect, a
   // quarter and four standard deviations over it: a list that overflows
   // costs the whole GEMM again (1e5 x 1e6 x 256 in bf16, t = 1000: 153.8
-  // ms a call with two runs, 70.6 with one).  Above 2^26 pairs the estimate is not followed: the first
-  // run counts the pairs exactly before that much memory is taken.
+  // ms a call with two runs, 70.6 with one).  Above 2^26 pairs the estimate
+  // is not followed: the first run counts the pairs exactly before that much
+  // memory is taken.
   const double want = ((double)sub * 1.25 + 4.0 * sqrt((double)sub)) *
                           (double)stride + 1024.0;
   if (want > (double)cap && want <= (double)(int64_t(1) << 26))

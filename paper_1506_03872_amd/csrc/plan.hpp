@@ -216,8 +216,8 @@ constexpr uint64_t kSlotMask = (1ull << 56) - 1;
 // Tables of different sizes: table s covers item positions [off[s],
 // off[s+1]) and 2^L_s slots from meta[s] & kSlotMask (L_s = meta[s] >> 56).
 // Tables of more than 512 items ("big", 2^L >= 1024 slots) come first, in
-// index order, then the others in index order.  The host plans the layout;
-// device arrays are reused across rebuilds while they are large enough.
+// index order, then the others in index order.  The layout is made on the
+// device; its arrays are reused across rebuilds while they are large enough.
 struct Ragged {
   int64_t S = 0;
   int64_t slots = 0, big_slots = 0, nbig = 0, runs = 0, edges = 0;
@@ -299,18 +299,18 @@ struct CsrTables {
   double* at_w = nullptr;     // nnzA: T1 weights |a_ki| na_i of this build
 };
 
-// Allocates and builds every table (synchronises: the layout of the
-// sparse tables is planned on the host).  Returns hipErrorInvalidValue when
-// the inputs are malformed or hold NaN/Inf, with t.bad set.
+// Allocates and builds every table (synchronises: the host sizes the arrays
+// by the totals of the layout).  Returns hipErrorInvalidValue when the inputs
+// are malformed or hold NaN/Inf, with t.bad set.
 hipError_t csr_tables_build(CsrTables& t, bool check, hipStream_t st);
-// structure and finiteness of sparse inputs (flag: device, 8-byte aligned
-// scratch); hipErrorInvalidValue when malformed or non-finite.  Synchronises.
 // exclusive prefixes over nb workgroups of V (<= 16) values each, and totals
 hipError_t launch_scan_parts(int64_t* part, int64_t nb, int V, int64_t* tot,
                              hipStream_t st);
 // *amax (cleared before) = max |v| over n values
 hipError_t launch_absmax(const float* v, int64_t n, float* amax,
                          hipStream_t st);
+// structure and finiteness of sparse inputs (flag: device, 8-byte aligned
+// scratch); hipErrorInvalidValue when malformed or non-finite.  Synchronises.
 hipError_t csr_validate(const CsrView& in, int64_t m, int64_t n, int64_t d,
                         int64_t nnzA, int64_t nnzB, int* flag,
                         hipStream_t st);

@@ -460,19 +460,8 @@ static hipError_t small_tables(W w, int64_t S, int64_t N, int L, double* tot,
   return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------
-// Tables of 2^L = 1024 .. 4096 slots, one workgroup of 2^L / 4 threads per
-// table, entirely on chip in the steps of the small tables: weights into LDS,
-// one lane per run of kRun items walks its prefixes, E_c and T, then each
-// thread F and the quanta of four slots in registers, the two lists by a scan
-// over the workgroup, and one search per slot.  X is read once and the
-// entries are written once, in slot order; the pipeline of the larger tables
-// (seven kernels with the lists in memory) took 95 us for 64 tables of 1000
-// items, mostly launches and their gaps, where this takes 12.  All tables of a
-// 1000 x 1000 x 50 plan 272 -> 120 us, of 4096 x 4096 x 1024 468 -> 277, of
-// 1e5 x 600 x 1000 (rows) 5.2 -> 3.0 ms.  4096 slots are the most whose
-// prefixes and lists fit the LDS (80 KB).
-// ---------------------------------------------------------------------------
+// tables of at most 2^kOnChipL slots are built on chip (k_small_tables,
+// k_mid_tables)
 constexpr int kOnChipL = 12;
 
 // Workgroups go to the 8 XCDs in turn; this remaps block b so that each
@@ -871,6 +860,19 @@ __global__ __launch_bounds__(256) void k_col_runoffsets(const double* rtot,
   if (threadIdx.x == 0) tot[seg] = e;
 }
 
+// ---------------------------------------------------------------------------
+// Tables of 2^L = 1024 .. 4096 slots, one workgroup of 2^L / 4 threads per
+// table, entirely on chip in the steps of the small tables: weights into LDS,
+// one lane per run of kRun items walks its prefixes, E_c and T, then each
+// thread F and the quanta of four slots in registers, the two lists by a scan
+// over the workgroup, and one search per slot.  X is read once and the
+// entries are written once, in slot order; the pipeline of the larger tables
+// (seven kernels with the lists in memory) took 95 us for 64 tables of 1000
+// items, mostly launches and their gaps, where this takes 12.  All tables of a
+// 1000 x 1000 x 50 plan 272 -> 120 us, of 4096 x 4096 x 1024 468 -> 277, of
+// 1e5 x 600 x 1000 (rows) 5.2 -> 3.0 ms.  4096 slots are the most whose
+// prefixes and lists fit the LDS (80 KB).
+// ---------------------------------------------------------------------------
 template <int L, class W>
 __global__ __launch_bounds__(1 << (L - 2)) void k_mid_tables(
     W w, int64_t N, double* tot, uint64_t* ent) {
