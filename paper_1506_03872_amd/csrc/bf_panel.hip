@@ -8,7 +8,7 @@ namespace mad {
 
 // The panel kernel keeps K in registers: up to 16 steps of 16 bytes per lane
 // for 64 rows (K = 256 in bf16, 512 in fp8: 128 VGPRs), in fp32 up to 32
-// steps (K = 256), for 32 rows from 20 on.  Longer vectors stay with the
+// steps (K = 256), for 32 rows above 20.  Longer vectors stay with the
 // LDS-tiled kernel.
 int panel_steps(int prec, int64_t d) {
   if (prec == kBF16 && d <= 256) return (int)((d + 15) / 16);

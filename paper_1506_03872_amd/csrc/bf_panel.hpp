@@ -34,8 +34,11 @@ constexpr int panel_tile_blocks(int ns) {
   return ns <= 4 ? 4 : ns <= 16 ? 2 : 1;
 }
 
-// blocks of 32 rows per wave: two while the rows fit in about 150 registers
-constexpr int panel_row_blocks(int ns) { return ns <= 19 ? 2 : 1; }
+// blocks of 32 rows per wave: two while the rows fit in 160 registers.  (fp32
+// at 65,536 x 65,536, pass B with two and with one: 9.02 and 9.12 ms at 19
+// steps, 9.41 and 9.61 at 20, 10.46 and 10.54 at 22, 11.53 and 11.47 at 24.
+// 20 is the last step count that is built singly.)
+constexpr int panel_row_blocks(int ns) { return ns <= 20 ? 2 : 1; }
 
 // rows of A per workgroup (4 waves)
 constexpr int panel_rows(int ns) { return 128 * panel_row_blocks(ns); }
