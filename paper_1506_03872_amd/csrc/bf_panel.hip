@@ -9,7 +9,10 @@ namespace mad {
 // The panel kernel keeps K in registers: up to 16 steps of 16 bytes per lane
 // for 64 rows (K = 256 in bf16, 512 in fp8: 128 VGPRs), in fp32 up to 32
 // steps (K = 256), for 32 rows above 20.  Longer vectors stay with the
-// LDS-tiled kernel.
+// LDS-tiled kernel.  Every step count up to 20 is built in fp32, whose time
+// follows it (65,536 x 65,536: 8.57 ms at 18 steps, 9.02 at 19, 9.41 at 20);
+// the 50 kernels of all precisions are 28 s of the build's 33 on 8 cores and
+// 4.6 MB of the library.
 int panel_steps(int prec, int64_t d) {
   if (prec == kBF16 && d <= 256) return (int)((d + 15) / 16);
   if (prec == kFP8 && d <= 512) return (int)((d + 63) / 64) * 2;
