@@ -72,3 +72,38 @@ def test_results_and_trim(gpu):
     # all of it is the device's again (torch's own blocks of this test: less
     # than 64 MiB)
     assert torch.cuda.mem_get_info()[0] >= free0 - (64 << 20)
+
+
+def test_threads_on_their_own_streams(gpu):
+    # two threads make and destroy plans, each on a stream of its own, from
+    # the one list
+    import threading
+
+    import torch
+
+    import paper_1506_03872_amd as mad
+    fs = [f for q, f in enumerate(calls()) if q not in (2, 4)]  # not MIPS
+    mad.trim_memory()
+    fresh = [f() for f in fs]
+    torch.cuda.synchronize()
+    wrong = []
+
+    def work(order):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            for q in order:
+                got = fs[q]()
+                for k in fresh[q]:
+                    if not torch.equal(got[k], fresh[q][k]):
+                        wrong.append((q, k))
+            st.synchronize()
+    n = len(fs)
+    ts = [threading.Thread(target=work, args=([q % n for q in order],))
+          for order in (range(3 * n), range(3 * n, 0, -1))]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    torch.cuda.synchronize()
+    assert not wrong
+    mad.trim_memory()
